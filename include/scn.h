@@ -287,12 +287,14 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
  * HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same computation and result, bit for bit, with the
  * forward's scratch (the ground-state terms and the packed weights) in a
- * static device array of scn_conv_fwd_noalloc_max_bytes() bytes (8 MiB) that
- * the library holds on each GPU it runs on until the process ends.  The call
+ * static device array (16 MiB: split weights take 6 bytes each) that the
+ * library holds on each GPU it runs on until the process ends.  The call
  * allocates nothing; the caller still passes every input and output.
- * Scratch needed: 4*((K+1)*NcP rounded up to 64 floats + K*NcP*RkP) bytes
- * with NcP = 64*ceil(Cout/64) and RkP = 16*ceil(Cin/16); every 3x3x3 layer
- * with Cin, Cout <= 256 fits.  Larger shapes return SCN_ERR_WORKSPACE before
+ * Shapes are accepted while their weights in fp32,
+ * 4*((K+1)*NcP rounded up to 64 floats + K*NcP*RkP) bytes with
+ * NcP = 64*ceil(Cout/64) and RkP = 16*ceil(Cin/16), are at most
+ * scn_conv_fwd_noalloc_max_bytes() (8 MiB); every 3x3x3 layer with Cin, Cout
+ * <= 256 fits.  Larger shapes return SCN_ERR_WORKSPACE before
  * any device work.  All calls on one GPU share its array: calls that overlap
  * on a GPU (on different streams, or from several threads without stream
  * order between them) race and give undefined results; calls ordered on one
@@ -302,7 +304,7 @@ scn_status scn_conv_fwd_noalloc(const scn_rulebook* rb, const float* x, const fl
                                 const float* W, const float* bias, int32_t Cin, int32_t Cout,
                                 uint32_t flags, float* y, float* g_out, hipStream_t stream);
 
-/* Size in bytes of the static scratch array of scn_conv_fwd_noalloc. */
+/* The bound of scn_conv_fwd_noalloc on a layer's fp32 weights, in bytes. */
 size_t scn_conv_fwd_noalloc_max_bytes(void);
 
 /* Bytes of device workspace scn_conv_bwd needs for this rulebook and shape. */

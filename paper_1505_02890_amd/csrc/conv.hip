@@ -8,7 +8,9 @@
 //     g_pre   = B + sum_k g_in W_k,
 // so only the active blocks are gathered and multiplied.
 //
-// Gather kernel (forward and input gradient).  A work-group of four waves owns
+// Stride-1 rulebooks (forward and input gradient) go to tile.hip.
+//
+// Gather kernel (forward and input gradient of strided rulebooks).  A work-group of four waves owns
 // a tile of accumulator rows (output rows for the forward, input ranks for the
 // input gradient) and 64 columns; the accumulators live in LDS and each wave
 // owns 16 of the columns.  For each offset k the tile's pairs form one
@@ -34,6 +36,7 @@
 #include <mutex>
 
 #include "scn_internal.h"
+#include "tile.h"
 
 namespace scn {
 namespace {
@@ -547,330 +550,6 @@ scn_status launch_gather(GatherArgs a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Dense-block forward (stride-1 rulebooks)
-// ---------------------------------------------------------------------------
-// The rulebook sorts the output rows by neighbour mask; cut into blocks of 32
-// (DENSE_ROWS) the rows of a block mostly share one mask.  One wave owns a
-// block and 64 output columns, with its 32 x 64 accumulators in registers:
-// for each offset k of the union of the block's masks it gathers the block's
-// 32 input rows (a row without offset k contributes zero) and multiplies them
-// by W_k, 64 input channels at a time.  Lane (n16, q) gathers block rows n16
-// and 16 + n16; a row's input at offset k is entry popcount(mask & (2^k - 1))
-// of its output-major neighbour list.  There is no scatter: the rows of a
-// block are distinct outputs, and the epilogue writes each once.  Rows hold
-// x - g_in, so y = g_pre + sum over active offsets of (x - g_in) W_k.  The
-// next (offset, channel chunk)'s rows are loaded while the current one is
-// multiplied.
-struct DenseArgs {
-  const float* x;          // [a_in][Cin]
-  const float* g_in;       // [Cin]
-  const float* Wp;         // packed like GatherArgs::Wp (fragment order, transposed W)
-  const float* add;        // [Cout] g_pre
-  const int32_t* nb;       // rulebook fnb
-  const uint32_t* nb_off;  // rulebook fnb_off
-  const int32_t* fperm;    // rulebook fperm
-  const uint32_t* fmask;   // rulebook fmask
-  float* y;                // [a_out][Cout]
-  int64_t a_out, nblk;
-  int K, Cin, Cout, NcP, relu, dvec_ok;
-};
-
-// One block row as the lane sees it: its mask and the start of its list.
-struct DRow {
-  uint32_t m, off;
-};
-
-// The rows of one (offset, 64-channel chunk) item: lane (n16, q) holds
-// channels 64ch + 16t + 4q .. +3 of block rows n16 and 16 + n16.
-template <int TC>
-struct DRows {
-  float4 v[2][TC];
-  int r0, r1;
-};
-
-__device__ inline int dense_src(const DenseArgs& a, const DRow& w, int k) {
-  // the list entry is read unconditionally (the list has a spare entry)
-  const int r = a.nb[w.off + __popc(w.m & ((1u << k) - 1u))];
-  return (w.m >> k) & 1u ? r : -1;
-}
-
-template <int NKT, bool VEC>
-__device__ inline DRows<(NKT < 4 ? NKT : 4)> dense_rows(const DenseArgs& a, const DRow& w0,
-                                                        const DRow& w1, int k, int ch, int q) {
-  constexpr int TC = NKT < 4 ? NKT : 4;
-  DRows<TC> R;
-  R.r0 = dense_src(a, w0, k);
-  R.r1 = dense_src(a, w1, k);
-  const float* p0 = a.x + (int64_t)(R.r0 >= 0 ? R.r0 : 0) * a.Cin;
-  const float* p1 = a.x + (int64_t)(R.r1 >= 0 ? R.r1 : 0) * a.Cin;
-#pragma unroll
-  for (int t = 0; t < TC; ++t) {
-    const int c = 64 * ch + 16 * t + 4 * q;
-    if (VEC) {
-      // channels past Cin read channel 0; their weights are zero
-      const int cc = c < a.Cin ? c : 0;
-      R.v[0][t] = *reinterpret_cast<const float4*>(p0 + cc);
-      R.v[1][t] = *reinterpret_cast<const float4*>(p1 + cc);
-    } else {
-      float e0[4], e1[4];
-#pragma unroll
-      for (int z = 0; z < 4; ++z) {
-        const int cz = c + z < a.Cin ? c + z : 0;
-        e0[z] = p0[cz];
-        e1[z] = p1[cz];
-      }
-      R.v[0][t] = make_float4(e0[0], e0[1], e0[2], e0[3]);
-      R.v[1][t] = make_float4(e1[0], e1[1], e1[2], e1[3]);
-    }
-  }
-  return R;
-}
-
-// rows of an item whose input rows are already known
-template <int NKT, bool VEC>
-__device__ inline DRows<(NKT < 4 ? NKT : 4)> dense_rows_i(const DenseArgs& a, int r0, int r1,
-                                                          int ch, int q) {
-  constexpr int TC = NKT < 4 ? NKT : 4;
-  DRows<TC> R;
-  R.r0 = r0;
-  R.r1 = r1;
-  const float* p0 = a.x + (int64_t)(r0 >= 0 ? r0 : 0) * a.Cin;
-  const float* p1 = a.x + (int64_t)(r1 >= 0 ? r1 : 0) * a.Cin;
-#pragma unroll
-  for (int t = 0; t < TC; ++t) {
-    const int c = 64 * ch + 16 * t + 4 * q;
-    if (VEC) {
-      const int cc = c < a.Cin ? c : 0;
-      R.v[0][t] = *reinterpret_cast<const float4*>(p0 + cc);
-      R.v[1][t] = *reinterpret_cast<const float4*>(p1 + cc);
-    } else {
-      float e0[4], e1[4];
-#pragma unroll
-      for (int z = 0; z < 4; ++z) {
-        const int cz = c + z < a.Cin ? c + z : 0;
-        e0[z] = p0[cz];
-        e1[z] = p1[cz];
-      }
-      R.v[0][t] = make_float4(e0[0], e0[1], e0[2], e0[3]);
-      R.v[1][t] = make_float4(e1[0], e1[1], e1[2], e1[3]);
-    }
-  }
-  return R;
-}
-
-template <int NKT, bool VEC>
-__global__ void __launch_bounds__(NT) dense_fwd_kernel(DenseArgs a) {
-  constexpr int TC = NKT < 4 ? NKT : 4;        // 16-channel steps per chunk
-  constexpr int NCH = (NKT + 3) / 4;           // 64-channel chunks
-  __shared__ float gsh[16 * NKT];  // g_in, zero past Cin (those weights are zero)
-  for (int c = threadIdx.x; c < 16 * NKT; c += NT) gsh[c] = c < a.Cin ? a.g_in[c] : 0.f;
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (b >= a.nblk) return;
-  const int cb = blockIdx.y;
-  // Two lane layouts.  MFMA layout: lane (n16, q) = n16 + 16q holds row n16
-  // (and 16 + n16), channels 4q .. 4q + 3 of each 16; the operand fixes it.
-  // Load layout: lane (rl, cq) = 4rl + cq loads row rl (and 16 + rl),
-  // channels 4cq .. 4cq + 3, so four adjacent lanes read one row's 64
-  // contiguous bytes (in the MFMA layout four adjacent lanes read four
-  // rows, and the L1 serves each 16-byte piece on its own).  The rows are
-  // gathered in the load layout and moved to the MFMA layout by ds_bpermute.
-  const int n16 = lane & 15, q = lane >> 4;
-  const int rl = lane >> 2, cq = lane & 3;
-  const int from = (n16 * 4 + q) * 4;  // bpermute address: MFMA lane <- load lane 4 n16 + q
-  const int ncb = a.NcP >> 6;
-  const int64_t pos0 = b * DENSE_ROWS + n16, pos1 = pos0 + 16;      // MFMA layout
-  const int64_t lpos0 = b * DENSE_ROWS + rl, lpos1 = lpos0 + 16;    // load layout
-  const int o0 = pos0 < a.a_out ? a.fperm[pos0] : 0, o1 = pos1 < a.a_out ? a.fperm[pos1] : 0;
-  const int lo0 = lpos0 < a.a_out ? a.fperm[lpos0] : 0, lo1 = lpos1 < a.a_out ? a.fperm[lpos1] : 0;
-  DRow w0, w1;
-  w0.m = lpos0 < a.a_out ? a.fmask[lpos0] : 0u;
-  w1.m = lpos1 < a.a_out ? a.fmask[lpos1] : 0u;
-  w0.off = a.nb_off[lo0];
-  w1.off = a.nb_off[lo1];
-  uint32_t u = w0.m | w1.m;
-#pragma unroll
-  for (int d = 4; d < 64; d <<= 1) u |= (uint32_t)__shfl_xor((int)u, d, 64);
-  const uint32_t U = (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
-  v4f acc[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[r][g] = v4f{0.f, 0.f, 0.f, 0.f};
-  if (U) {
-    // item = (offset k, channel chunk ch), in order; `rest` holds the offsets
-    // after k; past the last item an item stays where it is (its loads are in
-    // bounds and unused)
-    struct Item {
-      int k, ch;
-      uint32_t rest;
-    };
-    auto advance = [&](Item& t) {
-      if (t.ch + 1 < NCH) {
-        ++t.ch;
-      } else if (t.rest) {
-        t.k = __builtin_ctz(t.rest);
-        t.rest &= t.rest - 1;
-        t.ch = 0;
-      }
-    };
-    Item c{__builtin_ctz(U), 0, U & (U - 1)};
-    Item n = c;
-    advance(n);
-    Item nn = n;
-    advance(nn);
-    const int nit = __builtin_popcount(U) * NCH;
-    int n0 = dense_src(a, w0, n.k), n1 = dense_src(a, w1, n.k);
-    DRows<TC> cur = dense_rows_i<NKT, VEC>(a, dense_src(a, w0, c.k), dense_src(a, w1, c.k), 0, cq);
-    DRows<TC> nxt;
-    int nn0 = 0, nn1 = 0;
-    for (int it = 0; it < nit; ++it) {
-      const int ch = c.ch;
-      const float* wp = a.Wp + (((int64_t)c.k * ncb + cb) * 4) * (NKT * 256) + lane * 4;
-      auto wload = [&](int t, float4 (&A)[4]) {
-        const int tg = 4 * ch + t < NKT ? 4 * ch + t : NKT - 1;  // past NKT: never used
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          A[g] = *reinterpret_cast<const float4*>(wp + (int64_t)g * (NKT * 256) + tg * 256);
-      };
-      // the next item's rows and the indices after it: issued after this
-      // item's last weight load, so the waits for the weights leave them in
-      // flight
-      auto prefetch = [&]() {
-        nxt = dense_rows_i<NKT, VEC>(a, n0, n1, n.ch, cq);
-        nn0 = dense_src(a, w0, nn.k);
-        nn1 = dense_src(a, w1, nn.k);
-      };
-      auto mult = [&](int t, const float4 (&A)[4]) {
-        const int tg = 4 * ch + t;
-        // x - g_in, zero for an absent row, in the load layout; then to the
-        // MFMA layout
-        const float4 gq = *reinterpret_cast<const float4*>(&gsh[16 * tg + 4 * cq]);
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 d0 = cur.v[0][t], d1 = cur.v[1][t];
-        d0.x -= gq.x; d0.y -= gq.y; d0.z -= gq.z; d0.w -= gq.w;
-        d1.x -= gq.x; d1.y -= gq.y; d1.z -= gq.z; d1.w -= gq.w;
-        const float4 L0 = cur.r0 >= 0 ? d0 : z, L1 = cur.r1 >= 0 ? d1 : z;
-        auto perm = [&](float v) {
-          return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
-        };
-        const float4 B0 = make_float4(perm(L0.x), perm(L0.y), perm(L0.z), perm(L0.w));
-        const float4 B1 = make_float4(perm(L1.x), perm(L1.y), perm(L1.z), perm(L1.w));
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          acc[0][g] = mfma4(A[g].x, B0.x, acc[0][g]);
-          acc[1][g] = mfma4(A[g].x, B1.x, acc[1][g]);
-          acc[0][g] = mfma4(A[g].y, B0.y, acc[0][g]);
-          acc[1][g] = mfma4(A[g].y, B1.y, acc[1][g]);
-          acc[0][g] = mfma4(A[g].z, B0.z, acc[0][g]);
-          acc[1][g] = mfma4(A[g].z, B1.z, acc[1][g]);
-          acc[0][g] = mfma4(A[g].w, B0.w, acc[0][g]);
-          acc[1][g] = mfma4(A[g].w, B1.w, acc[1][g]);
-        }
-      };
-      // weights two 16-channel steps ahead of their products (two register
-      // sets, alternating)
-      float4 A0[4], A1[4];
-      wload(0, A0);
-      if (TC > 1) wload(1, A1);
-      if (TC <= 2) prefetch();
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int t = 0; t < TC; ++t) {
-        if (NCH > 1 && 4 * ch + t >= NKT) {
-          // a last chunk shorter than the step that issues the prefetch
-          // (t = TC - 3) issues it here, so the next item's rows are loaded
-          if (t <= TC - 3) prefetch();
-          break;
-        }
-        // step t's products, then step t + 2's weights into the set just read
-        if (t & 1) mult(t, A1); else mult(t, A0);
-        if (t + 2 < TC) {
-          if (t & 1) wload(t + 2, A1); else wload(t + 2, A0);
-          if (t + 2 == TC - 1) prefetch();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      c = n;
-      n = nn;
-      advance(nn);
-      n0 = nn0;
-      n1 = nn1;
-      cur = nxt;
-    }
-  }
-  // epilogue: rows n16 and 16 + n16 of the block, columns 64cb + 16g + 4q .. +3
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int64_t pos = r ? pos1 : pos0;
-    if (pos >= a.a_out) continue;
-    float* dp = a.y + (int64_t)(r ? o1 : o0) * a.Cout;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = 64 * cb + 16 * g + 4 * q;
-      if (col >= a.Cout) continue;
-      float e[4] = {acc[r][g][0], acc[r][g][1], acc[r][g][2], acc[r][g][3]};
-#pragma unroll
-      for (int u2 = 0; u2 < 4; ++u2) {
-        if (col + u2 < a.Cout) e[u2] += a.add[col + u2];
-        if (a.relu) e[u2] = e[u2] > 0.f ? e[u2] : 0.f;
-      }
-      if (a.dvec_ok && col + 3 < a.Cout) {
-        // a streaming store: y is read only by later calls (kernel 2.669 ->
-        // 2.653 ms on the 1M-site layer)
-        __builtin_nontemporal_store(v4f{e[0], e[1], e[2], e[3]}, reinterpret_cast<v4f*>(dp + col));
-      } else {
-#pragma unroll
-        for (int u2 = 0; u2 < 4; ++u2)
-          if (col + u2 < a.Cout) dp[col + u2] = e[u2];
-      }
-    }
-  }
-}
-
-typedef void (*DenseFn)(DenseArgs);
-
-template <int NKT>
-DenseFn pick_dense(bool vec) {
-  return vec ? dense_fwd_kernel<NKT, true> : dense_fwd_kernel<NKT, false>;
-}
-
-DenseFn dense_fn(int nkt, bool vec) {
-  switch (nkt) {
-    case 1: return pick_dense<1>(vec);
-    case 2: return pick_dense<2>(vec);
-    case 3: return pick_dense<3>(vec);
-    case 4: return pick_dense<4>(vec);
-    case 5: return pick_dense<5>(vec);
-    case 6: return pick_dense<6>(vec);
-    case 7: return pick_dense<7>(vec);
-    case 8: return pick_dense<8>(vec);
-    case 9: return pick_dense<9>(vec);
-    case 10: return pick_dense<10>(vec);
-    case 11: return pick_dense<11>(vec);
-    case 12: return pick_dense<12>(vec);
-    case 13: return pick_dense<13>(vec);
-    case 14: return pick_dense<14>(vec);
-    case 15: return pick_dense<15>(vec);
-    default: return pick_dense<16>(vec);
-  }
-}
-
-scn_status launch_dense(DenseArgs a, hipStream_t st) {
-  if (a.a_out <= 0 || a.nblk <= 0) return SCN_OK;
-  const bool vec = ((a.Cin & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0) &&
-                   ((reinterpret_cast<uintptr_t>(a.g_in) & 15) == 0);
-  a.dvec_ok = ((a.Cout & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0);
-  const int nkt = (int)ceil_div(a.Cin, 16);
-  const int64_t nwg = ceil_div(a.nblk, NT / 64);
-  hipLaunchKernelGGL(dense_fn(nkt, vec), dim3((unsigned)nwg, (unsigned)(a.NcP / 64)), dim3(NT), 0,
-                     st, a);
-  SCN_LAUNCH_CHECK();
-  return SCN_OK;
-}
-
-// ---------------------------------------------------------------------------
 // Backward helpers
 // ---------------------------------------------------------------------------
 constexpr int RB_ROWS = 1024;  // rows per column-sum block
@@ -1326,7 +1005,7 @@ constexpr int DW_ROUNDS = 4;
 
 struct BwdLayout {
   int64_t chp, maxc, nblk;
-  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, total;
+  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, o_pad, pad, total;
 };
 
 BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) {
@@ -1356,9 +1035,13 @@ BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) 
   L.o_T = cur;
   cur += al((size_t)rb->K * Cout * 4);
   L.o_wp = cur;
-  cur += al((size_t)rb->K * ceil_div(Cin, 64) * 64 * ceil_div(Cout, 16) * 16 * 4);
+  cur += al(rb->s == 1 ? tile_pack_bytes(rb->K, Cout, Cin)
+                       : (size_t)rb->K * ceil_div(Cin, 64) * 64 * ceil_div(Cout, 16) * 16 * 4);
   L.o_gz = cur;
-  cur += al((size_t)rb->K * ceil_div(Cin, 64) * 64 * 4);
+  cur += al(std::max((size_t)rb->K * ceil_div(Cin, 64) * 64, (size_t)TILE_PAD) * 4);
+  L.o_pad = cur;
+  L.pad = rb->s == 1 ? tile_pad_bytes(rb->a_out, Cout) : 0;
+  cur += al(L.pad);
   L.total = cur;
   return L;
 }
@@ -1387,6 +1070,7 @@ static scn_status timer_mark(TimedKernel k, int end, hipStream_t st) {
 struct FwdScratch {
   int RkP, NcP;
   size_t gw_bytes, total;
+  size_t bound;  // what scn_conv_fwd_noalloc limits: fp32 weights on padded tiles
 };
 
 static FwdScratch fwd_scratch(const scn_rulebook* rb, int Cin, int Cout) {
@@ -1394,7 +1078,9 @@ static FwdScratch fwd_scratch(const scn_rulebook* rb, int Cin, int Cout) {
   f.RkP = (int)ceil_div(Cin, 16) * 16;
   f.NcP = (int)ceil_div(Cout, 64) * 64;
   f.gw_bytes = ((size_t)(rb->K + 1) * f.NcP * sizeof(float) + 255) & ~size_t(255);
-  f.total = f.gw_bytes + (size_t)rb->K * f.NcP * f.RkP * sizeof(float);
+  f.total = f.bound = f.gw_bytes + (size_t)rb->K * f.NcP * f.RkP * sizeof(float);
+  if (rb->s == 1)
+    f.total = f.gw_bytes + TILE_PAD * sizeof(float) + tile_pack_bytes(rb->K, Cin, Cout);
   return f;
 }
 
@@ -1417,11 +1103,49 @@ static scn_status fwd_check(const char* who, const scn_rulebook* rb, const float
 static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g_in,
                           const float* W, const float* bias, int32_t Cin, int32_t Cout,
                           uint32_t flags, float* y, float* g_out, hipStream_t st,
-                          const FwdScratch& fs, float* gw) {
+                          const FwdScratch& fs, float* gw, float* pad) {
   const int relu = (flags & SCN_RELU) ? 1 : 0;
   const int RkP = fs.RkP, NcP = fs.NcP;
   float* const gpre = gw + (size_t)rb->K * NcP;
   float* Wp = reinterpret_cast<float*>(reinterpret_cast<char*>(gw) + fs.gw_bytes);
+  if (rb->s == 1) {
+    float* const sub = Wp;  // the shifted rows' g_in, then the split weights
+    uint32_t* const Ws = reinterpret_cast<uint32_t*>(Wp + TILE_PAD);
+    if (scn_status rc = tile_pack(W, (int64_t)Cin * Cout, Cout, 1, rb->K, Cin, Cout, g_in, bias,
+                                  relu, Ws, sub, gpre, g_out, st))
+      return rc;
+    TileArgs t{};
+    t.src = x;
+    t.ld = Cin;
+    t.sub = sub;
+    t.subtract = 1;
+    t.Wp = Ws;
+    t.W = W;
+    t.wk = (int64_t)Cin * Cout;
+    t.wj = Cout;
+    t.wn = 1;
+    t.gidx = rb->in_rows;
+    t.aidx = rb->out_rows;
+    t.tpos = rb->otile;
+    t.nb = rb->fnb;
+    t.nb_off = rb->fnb_off;
+    t.fperm = rb->fperm;
+    t.fmask = rb->fmask;
+    t.nsrc = rb->a_in;
+    t.npairs = rb->n_pairs;
+    t.ntile = ceil_div(rb->a_out, TILE);
+    t.nrows = rb->a_out;
+    t.K = rb->K;
+    t.Rk = Cin;
+    t.Nc = Cout;
+    t.add = gpre;
+    t.relu = relu;
+    t.dst = y;
+    scn_status rc;
+    if (pad && (rc = tile_pad(t, pad, st))) return rc;
+    if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = launch_tile(t, st))) return rc;
+    return timer_mark(TK_FWD, 1, st);
+  }
   hipLaunchKernelGGL(pack_w_kernel, dim3((unsigned)ceil_div((int64_t)rb->K * NcP * RkP, 256)),
                      dim3(256), 0, st, W, rb->K, Cin, Cout, 1, RkP, NcP, Wp);
   SCN_LAUNCH_CHECK();
@@ -1431,28 +1155,6 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
   hipLaunchKernelGGL(ground_pre_kernel, dim3((unsigned)ceil_div(Cout, 64)), dim3(64), 0, st, gw,
                      NcP, bias, rb->K, Cout, relu, gpre, g_out);
   SCN_LAUNCH_CHECK();
-  if (rb->fnb) {
-    DenseArgs d{};
-    d.x = x;
-    d.g_in = g_in;
-    d.Wp = Wp;
-    d.add = gpre;
-    d.nb = rb->fnb;
-    d.nb_off = rb->fnb_off;
-    d.fperm = rb->fperm;
-    d.fmask = rb->fmask;
-    d.y = y;
-    d.a_out = rb->a_out;
-    d.nblk = rb->n_fblocks;
-    d.K = rb->K;
-    d.Cin = Cin;
-    d.Cout = Cout;
-    d.NcP = NcP;
-    d.relu = relu;
-    scn_status rc;
-    if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = launch_dense(d, st))) return rc;
-    return timer_mark(TK_FWD, 1, st);
-  }
   GatherArgs a{};
   a.src = x;
   a.gidx = rb->in_rows;
@@ -1479,7 +1181,8 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
 // held until the process ends.  In host code its name is not a device
 // address; the address each device gives it (hipGetSymbolAddress, once per
 // device) is what kernels and copies get.
-constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(8) << 20;
+constexpr size_t NOALLOC_MAX_BYTES = size_t(8) << 20;
+constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(16) << 20;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 static std::mutex g_scratch_mutex;
@@ -1518,7 +1221,15 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
   const FwdScratch fs = fwd_scratch(rb, Cin, Cout);
   float* gw = nullptr;
   const Allocator al = current_allocator();
-  scn_status rc = dalloc(reinterpret_cast<void**>(&gw), fs.total, st, al);
+  // without room for padded rows, the rows are gathered as they are
+  const size_t at = (fs.total + 255) & ~size_t(255);
+  size_t pad = rb->s == 1 ? tile_pad_bytes(rb->a_in, Cin) : 0;
+  scn_status rc = dalloc(reinterpret_cast<void**>(&gw), pad ? at + pad : fs.total, st, al);
+  if (rc == SCN_ERR_NOMEM && pad) {
+    clear_error();
+    pad = 0;
+    rc = dalloc(reinterpret_cast<void**>(&gw), fs.total, st, al);
+  }
   if (rc) return rc;
   struct Free {
     float* p;
@@ -1526,10 +1237,11 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
     Allocator al;
     ~Free() { dfree(p, s, al); }
   } free_gw{gw, st, al};
-  return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs, gw);
+  return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs, gw,
+                 pad ? reinterpret_cast<float*>(reinterpret_cast<char*>(gw) + at) : nullptr);
 }
 
-size_t scn_conv_fwd_noalloc_max_bytes(void) { return NOALLOC_SCRATCH_BYTES; }
+size_t scn_conv_fwd_noalloc_max_bytes(void) { return NOALLOC_MAX_BYTES; }
 
 scn_status scn_set_kernel_timer(const hipEvent_t* events) {
   for (int i = 0; i < 6; ++i) g_kernel_timer[i] = events ? events[i] : nullptr;
@@ -1544,16 +1256,16 @@ scn_status scn_conv_fwd_noalloc(const scn_rulebook* rb, const float* x, const fl
   if (scn_status rc0 = fwd_check("scn_conv_fwd_noalloc", rb, x, g_in, W, Cin, Cout, y, g_out))
     return rc0;
   const FwdScratch fs = fwd_scratch(rb, Cin, Cout);
-  if (fs.total > NOALLOC_SCRATCH_BYTES) {
+  if (fs.bound > NOALLOC_MAX_BYTES || fs.total > NOALLOC_SCRATCH_BYTES) {
     set_error("scn_conv_fwd_noalloc: K=%d Cin=%d Cout=%d needs %zu bytes of scratch, more than "
               "the %zu the library holds",
-              rb->K, Cin, Cout, fs.total, NOALLOC_SCRATCH_BYTES);
+              rb->K, Cin, Cout, fs.bound, NOALLOC_MAX_BYTES);
     return SCN_ERR_WORKSPACE;
   }
   void* base = nullptr;
   if (scn_status rc0 = noalloc_scratch(&base)) return rc0;
   return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs,
-                 static_cast<float*>(base));
+                 static_cast<float*>(base), nullptr);
 }
 
 size_t scn_conv_bwd_workspace_bytes(const scn_rulebook* rb, int32_t Cin, int32_t Cout,
@@ -1616,7 +1328,37 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
   SCN_LAUNCH_CHECK();
 
   // input gradient: accumulate over input ranks with W_k^T
-  if (dx && rb->a_in > 0) {
+  if (dx && rb->a_in > 0 && rb->s == 1) {
+    scn_status rc = tile_pack(W, (int64_t)Cin * Cout, 1, Cout, K, Cout, Cin, nullptr,
+                              nullptr, 0, reinterpret_cast<uint32_t*>(wpack), gzero, nullptr,
+                              nullptr, st);
+    if (rc) return rc;
+    TileArgs a{};
+    a.src = dyb;
+    a.ld = Cout;
+    a.sub = gzero;
+    a.Wp = reinterpret_cast<uint32_t*>(wpack);
+    a.W = W;
+    a.wk = (int64_t)Cin * Cout;
+    a.wj = 1;
+    a.wn = Cout;
+    a.gidx = rb->out_rows;
+    a.aidx = rb->in_rank;
+    a.tpos = rb->itile;
+    a.nsrc = rb->a_out;
+    a.npairs = rb->n_pairs;
+    a.ntile = rb->n_itiles;
+    a.nrows = rb->a_in;
+    a.K = K;
+    a.Rk = Cout;
+    a.Nc = Cin;
+    a.dst = dx;
+    a.wmap = rb->input_sorted ? nullptr : rb->perm;
+    if (L.pad && (rc = tile_pad(a, reinterpret_cast<float*>(base + L.o_pad), st))) return rc;
+    if ((rc = timer_mark(TK_DX, 0, st)) || (rc = launch_tile(a, st)) ||
+        (rc = timer_mark(TK_DX, 1, st)))
+      return rc;
+  } else if (dx && rb->a_in > 0) {
     GatherArgs a{};
     a.src = dyb;
     a.gidx = rb->out_rows;

@@ -1,0 +1,64 @@
+// The tile contraction (tile.hip): rows gathered through a rulebook times W,
+// accumulated per destination row.  Serves the forward and the input gradient
+// of stride-1 rulebooks.
+#pragma once
+
+#include "scn_internal.h"
+
+namespace scn {
+
+struct TileArgs {
+  const float* src;      // gathered rows [nsrc][ld], Rk channels each
+  int ld;
+  const float* sub;      // [TILE_PAD] subtracted from every row (zero past Rk); 16-byte aligned
+  const uint32_t* Wp;    // split weights (tile_pack)
+  const float* W;        // the weights themselves: W_k(j, n) = W[k*wk + j*wj + n*wn]
+  int64_t wk, wj, wn;
+  // Rows from pair lists (nb == null): list k of the rulebook ascends by
+  // accumulator row, tpos[k*ntile + t] starts the part of the tile of rows
+  // [64t, 64t + 64).
+  const int32_t* gidx;   // per pair: row of src
+  const int32_t* aidx;   // per pair: accumulator row
+  const int64_t* tpos;   // [K*ntile + 1]
+  // Rows from the dense forward view: position p of the mask-sorted order is
+  // output row fperm[p], its inputs nb[nb_off[row] ..] in offset order.
+  const int32_t* nb;
+  const uint32_t* nb_off;
+  const int32_t* fperm;
+  const uint32_t* fmask;
+  int64_t nsrc;          // rows of src
+  int64_t npairs;        // pairs of all lists
+  int64_t ntile;         // tiles of 64 rows
+  int64_t nrows;         // accumulator rows
+  int K, Rk, Nc;
+  const float* add;      // [Nc] added to every row, or null
+  int relu;
+  int subtract;          // whether rows are shifted by sub (else sub is all zeros)
+  float* dst;            // [nrows][Nc]
+  const int32_t* wmap;   // dst row of accumulator row r (null = identity)
+};
+
+constexpr int TILE_PAD = 256;  // floats of TileArgs::sub (Rk <= 256, padded to whole chunks)
+
+// 16-channel steps of a reduction of Rk channels, and the bytes of its split
+// weights.
+int tile_steps(int Rk);
+size_t tile_pack_bytes(int K, int Rk, int Nc);
+
+// Splits W_k(j, n) into a.Wp's layout; fills sub[0 .. TILE_PAD) with g (zeros
+// if null or past Rk).  With g_pre (else null): g_pre = bias + sum_k g W_k and
+// g_out = act(g_pre).
+scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
+                     const float* g, const float* bias, int relu, uint32_t* Wp, float* sub,
+                     float* g_pre, float* g_out, hipStream_t st);
+
+// Rows whose channel count is no multiple of 16 are copied to a multiple
+// first where there is room (tile_pad_bytes, 0 if none is needed): a's rows
+// become out's.  (Gathered as they are, float by float, a 35 -> 50 layer on
+// 60k tetrahedral sites took 89 us.)
+size_t tile_pad_bytes(int64_t rows, int Rk);
+scn_status tile_pad(TileArgs& a, float* out, hipStream_t st);
+
+scn_status launch_tile(const TileArgs& a, hipStream_t st);
+
+}  // namespace scn

@@ -1,0 +1,774 @@
+// The tile contraction of stride-1 rulebooks, on the bf16 matrix cores in
+// three-way split fp32 (split.h):
+//   dst[row] = act(add + sum over offsets k of (src[row_k] - sub) W_k)
+// where row_k is the row that offset k gives the accumulator row, if any.
+//
+// One wave owns 64 accumulator rows and 64 columns, its 64 x 64 accumulators
+// in registers: no scatter, one write per row.  It walks items (offset,
+// channel chunk); an item's 64 rows are gathered while the item before is
+// multiplied, turned through LDS into the layout of the MFMA operand, split
+// and multiplied by the split W_k.  A row without the item's offset reads
+// `sub` itself, so its difference is exactly zero.
+//
+// What bounds it: per 16 channels a wave issues 24 MFMAs of 32 clocks (768)
+// against about 110 vector instructions (440) and, per CU, 10 KB of LDS reads
+// and 6 KB of L1 traffic per wave.  With everything in LDS the loop runs at
+// 1570 TFLOP/s of bf16 (the MFMAs alone at 2190); on the 1M-site 64 -> 64
+// layer the input gradient, whose tiles are full, runs at 985 (1.36 ms; 2.11
+// on the fp32 instruction with LDS accumulators), the clock at 1.95 GHz.
+// Gathering 1024 fixed rows takes 0.09 ms off it, no gather at all 0.2.
+// Measured and not kept there: LDS reads and splits of the next step
+// interleaved with a step's MFMAs (1.33 ms against 1.23 left in blocks, before
+// the sums went in two levels: the two waves of a SIMD then contend instead of
+// alternating), eight waves sharing weights (1.32), every wave loading its
+// weights from L2 (1.6), four steps per item (1.31), raised priority around
+// the MFMAs (1.37).
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
+#include "split.h"
+#include "tile.h"
+
+namespace scn {
+namespace {
+
+constexpr int NT = 256;  // threads per work-group (4 waves)
+
+// Fewer (tile, column block) items than this: four waves share each.
+constexpr int64_t TILE_SPLIT = 2048;
+
+// Channels go in chunks of one or two 16-channel steps, none of them padded.
+// (Longer chunks take registers that a third or second work-group per CU
+// needs: four steps per item, two work-groups, 2.71 ms for the forward of the
+// benchmark's layer against 2.60.)
+int chunk_steps(int Rk) { return ceil_div(Rk, 16) % 2 ? 1 : 2; }
+
+constexpr int PRE_COLS = 8;
+
+// Wp[k][cb][step][ct][part][lane][4 words]: the eight reduction entries
+// j = 16 step + 8 (lane >> 5) + 0..7 of column n = 64 cb + 32 ct + (lane & 31).
+__global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__ W, int64_t wk,
+                                                       int64_t wj, int64_t wn, int K, int Rk,
+                                                       int Nc, int nst, int ncb,
+                                                       const float* __restrict__ g,
+                                                       const float* __restrict__ bias, int relu,
+                                                       v4u* __restrict__ Wp,
+                                                       float* __restrict__ sub, int np,
+                                                       float* __restrict__ g_pre,
+                                                       float* __restrict__ g_out) {
+  if ((int)blockIdx.x >= np) {
+    // g_pre[n] = B[n] + sum_k g W_k(., n) and g_out = act(g_pre): PRE_COLS
+    // columns per block, NT / PRE_COLS threads each, their sums added in order
+    __shared__ float part[NT];
+    const int c = threadIdx.x % PRE_COLS, t = threadIdx.x / PRE_COLS;
+    const int n = ((int)blockIdx.x - np) * PRE_COLS + c;
+    float s = 0.f;
+    if (n < Nc) {
+      const int tot = K * Rk;
+#pragma unroll 4
+      for (int q = t; q < tot; q += NT / PRE_COLS) {
+        const int k = q / Rk, j = q - k * Rk;
+        s = fmaf(g[j], W[k * wk + j * wj + n * wn], s);
+      }
+    }
+    part[threadIdx.x] = s;
+    __syncthreads();
+    if (t == 0 && n < Nc) {
+      float v = bias ? bias[n] : 0.f;
+      for (int q = 0; q < NT / PRE_COLS; ++q) v += part[q * PRE_COLS + c];
+      g_pre[n] = v;
+      g_out[n] = relu && !(v > 0.f) ? 0.f : v;
+    }
+    return;
+  }
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  if (i < TILE_PAD) sub[i] = g && i < Rk ? g[i] : 0.f;
+  const int lane = (int)(i & 63), ct = (int)((i >> 6) & 1);
+  const int64_t f = i >> 7;  // (k*ncb + cb)*nst + step
+  if (f >= (int64_t)K * ncb * nst) return;
+  const int step = (int)(f % nst);
+  const int64_t kc = f / nst;
+  const int cb = (int)(kc % ncb), k = (int)(kc / ncb);
+  const int n = 64 * cb + 32 * ct + (lane & 31), j0 = 16 * step + 8 * (lane >> 5);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    v[e] = n < Nc && j0 + e < Rk ? W[k * wk + (j0 + e) * wj + n * wn] : 0.f;
+  const Frag3 s = split8(v);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) Wp[((f * 2 + ct) * 3 + p) * 64 + lane] = s.s[p];
+}
+
+// Orders the wave's LDS accesses: a lane reads what other lanes wrote, which
+// the compiler, seeing one lane's addresses, cannot know.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// An offset's index words of a lane's row, loaded ahead of their use.
+struct Idx {
+  int g, s;
+};
+
+// Where the 64 rows of a wave's tile come from: lane l knows accumulator row
+// row0 + l.  U: the offsets that any of the rows has.
+template <bool SORTED>
+struct Rows {
+  int64_t row0;
+  uint32_t U;
+  int64_t P;        // lists: lane k holds the tile's range of list k
+  int N;
+  uint32_t m, off;  // sorted: the lane's mask and list
+  const int32_t *gidx, *aidx;
+  int64_t last;     // lists: the last pair
+
+  __device__ inline void init(const TileArgs& a, int64_t tile, int lane) {
+    row0 = tile * TILE;
+    if (SORTED) {
+      const int64_t pos = row0 + lane;
+      gidx = a.nb;
+      m = pos < a.nrows ? a.fmask[pos] : 0u;
+      off = a.nb_off[pos < a.nrows ? a.fperm[pos] : 0];
+      uint32_t o = m;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) o |= (uint32_t)__shfl_xor((int)o, d, 64);
+      U = (uint32_t)__builtin_amdgcn_readfirstlane((int)o);
+    } else {
+      const int k = lane < a.K ? lane : 0;
+      gidx = a.gidx;
+      aidx = a.aidx;
+      P = a.tpos[(int64_t)k * a.ntile + tile];
+      N = lane < a.K ? (int)(a.tpos[(int64_t)k * a.ntile + tile + 1] - P) : 0;
+      U = (uint32_t)__ballot(N > 0);
+      last = a.npairs - 1;
+    }
+  }
+  __device__ inline Idx load(int k, int lane) const {
+    Idx x;
+    if (SORTED) {
+      // read unconditionally (the list has a spare entry)
+      x.g = gidx[off + __popc(m & ((1u << k) - 1u))];
+      x.s = 0;
+    } else {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)P, k);
+      const uint32_t hi =
+          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)P >> 32), k);
+      const int n = __builtin_amdgcn_readlane(N, k);
+      // lanes past the pairs repeat the last one; an offset without pairs
+      // here reads some pair
+      const int64_t p = min((int64_t)(((uint64_t)hi << 32) | lo) + max(min(lane, n - 1), 0), last);
+      x.g = gidx[p];
+      x.s = aidx[p];
+    }
+    return x;
+  }
+  // row of src for the lane's accumulator row at offset k, or -1
+  __device__ inline int row(const Idx& x, int k) const {
+    if (SORTED) return (m >> k) & 1u ? x.g : -1;
+    // the pair's row takes it; a row that no pair names receives 0
+    const int r = __builtin_amdgcn_ds_permute((int)(x.s - row0) * 4, x.g + 1) - 1;
+    return (U >> k) & 1u ? r : -1;
+  }
+};
+
+// Items in (offset, chunk) order; past the last one an item stays where it is
+// (its loads are in bounds and unused).
+struct Item {
+  int k, ch;
+  uint32_t rest;  // offsets after k
+  __device__ inline void advance(int nchunk) {
+    if (ch + 1 < nchunk) {
+      ++ch;
+    } else if (rest) {
+      k = __builtin_ctz(rest);
+      rest &= rest - 1;
+      ch = 0;
+    }
+  }
+};
+
+// Gather of an item's 64 rows.  Load layout: lane 4 rl + cq takes 16 bytes of
+// row 16 g + rl, so four adjacent lanes read 64 contiguous bytes (in the MFMA
+// layout adjacent lanes hold different rows, and the L1 would serve each
+// 16-byte piece on its own).
+template <int TC, bool VEC>
+__device__ inline void gather_rows(v4f (&nx)[4][TC], const float* src, int Rk, int ld,
+                                   int64_t absent, int row, int ch, int rl, int piece) {
+  const int c0 = 16 * TC * ch;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int r = __builtin_amdgcn_ds_bpermute((16 * g + rl) * 4, row);
+    const float* const p = src + (r >= 0 ? (int64_t)r * ld : absent);
+#pragma unroll
+    for (int s = 0; s < TC; ++s) {
+      const int c = c0 + 16 * s + 4 * piece;
+      if (VEC) {
+        nx[g][s] = *reinterpret_cast<const v4f*>(p + c);
+      } else {
+        // channels past Rk read channel 0; their weights are zero
+#pragma unroll
+        for (int z = 0; z < 4; ++z) nx[g][s][z] = p[c + z < Rk ? c + z : 0];
+      }
+    }
+  }
+}
+
+// A step's 64 rows pass through 4 KB of LDS into the MFMA layout: lane
+// (n32, h) of row tile rt holds row 32 rt + n32, channels 16 s + 8 h + 0..7.
+// Piece p of row 16 g + rl sits at g*1024 + rl*64 + 16*(p ^ ((rl >> 1) & 3)):
+// the exchange of pieces (made on the addresses loaded from) puts the eight
+// rows that a read serves at once on different banks.
+struct Turn {
+  int wr, rd0, rd1;  // byte offsets: lane's write; reads of the two halves
+  __device__ inline explicit Turn(int lane) {
+    const int n32 = lane & 31, h = lane >> 5, rr = n32 & 15, sw = (rr >> 1) & 3;
+    wr = lane * 16;
+    rd0 = (n32 >> 4) * 1024 + rr * 64 + 16 * ((2 * h) ^ sw);
+    rd1 = (n32 >> 4) * 1024 + rr * 64 + 16 * ((2 * h + 1) ^ sw);
+  }
+};
+
+// Reads one row tile of a step, shifts and splits it.
+template <bool SUB>
+__device__ inline Frag3 turn_read(const char* b, const Turn& t, int rt, v4f g0, v4f g1) {
+  const v4f x0 = *reinterpret_cast<const v4f*>(b + rt * 2048 + t.rd0);
+  const v4f x1 = *reinterpret_cast<const v4f*>(b + rt * 2048 + t.rd1);
+  float v[8];
+#pragma unroll
+  for (int z = 0; z < 4; ++z) {
+    v[z] = SUB ? x0[z] - g0[z] : x0[z];
+    v[4 + z] = SUB ? x1[z] - g1[z] : x1[z];
+  }
+  return split8(v);
+}
+
+// One step: 2 x 2 tiles of 32 rows x 32 columns, six products each, added to
+// acc (FIRST: acc starts from zero).
+template <bool FIRST>
+__device__ inline void step_products(v16f (&acc)[2][2], const v4u (&W)[2][3], const Frag3 (&X)[2]) {
+  v16f zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+#pragma unroll
+  for (int q = 0; q < SPLIT_PROD; ++q)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct)
+        acc[rt][ct] = mfma_bf16(W[ct][split_a(q)], X[rt].s[split_b(q)],
+                                FIRST && q == 0 ? zero : acc[rt][ct]);
+}
+
+// Sums in two levels, per offset and over the offsets: a chain over all
+// offsets' channels would round as often as 27 x 64 channels have steps (the
+// error of an input gradient against 64-bit sums: 3.1e-7 for one chain,
+// 1.3e-7 for two levels, 1.4e-7 for the two levels of the fp32 instruction).
+__device__ inline void add_offset(v16f (&acc)[2][2], const v16f (&part)[2][2]) {
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[rt][ct][r] += part[rt][ct][r];
+}
+
+// A 32 x 32 quarter of a tile: a lane holds row 32 rt + n32 and, in register
+// 4 j + z, column 64 cb + 32 ct + 8 j + 4 h + z.  If one of its sums is not
+// finite, the operands held an infinity, a NaN or a value past bf16's range
+// (or the sum itself overflows): it is computed again in plain fp32.
+template <bool SUB, bool SORTED>
+__device__ inline void redo_if_special(const TileArgs& a, const Rows<SORTED>& R, v16f& e, int rt,
+                                       int ct, int cb, int lane) {
+  float t = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) t = fmaf(e[r], 0.f, t);
+  if (!__ballot(!(t == 0.f))) return;
+  const int n32 = lane & 31, col0 = 64 * cb + 32 * ct + 4 * (lane >> 5);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) e[r] = 0.f;
+  uint32_t rest = R.U;
+  while (rest) {
+    const int k = __builtin_ctz(rest);
+    rest &= rest - 1;
+    const int row = __builtin_amdgcn_ds_bpermute((32 * rt + n32) * 4, R.row(R.load(k, lane), k));
+    if (row < 0) continue;
+    const float* xp = a.src + (int64_t)row * a.ld;
+    for (int j = 0; j < a.Rk; ++j) {
+      const float x = SUB ? xp[j] - a.sub[j] : xp[j];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int col = col0 + 8 * (r >> 2) + (r & 3);
+        if (col < a.Nc) e[r] = fmaf(x, a.W[k * a.wk + j * a.wj + col * a.wn], e[r]);
+      }
+    }
+  }
+}
+
+// Columns col .. col + 3 of accumulator row pos: dst = act(v + add).
+// STREAM: written past the caches (a large layer's output is read only by
+// later calls: 2.70 -> 2.60 ms for the forward of the benchmark's layer).
+template <bool SORTED, bool STREAM>
+__device__ inline void put4(const TileArgs& a, int64_t pos, int col, v4f v) {
+  if (pos >= a.nrows || col >= a.Nc) return;
+  const bool dvec = (a.Nc & 3) == 0 && (reinterpret_cast<uintptr_t>(a.dst) & 15) == 0;
+  const int64_t drow = SORTED ? (int64_t)a.fperm[pos] : a.wmap ? (int64_t)a.wmap[pos] : pos;
+  float* const dp = a.dst + drow * a.Nc + col;
+#pragma unroll
+  for (int z = 0; z < 4; ++z) {
+    if (a.add && col + z < a.Nc) v[z] += a.add[col + z];
+    if (a.relu) v[z] = v[z] > 0.f ? v[z] : 0.f;
+  }
+  if (dvec) {
+    if (STREAM)
+      __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(dp));
+    else
+      *reinterpret_cast<v4f*>(dp) = v;
+  } else {
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+      if (col + z < a.Nc) dp[z] = v[z];
+  }
+}
+
+// Work items are contiguous per XCD (work-groups are dispatched round-robin
+// over the eight), so that neighbouring tiles share its L2.
+__device__ inline int64_t xcd_item(int64_t b, int64_t n) {
+  const int64_t x = b & 7, j = b >> 3, base = n >> 3, rem = n & 7;
+  return x * base + min(x, rem) + j;
+}
+
+// Large layers: four waves, a tile of 64 rows each, walk the same items; the
+// item's weights are loaded into LDS once for all of them, an item ahead, and
+// so are each step's rows into registers.  Two or three work-groups per CU:
+// one's splits, waits, prologue and stores run under the others' products.
+// TC: 16-channel steps per item.  VEC: rows of src are whole steps, 16-byte
+// aligned.  SUB: rows are shifted by a.sub.  SORTED: rows from the dense
+// forward view, else from pair lists; its sums run in one chain (3.1e-7 off
+// 64-bit sums on the benchmark's layer, as before it 3.7e-7), the lists' in
+// two levels.
+constexpr int WGW = 4;              // waves per work-group
+constexpr int OUT_LD = 68;          // floats per row of the epilogue's LDS tile
+constexpr int OUT_B = 32 * OUT_LD * 4;
+constexpr size_t wg_lds(int tc) {
+  return std::max<size_t>((size_t)tc * 12288 + WGW * 4096, (size_t)WGW * OUT_B);
+}
+template <int TC, bool VEC, bool SUB, bool SORTED>
+__global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileArgs a, int nchunk, int ncb) {
+  extern __shared__ char smem[];
+  constexpr int WB = TC * 6144;                    // bytes of an item's weights
+  constexpr int NR = TC * 384 / (64 * WGW);        // ... 16-byte pieces per thread
+  constexpr int NX = TC * 384 % (64 * WGW);        // ... and threads with one more
+  char* const wbuf = smem;                         // [2][WB]
+  uint32_t* const ush = reinterpret_cast<uint32_t*>(smem + wg_lds(TC));
+  float* const gsh = reinterpret_cast<float*>(smem + wg_lds(TC) + 64);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  char* const buf = smem + 2 * WB + w * 4096;      // one step of the wave's rows
+  const int rl = lane >> 2, piece = (lane & 3) ^ ((rl >> 1) & 3);
+  const int nst = nchunk * TC;
+  if (SUB)
+    for (int c = tid; c < 16 * nst; c += 64 * WGW) gsh[c] = a.sub[c];
+  const int64_t u = xcd_item(blockIdx.x, gridDim.x);
+  const int64_t grp = u / ncb;
+  const int cb = (int)(u - grp * ncb);
+  const int64_t tile = min(grp * WGW + w, a.ntile - 1);
+  const bool live = grp * WGW + w < a.ntile;
+  Rows<SORTED> R;
+  R.init(a, tile, lane);
+  if (lane == 0) ush[w] = R.U;
+  __syncthreads();
+  uint32_t U = 0;
+#pragma unroll
+  for (int i = 0; i < WGW; ++i) U |= ush[i];
+  U = (uint32_t)__builtin_amdgcn_readfirstlane((int)U);
+
+  const float* const src = a.src;
+  const int Rk = a.Rk, ld = a.ld;
+  const Turn turn(lane);
+  const v4u* const Wb = reinterpret_cast<const v4u*>(a.Wp);
+  v4u wr[NR + (NX > 0)];  // weights on their way to LDS
+  auto wload = [&](const Item& t) {
+    const v4u* p = Wb + (((int64_t)t.k * ncb + cb) * nst + t.ch * TC) * 384;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) wr[i] = p[tid + 64 * WGW * i];
+    if (NX) wr[NR] = p[64 * WGW * NR + min(tid, NX - 1)];
+  };
+  auto wstore = [&](char* b) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      *reinterpret_cast<v4u*>(b + (tid + 64 * WGW * i) * 16) = wr[i];
+    if (NX && tid < NX) *reinterpret_cast<v4u*>(b + (tid + 64 * WGW * NR) * 16) = wr[NR];
+  };
+  // Where the lane gathers from, in the load layout: the row's start, or `sub`
+  // for a row without the offset.  The product is taken where a lane knows one
+  // row, not after the spread, where it knows four (VEC: in 16-byte units).
+  struct From {
+    const float* p[4];
+  };
+  auto spread = [&](int row, int ch) -> From {
+    From q;
+    const int at = VEC ? (row < 0 ? -1 : (int)((uint32_t)row * (uint32_t)(ld >> 2))) : row;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int v = __builtin_amdgcn_ds_bpermute((16 * g + rl) * 4, at);
+      const float* const f = VEC ? src + ((int64_t)(uint32_t)v << 2) : src + (int64_t)v * ld;
+      q.p[g] = (v == -1 ? a.sub : f) + 16 * TC * ch + (VEC ? 4 * piece : 0);
+    }
+    return q;
+  };
+  v4f nx[4][TC];  // rows on their way to LDS
+  auto gather = [&](const From& q, int s, int ch) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (VEC) {
+        nx[g][s] = *reinterpret_cast<const v4f*>(q.p[g] + 16 * s);
+      } else {
+        // channels past Rk read channel 0; their weights are zero
+        const int c0 = 16 * TC * ch, c = 16 * s + 4 * piece;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) nx[g][s][z] = q.p[g][c0 + c + z < Rk ? c + z : -c0];
+      }
+    }
+  };
+  auto commit = [&](int s) {
+    wave_sync();
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<v4f*>(buf + g * 1024 + turn.wr) = nx[g][s];
+    wave_sync();
+  };
+  v16f acc[2][2], part[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int nit = __builtin_popcount(U) * nchunk;
+  if (nit > 0) {
+    Item c{__builtin_ctz(U), 0, U & (U - 1)};
+    Item n = c;
+    n.advance(nchunk);
+    Item n2 = n;
+    n2.advance(nchunk);
+    const Idx xc = R.load(c.k, lane);
+    Idx xn = R.load(n.k, lane);
+    wload(c);
+    {
+      const From q = spread(R.row(xc, c.k), c.ch);
+#pragma unroll
+      for (int s = 0; s < TC; ++s) gather(q, s, c.ch);
+    }
+    wstore(wbuf);
+    wload(n);
+    __syncthreads();
+    // drained once, so that the waits in the loop follow from its own loads
+    __builtin_amdgcn_s_waitcnt(0);
+    for (int it = 0; it < nit; ++it) {
+      const char* const wl = wbuf + (it & 1) * WB + lane * 16;
+      // the other half held the item before, which every wave has left
+      wstore(wbuf + ((it & 1) ^ 1) * WB);
+      wload(n2);
+      const From qn = spread(R.row(xn, n.k), n.ch);
+      xn = R.load(n2.k, lane);
+#pragma unroll
+      for (int s = 0; s < TC; ++s) {
+        commit(s);
+        gather(qn, s, n.ch);
+        Frag3 X[2];
+        v4u Wf[2][3];
+        v4f g0 = {}, g1 = {};
+        if (SUB) {
+          const float* gp = gsh + 16 * (TC * c.ch + s) + 8 * (lane >> 5);
+          g0 = *reinterpret_cast<const v4f*>(gp);
+          g1 = *reinterpret_cast<const v4f*>(gp + 4);
+        }
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB>(buf, turn, rt, g0, g1);
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            Wf[ct][q] = *reinterpret_cast<const v4u*>(wl + ((s * 2 + ct) * 3 + q) * 1024);
+        if (SORTED)
+          step_products<false>(acc, Wf, X);
+        else if (s == 0 && c.ch == 0)
+          step_products<true>(part, Wf, X);
+        else
+          step_products<false>(part, Wf, X);
+      }
+      if (!SORTED && c.ch == nchunk - 1) add_offset(acc, part);
+      c = n;
+      n = n2;
+      n2.advance(nchunk);
+      __syncthreads();
+    }
+  }
+  if (!live) return;
+  // The accumulators leave through LDS, 32 rows at a time, so that a store
+  // instruction writes whole rows (16 lanes each): 16-byte pieces of 32 rows
+  // at a time cost the 1.1 GB output of the benchmark's layer 0.56 ms.
+  float* const ob = reinterpret_cast<float*>(smem + w * OUT_B);
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    wave_sync();
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      redo_if_special<SUB, SORTED>(a, R, acc[rt][ct], rt, ct, cb, lane);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<v4f*>(ob + (lane & 31) * OUT_LD + 32 * ct + 8 * j + 4 * (lane >> 5)) =
+            v4f{acc[rt][ct][4 * j], acc[rt][ct][4 * j + 1], acc[rt][ct][4 * j + 2],
+                acc[rt][ct][4 * j + 3]};
+    }
+    wave_sync();
+    const int col = 64 * cb + 4 * (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = 4 * i + (lane >> 4);
+      put4<SORTED, SORTED>(a, R.row0 + 32 * rt + r, col,
+                   *reinterpret_cast<const v4f*>(ob + r * OUT_LD + 4 * (lane & 15)));
+    }
+  }
+}
+
+// Small layers: the four waves of a work-group share one tile and take every
+// fourth item, with their own weights from L2; their sums are added in wave
+// order.
+template <int TC, bool VEC, bool SUB, bool SORTED>
+__global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a, int nchunk,
+                                                                     int ncb) {
+  extern __shared__ char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rl = lane >> 2, piece = (lane & 3) ^ ((rl >> 1) & 3);
+  constexpr int GOFF = 65536;
+  char* const buf = smem + w * 16384;
+  const int nst = nchunk * TC;
+  const float* const gsh = reinterpret_cast<const float*>(smem + GOFF);
+  if (SUB) {
+    for (int c = tid; c < 16 * nst; c += NT)
+      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[c];
+    __syncthreads();
+  }
+  const int64_t u = xcd_item(blockIdx.x, gridDim.x);
+  const int64_t tile = u / ncb;
+  const int cb = (int)(u - tile * ncb);
+  Rows<SORTED> R;
+  R.init(a, tile, lane);
+  const uint32_t U = R.U;
+  const float* const src = a.src;
+  const int Rk = a.Rk, ld = a.ld;
+  const int64_t absent = a.sub - a.src;  // where rows without the offset read
+  const Turn turn(lane);
+
+  struct WSet {
+    v4u f[2][3];
+  };
+  const v4u* const Wb = reinterpret_cast<const v4u*>(a.Wp) + lane;
+  auto wload = [&](const Item& t, int s, WSet& A) {
+    const v4u* p = Wb + (((int64_t)t.k * ncb + cb) * nst + (t.ch * TC + s)) * 384;
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) A.f[ct][q] = p[(ct * 3 + q) * 64];
+  };
+  v16f acc[2][2], part[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  auto mult = [&](int s, int ch, const WSet& A) {
+    Frag3 X[2];
+    v4f g0 = {0.f, 0.f, 0.f, 0.f}, g1 = g0;
+    if (SUB) {
+      const float* gp = gsh + 16 * (TC * ch + s) + 8 * (lane >> 5);
+      g0 = *reinterpret_cast<const v4f*>(gp);
+      g1 = *reinterpret_cast<const v4f*>(gp + 4);
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB>(buf + s * 4096, turn, rt, g0, g1);
+    if (s == 0)
+      step_products<true>(part, A.f, X);
+    else
+      step_products<false>(part, A.f, X);
+  };
+
+  auto step_item = [&](Item t) -> Item {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t.advance(nchunk);
+    return t;
+  };
+  const int cnt = (__builtin_popcount(U) * nchunk - w + 3) >> 2;
+  if (cnt > 0) {
+    Item c{__builtin_ctz(U), 0, U & (U - 1)};
+    for (int i = 0; i < w; ++i) c.advance(nchunk);
+    Item n = step_item(c), nn = step_item(n);
+    WSet A[TC];
+    v4f nx[4][TC];
+    const Idx xc = R.load(c.k, lane);
+    Idx xn = R.load(n.k, lane);
+    gather_rows<TC, VEC>(nx, src, Rk, ld, absent, R.row(xc, c.k), c.ch, rl, piece);
+#pragma unroll
+    for (int s = 0; s < TC; ++s) wload(c, s, A[s]);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int it = 0; it < cnt; ++it) {
+      wave_sync();
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int s = 0; s < TC; ++s)
+          *reinterpret_cast<v4f*>(buf + s * 4096 + g * 1024 + turn.wr) = nx[g][s];
+      wave_sync();
+      // Loads return in order, so a wait for one waits for all before it: the
+      // next item's rows and the indices after them are issued ahead of its
+      // weights, so that no wait for weights drains them early.
+      __builtin_amdgcn_sched_barrier(0);
+      gather_rows<TC, VEC>(nx, src, Rk, ld, absent, R.row(xn, n.k), n.ch, rl, piece);
+      xn = R.load(nn.k, lane);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < TC; ++s) {
+        mult(s, c.ch, A[s]);
+        __builtin_amdgcn_sched_barrier(0);
+        wload(n, s, A[s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      add_offset(acc, part);  // (per item: its chunk of the offset's channels)
+      c = n;
+      n = nn;
+      nn = step_item(nn);
+    }
+  }
+
+  // quarter j = 2 rt + ct of the tile goes to wave j, which adds the four
+  // waves' sums in wave order
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const v16f& q = acc[j >> 1][j & 1];
+      *reinterpret_cast<v4f*>(smem + ((j * 4 + w) * 4 + r) * 1024 + lane * 16) =
+          v4f{q[4 * r], q[4 * r + 1], q[4 * r + 2], q[4 * r + 3]};
+    }
+  __syncthreads();
+  v16f e;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    v4f s = *reinterpret_cast<const v4f*>(smem + ((w * 4 + 0) * 4 + r) * 1024 + lane * 16);
+#pragma unroll
+    for (int v = 1; v < 4; ++v)
+      s += *reinterpret_cast<const v4f*>(smem + ((w * 4 + v) * 4 + r) * 1024 + lane * 16);
+#pragma unroll
+    for (int z = 0; z < 4; ++z) e[4 * r + z] = s[z];
+  }
+  redo_if_special<SUB, SORTED>(a, R, e, w >> 1, w & 1, cb, lane);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    put4<SORTED, false>(a, R.row0 + 32 * (w >> 1) + (lane & 31),
+                 64 * cb + 32 * (w & 1) + 8 * j + 4 * (lane >> 5),
+                 v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
+}
+
+typedef void (*TileFn)(TileArgs, int, int);
+
+template <int TC, bool VEC>
+TileFn pick_rows(bool sub, bool sorted, bool split) {
+  if (sorted)
+    return split ? tile_split_kernel<TC, VEC, true, true> : tile_wg_kernel<TC, VEC, true, true>;
+  if (sub)
+    return split ? tile_split_kernel<TC, VEC, true, false> : tile_wg_kernel<TC, VEC, true, false>;
+  return split ? tile_split_kernel<TC, VEC, false, false> : tile_wg_kernel<TC, VEC, false, false>;
+}
+
+TileFn tile_fn(int tc, bool vec, bool sub, bool sorted, bool split) {
+  if (tc == 1)
+    return vec ? pick_rows<1, true>(sub, sorted, split) : pick_rows<1, false>(sub, sorted, split);
+  return vec ? pick_rows<2, true>(sub, sorted, split) : pick_rows<2, false>(sub, sorted, split);
+}
+
+// out[r][0 .. 16 ceil(C/16)) = row r of x, zeros past C
+__global__ void __launch_bounds__(NT) tile_pad_kernel(const float* __restrict__ x, int64_t rows,
+                                                      int C, int q4, v4f* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  const int64_t r = i / q4;
+  if (r >= rows) return;
+  const int c = 4 * (int)(i - r * q4);
+  const float* p = x + r * C + c;
+  v4f v;
+#pragma unroll
+  for (int z = 0; z < 4; ++z) v[z] = c + z < C ? p[z] : 0.f;
+  out[i] = v;
+}
+
+}  // namespace
+
+int tile_steps(int Rk) { return (int)ceil_div(Rk, 16); }
+
+size_t tile_pack_bytes(int K, int Rk, int Nc) {
+  return (size_t)K * ceil_div(Nc, 64) * tile_steps(Rk) * 6144;
+}
+
+scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
+                     const float* g, const float* bias, int relu, uint32_t* Wp, float* sub,
+                     float* g_pre, float* g_out, hipStream_t st) {
+  const int nst = tile_steps(Rk), ncb = (int)ceil_div(Nc, 64);
+  const int64_t n = std::max<int64_t>((int64_t)K * ncb * nst * 128, TILE_PAD);
+  const int64_t np = ceil_div(n, NT), ng = g_pre ? ceil_div(Nc, PRE_COLS) : 0;
+  hipLaunchKernelGGL(tile_pack_kernel, dim3((unsigned)(np + ng)), dim3(NT), 0, st, W, wk, wj, wn,
+                     K, Rk, Nc, nst, ncb, g, bias, relu, reinterpret_cast<v4u*>(Wp), sub, (int)np,
+                     g_pre, g_out);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+size_t tile_pad_bytes(int64_t rows, int Rk) {
+  return Rk % 16 ? (size_t)rows * ceil_div(Rk, 16) * 64 : 0;
+}
+
+scn_status tile_pad(TileArgs& a, float* out, hipStream_t st) {
+  const int q4 = 4 * tile_steps(a.Rk);
+  if (a.nsrc > 0) {
+    hipLaunchKernelGGL(tile_pad_kernel, dim3((unsigned)ceil_div(a.nsrc * q4, NT)), dim3(NT), 0, st,
+                       a.src, a.nsrc, a.Rk, q4, reinterpret_cast<v4f*>(out));
+    SCN_LAUNCH_CHECK();
+  }
+  a.src = out;
+  a.ld = 4 * q4;
+  return SCN_OK;
+}
+
+scn_status launch_tile(const TileArgs& a, hipStream_t st) {
+  if (a.nrows <= 0 || a.ntile <= 0) return SCN_OK;
+  const int nst = tile_steps(a.Rk), ncb = (int)ceil_div(a.Nc, 64);
+  // whole aligned steps, and row starts in 16-byte units below 2^32 - 1
+  const bool vec = (a.ld & 15) == 0 && (reinterpret_cast<uintptr_t>(a.src) & 15) == 0 &&
+                   a.nsrc * (a.ld >> 2) < (int64_t)0xffffffff;
+  const int64_t items = a.ntile * ncb;
+  const bool split = items < TILE_SPLIT;
+  const int tc = chunk_steps(a.Rk);
+  const size_t base = split ? 65536 : wg_lds(tc) + 64, smem = base + (size_t)nst * 64;
+  TileFn fn = tile_fn(tc, vec, a.subtract, a.nb != nullptr, split);
+  // once per process and kernel: its largest size
+  static std::atomic<bool> sized[2][2][3][2];
+  std::atomic<bool>& done = sized[tc - 1][vec][a.nb ? 2 : a.subtract ? 1 : 0][split];
+  if (base + 1024 > 65536 && !done.load(std::memory_order_acquire)) {
+    SCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)(base + 1024)));
+    done.store(true, std::memory_order_release);
+  }
+  const int64_t nwg = split ? items : ceil_div(a.ntile, WGW) * ncb;
+  hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(split ? NT : 64 * WGW), smem, st, a, nst / tc,
+                     ncb);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+}  // namespace scn

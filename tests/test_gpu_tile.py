@@ -1,0 +1,128 @@
+"""The tile contraction of stride-1 rulebooks (forward and input gradient) at
+the sizes where it can go wrong: rows around the tile of 64 and the work-group
+of 256, both its kernels (four waves on one tile; four tiles sharing their
+weights), pair lists and the mask-sorted view, channel counts around the
+16-channel step and the 64-column block, and operands that the bf16 split
+cannot hold.
+
+Reference: the sums in float64 over the rulebook's own pair lists.  Bound: a
+sum of n products, each rounded once and added in any order, is off by at most
+(n + 4) 2^-24 sum |terms|; x - g_in is rounded before it (one more), and the
+dropped products of the split stay below 2^-24 of their term."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from gen import random_sites, stream_rng  # noqa: E402
+
+from helpers import dev, host  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+@pytest.fixture()
+def scn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1505_02890_amd as m
+    m.lib()
+    yield m
+    m.set_dense_forward()
+
+
+def _layer(scn, f, m, n, cin, cout, seed, shuffle=True):
+    rng = stream_rng(seed, 7)
+    c = random_sites(rng, 1, (m, m, m), n, shuffle=shuffle)
+    rb = scn.build_rulebook(dev(c), (1, m, m, m), f, 1)
+    x = rng.standard_normal((n, cin)).astype(np.float32)
+    g = rng.standard_normal(cin).astype(np.float32)
+    W = (rng.standard_normal((rb.K, cin, cout)) * 0.1).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    _, ir, orr = (t.long().cpu() for t in rb.export())
+    return rb, x, g, W, b, ir, orr
+
+
+def _forward(rb, ir, orr, x, g, W, b):
+    """(y, sum of |terms|) in float64 on the CPU"""
+    d = [torch.from_numpy(np.asarray(a, np.float64)) for a in (x - g, x.astype(np.float64) - g, g,
+                                                               W, b)]
+    y = torch.zeros(rb.a_out, W.shape[2], dtype=torch.float64)
+    s = torch.zeros_like(y)
+    pre, spre = d[4].clone(), d[4].abs()
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        y.index_add_(0, o, d[1][i] @ d[3][k])
+        s.index_add_(0, o, d[1][i].abs() @ d[3][k].abs())
+        pre += d[2] @ d[3][k]
+        spre += d[2].abs() @ d[3][k].abs()
+    return (y + pre).numpy(), (s + spre).numpy()
+
+
+def _check(got, want, mass, terms):
+    err = np.abs(got.astype(np.float64) - want)
+    assert np.all(err <= (terms + 8) * U * mass + 1e-30), float(np.max(err / (mass + 1e-30)) / U)
+
+
+SIZES = [
+    # f, m, n, cin, cout, dense view
+    (2, 9, 1, 16, 16, False), (2, 9, 2, 1, 1, False), (1, 9, 64, 16, 64, False),
+    (1, 9, 63, 32, 65, False), (1, 9, 65, 48, 3, False), (1, 17, 255, 33, 64, False),
+    (1, 17, 257, 17, 100, True), (3, 12, 300, 64, 64, False), (3, 12, 300, 64, 64, True),
+    (3, 10, 500, 15, 31, True), (2, 14, 1000, 160, 96, False), (2, 14, 1000, 176, 256, True),
+    # enough tiles for the shared-weights kernel, forward and input gradient
+    (2, 48, 20000, 32, 130, False), (2, 48, 20000, 80, 130, True), (2, 60, 45001, 192, 16, False),
+    (2, 60, 45001, 200, 40, True), (1, 60, 131073, 16, 8, False), (1, 60, 131009, 7, 5, True),
+]
+
+
+@pytest.mark.parametrize("case", SIZES)
+def test_tile_sizes(scn, case):
+    f, m, n, cin, cout, view = case
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, f, m, n, cin, cout, 11, shuffle=n % 2 == 1)
+    assert rb.dense_view == (view and rb.a_out > 0)
+    y, _ = scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))
+    want, mass = _forward(rb, ir, orr, x, g, W, b)
+    _check(host(y), want, mass, rb.K * cin)
+    rng = stream_rng(12, 1)
+    dy = rng.uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+    dx = scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=("dx",))["dx"]
+    dy64, W64 = torch.from_numpy(dy).double(), torch.from_numpy(W).double()
+    want = torch.zeros(n, cin, dtype=torch.float64)
+    mass = torch.zeros_like(want)
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        want.index_add_(0, i, dy64[o] @ W64[k].t())
+        mass.index_add_(0, i, dy64[o].abs() @ W64[k].t().abs())
+    _check(host(dx), want.numpy(), mass.numpy(), rb.K * cout)
+
+
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("view", [False, True])
+def test_values_past_the_split(scn, view, big):
+    """Infinities, NaN and floats that round past bf16's largest value: the
+    same entries are infinite and NaN as in fp32, and the others as close as
+    ever.  Values whose low parts are subnormal in bf16 lose no more than
+    those parts (2^-126 at most per factor)."""
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    n, cout = (20000, 130) if big else (900, 40)
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, 48 if big else 14, n, 32, cout, 21)
+    g[:] = 0
+    W = (np.abs(W) + 0.01).astype(np.float32)
+    for r, v in ((3, np.inf), (100, -np.inf), (200, np.nan), (300, 3.4e38), (400, -3.402e38),
+                 (500, 1e-37), (600, 3e38)):
+        x[r, r % 32] = v
+    W[:, 300 % 32] *= 1e-3  # 3.4e38 itself stays in range
+    with np.errstate(all="ignore"):
+        want, mass = _forward(rb, ir, orr, x, g, W, b)
+        f32 = want.astype(np.float32)
+    y = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+    assert np.array_equal(np.isnan(y), np.isnan(want))
+    assert np.array_equal(np.isinf(y), np.isinf(f32))
+    assert np.array_equal(y[np.isinf(y)], f32[np.isinf(y)])
+    ok = np.isfinite(f32) & np.isfinite(mass)
+    _check(y[ok], want[ok], mass[ok], rb.K * 32)
