@@ -36,12 +36,11 @@
 #include <mutex>
 
 #include "scn_internal.h"
+#include "split.h"
 #include "tile.h"
 
 namespace scn {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;     // threads per work-group (4 waves)
 constexpr int CB = 64;      // columns per work-group
@@ -684,18 +683,25 @@ __global__ void __launch_bounds__(NT) finish_vec_kernel(const float* __restrict_
 }
 
 // Weight gradient partials.  A work-group accumulates one 64x64 block of
-// dW_k = sum_pairs (x[r] - g_in)^T dy[o] over a fixed chunk of list k, 64 pairs
-// per stage.  The stage is stored transposed in LDS ([channel][pair]) so that
-// MFMA fragments along the pair axis are single ds_read_b128s.  Thread
-// (channel c = tid % 64, pair quad group w = tid / 64) loads channel c of 16
-// pairs: every wave-wide load reads 64 consecutive channels of one row (two
-// cache lines), and each 4 pairs of one channel leave as one ds_write_b128.
-// Pair indices are staged through LDS two stages ahead, rows one stage ahead.
-constexpr int DW_SC = 64;          // pairs per stage
-constexpr int DW_LD = DW_SC + 4;   // pitch of a channel row (floats)
-// Pair quad p of channel row r sits at quad p ^ (r / 16) of the row: with the
-// 17-quad pitch this keeps every 16-lane group of both the transposed stores
-// and the fragment reads on 16 distinct bank groups.
+// dW_k = sum_pairs (x[r] - g_in)^T dy[o] over a fixed chunk of list k, on the
+// bf16 matrix cores in three-way split fp32 (split.h).  Each of its four waves
+// takes every fourth stage of 16 pairs on its own; nothing passes through LDS
+// and nothing waits for another wave until the four sums are added at the end,
+// in wave order.
+//
+// A load instruction reads four pairs' 64 channels as 16-byte pieces (with a
+// float per lane and one pair per instruction the address unit takes as long
+// per instruction, and the kernel four times as long for its gather): lane
+// 16 pg + cq gets channels 4 cq .. + 3 of pairs 4 pg + i, i < 4.  After the
+// split two pairs of a channel share a word, the order the MFMA wants along
+// the pair axis; exchanging odd and even 16-lane rows between the words of
+// neighbouring channels (v_permlane16_swap) then gives every lane 8 pairs of
+// one channel: operand row m of tile t is channel 4 (m & 15) + 2 t + (m >> 4).
+// Per stage a wave issues 24 MFMAs (768 clocks) against about 270 vector
+// instructions (1080, most of them splits): the vector unit bounds it.
+constexpr int DW_SC = 64;  // chunks are whole multiples: one stage per wave
+constexpr int DW_ST = 16;  // pairs per stage
+constexpr int DW_OCC = 2;  // work-groups per CU
 
 struct DwArgs {
   const float* x;        // [a_in][Cin]
@@ -714,48 +720,12 @@ struct DwArgs {
   float* partT;          // [K][maxc][Cout]
 };
 
-// channel c of pairs 4*(w + 4v) + u, v < 4, u < 4 of a stage
-struct DwRows {
-  float x[16], d[16];
-};
-
-__device__ inline void dw_rows(const DwArgs& a, const int* ix, const int* io, int cx, int cd,
-                               int w, DwRows& R) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int pr = 4 * (w + 4 * v) + u;
-      R.x[4 * v + u] = a.x[(int64_t)ix[pr] * a.Cin + cx];
-      R.d[4 * v + u] = a.dyb[(int64_t)io[pr] * a.Cout + cd];
-    }
-}
-
-// V4 (Cin and Cout multiples of 4, 16-byte aligned rows): thread (pair quad
-// pq = tid / 16, channel quad cq = tid % 16) loads channels 4cq .. 4cq+3 of
-// pairs 4pq .. 4pq+3 of each operand as float4 (a wave reads four whole
-// 256-byte row segments per load) and transposes the 4x4 blocks in registers.
-struct DwRows4 {
-  float4 x[4], d[4];
-};
-
-__device__ inline void dw_rows4(const DwArgs& a, const int* ix, const int* io, int cx4, int cd4,
-                                int pq, DwRows4& R) {
-  const float4* x4 = reinterpret_cast<const float4*>(a.x);
-  const float4* d4 = reinterpret_cast<const float4*>(a.dyb);
-  const int nx4 = a.Cin >> 2, nd4 = a.Cout >> 2;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    R.x[u] = x4[(int64_t)ix[4 * pq + u] * nx4 + cx4];
-    R.d[u] = d4[(int64_t)io[4 * pq + u] * nd4 + cd4];
-  }
-}
+typedef int32_t v4i_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <bool V4>
-__global__ void __launch_bounds__(NT) dw_partial_kernel(DwArgs a) {
-  __shared__ float xsT[64 * DW_LD];  // [ci][pair], x - g_in
-  __shared__ float dsT[64 * DW_LD];  // [co][pair]
-  __shared__ int idx[2][2][DW_SC];   // [buffer][input row, output row][pair]
+__global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
+  __shared__ __align__(16) float red[4 * 32 * 64];
+  __shared__ float redT[4 * 64];
   // flattened (chunk, offset, block) work item, blocks then offsets fastest,
   // contiguous per XCD
   const int64_t item = xcd_remap(blockIdx.x, gridDim.x);
@@ -768,143 +738,193 @@ __global__ void __launch_bounds__(NT) dw_partial_kernel(DwArgs a) {
   if (p_begin >= le) return;
   const int64_t p_end = min(le, p_begin + a.chp);
   const int ci0 = (blk / a.nco) * 64, co0 = (blk % a.nco) * 64;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int n16 = lane & 15, q = lane >> 4;
-  // this thread's channel (V4: channel quad) of each operand, clamped into
-  // the layer; out-of-layer channels are zeroed on store
-  const int ch = V4 ? 4 * (tid & 15) : lane;
-  const bool xin = ci0 + ch < a.Cin, din = co0 + ch < a.Cout;
-  const int cx = xin ? ci0 + ch : 0, cd = din ? co0 + ch : 0;
-  const float gsub = (!V4 && xin) ? a.g_in[cx] : 0.f;
-  const float4 gsub4 = (V4 && xin) ? *reinterpret_cast<const float4*>(a.g_in + cx)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-  const int pq = tid >> 4;  // V4: pair quad
-
-  // index loaders: threads 0..63 input rows, 64..127 output rows of one stage
-  auto load_index = [&](int64_t p0) -> int {
-    const int64_t pp = min(p0 + (tid & 63), p_end - 1);
-    return tid < 64 ? a.in_rows[pp] : a.out_rows[pp];
-  };
-  if (tid < 128) {
-    idx[0][tid >> 6][tid & 63] = load_index(p_begin);
-    idx[1][tid >> 6][tid & 63] = load_index(p_begin + DW_SC);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pg = lane >> 4, cq = lane & 15;
+  const int64_t ldx = a.Cin, ldd = a.Cout;
+  const uint32_t bx = 4u * (uint32_t)a.Cin, bd = 4u * (uint32_t)a.Cout;  // bytes per row
+  // the lane's channels; past the layer they repeat its last ones (those rows
+  // and columns of the block are not written)
+  int cx[4], cd[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    cx[e] = V4 ? min(ci0 + 4 * cq, a.Cin - 4) + e : min(ci0 + 4 * cq + e, a.Cin - 1);
+    cd[e] = V4 ? min(co0 + 4 * cq, a.Cout - 4) + e : min(co0 + 4 * cq + e, a.Cout - 1);
   }
-  __syncthreads();
-  DwRows R;
-  DwRows4 R4;
-  if (V4)
-    dw_rows4(a, idx[0][0], idx[0][1], cx >> 2, cd >> 2, pq, R4);
-  else
-    dw_rows(a, idx[0][0], idx[0][1], cx, cd, w, R);
+  // The matrix core drops the bits of small addends below its adder, always
+  // downwards: over a million pairs the drift of every sum was 2.4e-6 of dW's
+  // size (1.0e-6 in all on the fp32 instruction).  Odd waves sum the negated
+  // products, and the drifts cancel where the waves' sums meet.
+  const float sgn = w & 1 ? -1.f : 1.f;
+  v4f gs;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) gs[e] = -sgn * a.g_in[cx[e]];
+  const float* const x = V4 ? a.x + cx[0] : a.x;
+  const float* const dyb = V4 ? a.dyb + cd[0] : a.dyb;
 
-  v4f acc[4];
+  struct Idx {
+    int r[4], o[4];
+  };
+  struct Stage {
+    v4f x[4], d[4];
+  };
+  // rows of pairs 4 pg + i of the stage at p0; pairs past the chunk repeat its
+  // last one
+  auto load_idx = [&](Idx& I, int64_t p0) {
+    const int64_t p = p0 + 4 * pg;
+    if (p0 + DW_ST <= p_end) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
-  float tsum = 0.f;
-  const int tcol = 16 * w + n16;
-
-  int buf = 0;
-  for (int64_t p0 = p_begin; p0 < p_end; p0 += DW_SC) {
-    const int n = (int)min<int64_t>(DW_SC, p_end - p0);
-    // stage rows -> LDS, transposed; pairs past the chunk and channels past
-    // the layer are zero; x is shifted by the ground state
-    if (V4) {
-      const int pb = 4 * pq;
-      float xe[4][4], de[4][4];  // [channel][pair]
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool lx = pb + u < n && xin, ld = pb + u < n && din;
-        xe[0][u] = lx ? R4.x[u].x - gsub4.x : 0.f;
-        xe[1][u] = lx ? R4.x[u].y - gsub4.y : 0.f;
-        xe[2][u] = lx ? R4.x[u].z - gsub4.z : 0.f;
-        xe[3][u] = lx ? R4.x[u].w - gsub4.w : 0.f;
-        de[0][u] = ld ? R4.d[u].x : 0.f;
-        de[1][u] = ld ? R4.d[u].y : 0.f;
-        de[2][u] = ld ? R4.d[u].z : 0.f;
-        de[3][u] = ld ? R4.d[u].w : 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int sq = 4 * (pq ^ ((ch + e) >> 4));  // swizzled pair quad
-        *reinterpret_cast<float4*>(&xsT[(ch + e) * DW_LD + sq]) =
-            make_float4(xe[e][0], xe[e][1], xe[e][2], xe[e][3]);
-        *reinterpret_cast<float4*>(&dsT[(ch + e) * DW_LD + sq]) =
-            make_float4(de[e][0], de[e][1], de[e][2], de[e][3]);
+      for (int i = 0; i < 4; ++i) {
+        I.r[i] = (*reinterpret_cast<const v4i_any*>(a.in_rows + p))[i];
+        I.o[i] = (*reinterpret_cast<const v4i_any*>(a.out_rows + p))[i];
       }
     } else {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int pb = 4 * (w + 4 * v);
-        float xe[4], de[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const bool live = pb + u < n;
-          xe[u] = (live && xin) ? R.x[4 * v + u] - gsub : 0.f;
-          de[u] = (live && din) ? R.d[4 * v + u] : 0.f;
-        }
-        const int sq = 4 * ((pb >> 2) ^ (ch >> 4));  // swizzled pair quad
-        *reinterpret_cast<float4*>(&xsT[ch * DW_LD + sq]) = make_float4(xe[0], xe[1], xe[2], xe[3]);
-        *reinterpret_cast<float4*>(&dsT[ch * DW_LD + sq]) = make_float4(de[0], de[1], de[2], de[3]);
-      }
-    }
-    int nidx = 0;
-    if (tid < 128) nidx = load_index(p0 + 2 * DW_SC);  // stage s+2 indices in flight
-    __syncthreads();
-    // stage s+1 rows while the matrix cores work on stage s
-    if (V4)
-      dw_rows4(a, idx[buf ^ 1][0], idx[buf ^ 1][1], cx >> 2, cd >> 2, pq, R4);
-    else
-      dw_rows(a, idx[buf ^ 1][0], idx[buf ^ 1][1], cx, cd, w, R);
-    // keep those loads ahead of the matrix-core section (left to itself the
-    // scheduler sinks them below it to reuse their registers, and the next
-    // stage then waits for the full memory latency)
-    __builtin_amdgcn_sched_barrier(0);
-    // A(m = ci, kk = pair) = xsT[16w + m][pair];  B(kk = pair, n = co) = dsT[16j + n][pair]
-    const float* ar = xsT + (16 * w + n16) * DW_LD + 4 * (q ^ w);
-#pragma unroll
-    for (int t = 0; t < DW_SC / 16; ++t) {
-      const float4 av = *reinterpret_cast<const float4*>(ar + 16 * t);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float4 bv =
-            *reinterpret_cast<const float4*>(dsT + (16 * j + n16) * DW_LD + 4 * (q ^ j) + 16 * t);
-        acc[j] = mfma4(av.x, bv.x, acc[j]);
-        acc[j] = mfma4(av.y, bv.y, acc[j]);
-        acc[j] = mfma4(av.z, bv.z, acc[j]);
-        acc[j] = mfma4(av.w, bv.w, acc[j]);
-      }
-    }
-    if (ci0 == 0) {
-      // this lane sums column tcol over pairs [16q, 16q + 16) of the stage
-      const float* tr = dsT + tcol * DW_LD + 16 * q;
-#pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(tr + 4 * (i ^ w));
-        tsum += ((v.x + v.y) + v.z) + v.w;
+        I.r[i] = a.in_rows[min(p + i, p_end - 1)];
+        I.o[i] = a.out_rows[min(p + i, p_end - 1)];
       }
     }
-    if (tid < 128) idx[buf][tid >> 6][tid & 63] = nidx;  // stage s's slot is free
-    buf ^= 1;
-    __syncthreads();
-  }
-  // write partial dW: lane holds rows 4q + v (ci), column n16 of tile j (co)
-  float* out = a.part + ((int64_t)k * a.maxc + c) * a.Cin * a.Cout;
+  };
+  auto load = [&](Stage& S, const Idx& I) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+    for (int i = 0; i < 4; ++i) {
+      if (V4) {
+        S.x[i] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(x) +
+                                               (uint64_t)(uint32_t)I.r[i] * bx);
+        S.d[i] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(dyb) +
+                                               (uint64_t)(uint32_t)I.o[i] * bd);
+      } else {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int ci = ci0 + 16 * w + 4 * q + v, co = co0 + 16 * j + n16;
-      if (ci < a.Cin && co < a.Cout) out[(int64_t)ci * a.Cout + co] = acc[j][v];
+        for (int e = 0; e < 4; ++e) {
+          S.x[i][e] = x[I.r[i] * ldx + cx[e]];
+          S.d[i][e] = dyb[I.o[i] * ldd + cd[e]];
+        }
+      }
     }
-  if (ci0 == 0) {
-    // combine the four quarters in a fixed order
-    const float t1 = __shfl_xor(tsum, 16, 64);
-    const float s01 = q & 1 ? t1 + tsum : tsum + t1;
-    const float t2 = __shfl_xor(s01, 32, 64);
-    const float s = q & 2 ? t2 + s01 : s01 + t2;
-    const int co = co0 + tcol;
-    if (q == 0 && co < a.Cout) a.partT[((int64_t)k * a.maxc + c) * a.Cout + co] = s;
+  };
+  // the MFMA operands of the two tiles
+  auto operands = [&](const v4f (&v)[4], v4u (&f)[2][3]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint32_t p[3], q[3];
+        split2(v[2 * j][2 * t], v[2 * j + 1][2 * t], p[0], p[1], p[2]);
+        split2(v[2 * j][2 * t + 1], v[2 * j + 1][2 * t + 1], q[0], q[1], q[2]);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const auto r = __builtin_amdgcn_permlane16_swap(p[s], q[s], false, false);
+          f[t][s][j] = r[0];
+          f[t][s][2 + j] = r[1];
+        }
+      }
+  };
+  v16f acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  v4f tsum = {0.f, 0.f, 0.f, 0.f};  // the lane's channels of dy over its pairs
+  int64_t p0 = p_begin + DW_ST * w;
+  if (p0 < p_end) {
+    constexpr int STEP = 4 * DW_ST;
+    Stage S;
+    Idx I;
+    load_idx(I, p0);
+    load(S, I);
+    load_idx(I, min(p0 + STEP, p_end - 1));
+    while (true) {
+      v4u X[2][3], D[2][3];
+      if (p0 + DW_ST > p_end) {  // the chunk's last stage: pairs past it are zero
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            S.d[i][e] = p0 + 4 * pg + i < p_end ? S.d[i][e] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          S.x[i][e] = fmaf(S.x[i][e], sgn, gs[e]);  // +-(x - g_in), rounded once
+          tsum[e] += S.d[i][e];
+        }
+      operands(S.x, X);
+      operands(S.d, D);
+      // the next stage's rows, and the indices after them, are on their way
+      // during this one's products (past the chunk: its last pairs, unused)
+      load(S, I);
+      p0 += STEP;
+      load_idx(I, min(p0 + STEP, p_end - 1));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < SPLIT_PROD; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = mfma_bf16(X[i][split_a(q)], D[j][split_b(q)], acc[i][j]);
+      if (p0 >= p_end) break;
+    }
   }
+  // Add the four waves' blocks, tile row i of x at a time.  Register 4 v + z of
+  // tile (i, j) holds operand row 8 v + 4 h + z of x and n32 of dy.
+  float* const out = a.part + ((int64_t)k * a.maxc + c) * a.Cin * a.Cout;
+  const int n32 = lane & 31, h = lane >> 5;
+  // over the lanes of a channel quad (pairs in a fixed order)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float t1 = __shfl_xor(tsum[e], 16, 64);
+    const float s1 = pg & 1 ? t1 + tsum[e] : tsum[e] + t1;
+    const float t2 = __shfl_xor(s1, 32, 64);
+    if (pg == 0) redT[w * 64 + 4 * cq + e] = s1 + t2;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (i) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        red[w * 2048 + (8 * (r >> 2) + 4 * h + (r & 3)) * 64 + 4 * (n32 & 15) + 2 * j +
+            (n32 >> 4)] = acc[i][j][r];
+    __syncthreads();
+    float v[8];
+    bool odd = false;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = u * NT + tid;  // operand row e / 64, column e % 64
+        v[u] = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+      odd = odd || !(v[u] * 0.f == 0.f);
+    }
+    // sums that are not finite (operands the split cannot hold): in plain fp32
+    if (__syncthreads_or(odd)) {
+      for (int u = 0; u < 8; ++u) {
+        const int m = (u * NT + tid) / 64;
+        const int ci = ci0 + 4 * (m & 15) + 2 * i + (m >> 4), co = co0 + (tid & 63);
+        if (ci >= a.Cin || co >= a.Cout) continue;
+        const float g = a.g_in[ci];
+        float s = 0.f;
+        for (int64_t p = p_begin; p < p_end; ++p)
+          s = fmaf(a.x[a.in_rows[p] * ldx + ci] - g, a.dyb[a.out_rows[p] * ldd + co], s);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (q == u) v[q] = s;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int m = (u * NT + tid) / 64;
+      const int ci = ci0 + 4 * (m & 15) + 2 * i + (m >> 4), co = co0 + (tid & 63);
+      if (ci < a.Cin && co < a.Cout) out[(int64_t)ci * a.Cout + co] = v[u];
+    }
+  }
+  if (ci0 == 0 && tid < 64 && co0 + tid < a.Cout)
+    a.partT[((int64_t)k * a.maxc + c) * a.Cout + co0 + tid] =
+        ((redT[tid] + redT[64 + tid]) + redT[128 + tid]) + redT[192 + tid];
 }
 
 // dW[k][ci][co] = sum_c part + g_in[ci] * u0[co];  T[k][co] = sum_c partT.
@@ -1409,10 +1429,10 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
     d.partT = partT;
     if (rb->n_pairs > 0) {
       const int64_t nwg = L.maxc * K * d.nblk;
-      const bool v4 = Cin % 4 == 0 && Cout % 4 == 0 &&
-                      ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dyb) |
-                        reinterpret_cast<uintptr_t>(g_in)) & 15) == 0;
       if (scn_status rc = timer_mark(TK_DW, 0, st)) return rc;
+      const bool v4 = Cin % 4 == 0 && Cout % 4 == 0 &&
+                      ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dyb)) & 15) ==
+                          0;
       if (v4)
         hipLaunchKernelGGL(dw_partial_kernel<true>, dim3((unsigned)nwg), dim3(NT), 0, st, d);
       else

@@ -59,24 +59,28 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
                                                        float* __restrict__ g_out) {
   if ((int)blockIdx.x >= np) {
     // g_pre[n] = B[n] + sum_k g W_k(., n) and g_out = act(g_pre): PRE_COLS
-    // columns per block, NT / PRE_COLS threads each, their sums added in order
-    __shared__ float part[NT];
+    // columns per block, NT / PRE_COLS threads each, in 64 bits (few products,
+    // and every output starts from them)
+    __shared__ double part[NT];
     const int c = threadIdx.x % PRE_COLS, t = threadIdx.x / PRE_COLS;
     const int n = ((int)blockIdx.x - np) * PRE_COLS + c;
-    float s = 0.f;
+    double s = 0.;
     if (n < Nc) {
       const int tot = K * Rk;
 #pragma unroll 4
       for (int q = t; q < tot; q += NT / PRE_COLS) {
         const int k = q / Rk, j = q - k * Rk;
-        s = fmaf(g[j], W[k * wk + j * wj + n * wn], s);
+        s = fma((double)g[j], (double)W[k * wk + j * wj + n * wn], s);
       }
     }
     part[threadIdx.x] = s;
     __syncthreads();
+    for (int q = NT / 2; q >= PRE_COLS; q >>= 1) {
+      if ((int)threadIdx.x < q) part[threadIdx.x] += part[threadIdx.x + q];
+      __syncthreads();
+    }
     if (t == 0 && n < Nc) {
-      float v = bias ? bias[n] : 0.f;
-      for (int q = 0; q < NT / PRE_COLS; ++q) v += part[q * PRE_COLS + c];
+      const float v = (float)(part[c] + (bias ? (double)bias[n] : 0.));
       g_pre[n] = v;
       g_out[n] = relu && !(v > 0.f) ? 0.f : v;
     }
@@ -95,6 +99,10 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
 #pragma unroll
   for (int e = 0; e < 8; ++e)
     v[e] = n < Nc && j0 + e < Rk ? W[k * wk + (j0 + e) * wj + n * wn] : 0.f;
+  if (k & 1) {  // odd offsets negated (add_item)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = -v[e];
+  }
   const Frag3 s = split8(v);
 #pragma unroll
   for (int p = 0; p < 3; ++p) Wp[((f * 2 + ct) * 3 + p) * 64 + lane] = s.s[p];
@@ -231,48 +239,58 @@ struct Turn {
   }
 };
 
-// Reads one row tile of a step, shifts and splits it.
-template <bool SUB>
-__device__ inline Frag3 turn_read(const char* b, const Turn& t, int rt, v4f g0, v4f g1) {
+// Reads one row tile of a step, shifts and splits it; NEG: times sgn (1 or
+// -1), with g0 and g1 already so.
+template <bool SUB, bool NEG>
+__device__ inline Frag3 turn_read(const char* b, const Turn& t, int rt, v4f g0, v4f g1,
+                                  float sgn) {
   const v4f x0 = *reinterpret_cast<const v4f*>(b + rt * 2048 + t.rd0);
   const v4f x1 = *reinterpret_cast<const v4f*>(b + rt * 2048 + t.rd1);
   float v[8];
 #pragma unroll
   for (int z = 0; z < 4; ++z) {
-    v[z] = SUB ? x0[z] - g0[z] : x0[z];
-    v[4 + z] = SUB ? x1[z] - g1[z] : x1[z];
+    v[z] = NEG ? fmaf(x0[z], sgn, -g0[z]) : SUB ? x0[z] - g0[z] : x0[z];
+    v[4 + z] = NEG ? fmaf(x1[z], sgn, -g1[z]) : SUB ? x1[z] - g1[z] : x1[z];
   }
   return split8(v);
 }
 
-// One step: 2 x 2 tiles of 32 rows x 32 columns, six products each, added to
-// acc (FIRST: acc starts from zero).
-template <bool FIRST>
+// One step: 2 x 2 tiles of 32 rows x 32 columns, products q0 .. q1 - 1 of the
+// six, added to acc (FIRST: acc starts from zero).
+template <bool FIRST, int q0 = 0, int q1 = SPLIT_PROD>
 __device__ inline void step_products(v16f (&acc)[2][2], const v4u (&W)[2][3], const Frag3 (&X)[2]) {
   v16f zero;
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 #pragma unroll
-  for (int q = 0; q < SPLIT_PROD; ++q)
+  for (int q = q0; q < q1; ++q)
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct)
         acc[rt][ct] = mfma_bf16(W[ct][split_a(q)], X[rt].s[split_b(q)],
-                                FIRST && q == 0 ? zero : acc[rt][ct]);
+                                FIRST && q == q0 ? zero : acc[rt][ct]);
 }
 
-// Sums in two levels, per offset and over the offsets: a chain over all
-// offsets' channels would round as often as 27 x 64 channels have steps (the
-// error of an input gradient against 64-bit sums: 3.1e-7 for one chain,
-// 1.3e-7 for two levels, 1.4e-7 for the two levels of the fp32 instruction).
-__device__ inline void add_offset(v16f (&acc)[2][2], const v16f (&part)[2][2]) {
+// Sums in two levels, of 64 channels of an offset (tile_wg_kernel; 32 in
+// tile_split_kernel) and over these: a chain over all of a row's products
+// would round with every one of their MFMAs.  An item's ten small products
+// come before its two large ones, so that a sum's first ones round while it is
+// still small.  Error of the benchmark's input gradient against 64-bit sums:
+// 3.1e-7 in one chain, 1.45e-7 in two levels without that order, 1.52e-7 in
+// levels of 32 channels, 1.33e-7 as it is, 1.42e-7 on the fp32 instruction.
+// The matrix core drops the bits of small addends below its adder, always
+// downwards; odd offsets' weights are packed negated and their sums
+// subtracted, so that these drifts cancel as well.
+__device__ inline void add_item(v16f (&acc)[2][2], const v16f (&part)[2][2], int k) {
+  const float sgn = k & 1 ? -1.f : 1.f;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[rt][ct][r] += part[rt][ct][r];
+      for (int r = 0; r < 16; ++r)
+        acc[rt][ct][r] = fmaf(part[rt][ct][r], sgn, acc[rt][ct][r]);
 }
 
 // A 32 x 32 quarter of a tile: a lane holds row 32 rt + n32 and, in register
@@ -475,33 +493,47 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
       wload(n2);
       const From qn = spread(R.row(xn, n.k), n.ch);
       xn = R.load(n2.k, lane);
+      // lists: sums of two items of an offset
+      const bool first = SORTED || TC == 1 || !(c.ch & 1);
+      Frag3 X[TC][2];
+      v4u Wf[TC][2][3];
 #pragma unroll
       for (int s = 0; s < TC; ++s) {
         commit(s);
         gather(qn, s, n.ch);
-        Frag3 X[2];
-        v4u Wf[2][3];
         v4f g0 = {}, g1 = {};
         if (SUB) {
           const float* gp = gsh + 16 * (TC * c.ch + s) + 8 * (lane >> 5);
           g0 = *reinterpret_cast<const v4f*>(gp);
           g1 = *reinterpret_cast<const v4f*>(gp + 4);
         }
+        // one chain (SORTED) needs odd offsets' rows negated like their weights
+        const float sgn = SORTED && (c.k & 1) ? -1.f : 1.f;
+        if (SORTED) {
+          g0 *= sgn;
+          g1 *= sgn;
+        }
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB>(buf, turn, rt, g0, g1);
+        for (int rt = 0; rt < 2; ++rt)
+          X[s][rt] = turn_read<SUB, SORTED>(buf, turn, rt, g0, g1, sgn);
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
           for (int q = 0; q < 3; ++q)
-            Wf[ct][q] = *reinterpret_cast<const v4u*>(wl + ((s * 2 + ct) * 3 + q) * 1024);
+            Wf[s][ct][q] = *reinterpret_cast<const v4u*>(wl + ((s * 2 + ct) * 3 + q) * 1024);
         if (SORTED)
-          step_products<false>(acc, Wf, X);
-        else if (s == 0 && c.ch == 0)
-          step_products<true>(part, Wf, X);
+          step_products<false>(acc, Wf[s], X[s]);
+        else if (s == 0 && first)
+          step_products<true, 0, SPLIT_PROD - 1>(part, Wf[s], X[s]);
         else
-          step_products<false>(part, Wf, X);
+          step_products<false, 0, SPLIT_PROD - 1>(part, Wf[s], X[s]);
       }
-      if (!SORTED && c.ch == nchunk - 1) add_offset(acc, part);
+      if (!SORTED) {
+#pragma unroll
+        for (int s = 0; s < TC; ++s)
+          step_products<false, SPLIT_PROD - 1, SPLIT_PROD>(part, Wf[s], X[s]);
+        if (TC == 1 || (c.ch & 1) || c.ch == nchunk - 1) add_item(acc, part, c.k);
+      }
       c = n;
       n = n2;
       n2.advance(nchunk);
@@ -593,7 +625,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
       g1 = *reinterpret_cast<const v4f*>(gp + 4);
     }
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB>(buf + s * 4096, turn, rt, g0, g1);
+    for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB, false>(buf + s * 4096, turn, rt, g0, g1, 1.f);
     if (s == 0)
       step_products<true>(part, A.f, X);
     else
@@ -640,7 +672,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
         wload(n, s, A[s]);
         __builtin_amdgcn_sched_barrier(0);
       }
-      add_offset(acc, part);  // (per item: its chunk of the offset's channels)
+      add_item(acc, part, c.k);
       c = n;
       n = nn;
       nn = step_item(nn);

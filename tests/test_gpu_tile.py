@@ -1,5 +1,5 @@
-"""The tile contraction of stride-1 rulebooks (forward and input gradient) at
-the sizes where it can go wrong: rows around the tile of 64 and the work-group
+"""The tile contraction of stride-1 rulebooks (forward and input gradient) and
+the weight gradient at the sizes where it can go wrong: rows around the tile of 64 and the work-group
 of 256, both its kernels (four waves on one tile; four tiles sharing their
 weights), pair lists and the mask-sorted view, channel counts around the
 16-channel step and the 64-column block, and operands that the bf16 split
@@ -126,3 +126,49 @@ def test_values_past_the_split(scn, view, big):
     assert np.array_equal(y[np.isinf(y)], f32[np.isinf(y)])
     ok = np.isfinite(f32) & np.isfinite(mass)
     _check(y[ok], want[ok], mass[ok], rb.K * 32)
+
+
+def _weight_gradient(rb, ir, orr, x, g, dy):
+    """(dW, sum of |terms|) in float64; dW = sum (x - g)^T dy + g^T sum dy"""
+    xs, d = torch.from_numpy(x.astype(np.float64) - g), torch.from_numpy(dy.astype(np.float64))
+    g64 = torch.from_numpy(g.astype(np.float64))
+    dW = torch.zeros(rb.K, x.shape[1], dy.shape[1], dtype=torch.float64)
+    mass = torch.zeros_like(dW)
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        dW[k] = xs[i].t() @ d[o] + torch.outer(g64, d.sum(0))
+        mass[k] = xs[i].abs().t() @ d[o].abs() + torch.outer(g64.abs(), d.abs().sum(0))
+    return dW.numpy(), mass.numpy()
+
+
+@pytest.mark.parametrize("case", [
+    # f, s, m, n, cin, cout: one pair, around a stage of 16 and four waves of
+    # them, several chunks, quads and single floats, several blocks
+    (1, 1, 9, 1, 4, 4), (1, 1, 9, 15, 64, 64), (1, 1, 9, 16, 1, 1), (1, 1, 9, 17, 65, 64),
+    (1, 1, 9, 63, 16, 130), (1, 1, 9, 64, 3, 5), (1, 1, 9, 65, 128, 68), (2, 1, 14, 1000, 33, 34),
+    (3, 1, 40, 30000, 64, 60), (3, 2, 12, 300, 32, 96), (2, 2, 30, 5000, 7, 64),
+    (1, 1, 60, 131073, 8, 12),
+])
+def test_weight_gradient_sizes(scn, case):
+    f, s, m, n, cin, cout = case
+    rng = stream_rng(31, 7)
+    c = random_sites(rng, 1, (m, m, m), n, shuffle=True)
+    rb = scn.build_rulebook(dev(c), (1, m, m, m), f, s)
+    x = rng.standard_normal((n, cin)).astype(np.float32)
+    g = rng.standard_normal(cin).astype(np.float32)
+    W = rng.standard_normal((rb.K, cin, cout)).astype(np.float32)
+    dy = rng.uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+    _, ir, orr = (t.long().cpu() for t in rb.export())
+    got = scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy))
+    want, mass = _weight_gradient(rb, ir, orr, x, g, dy)
+    _check(host(got["dW"]), want, mass, max(rb.n_pairs // rb.K, 1))
+    # special values reach exactly the entries they reach in fp32
+    x[0, cin - 1] = np.inf
+    dy[rb.a_out - 1, 0] = -3.402e38
+    with np.errstate(all="ignore"):
+        want, mass = _weight_gradient(rb, ir, orr, x, g, dy)
+    got = host(scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy))["dW"])
+    ok = np.isfinite(want) & (np.abs(mass) < 3e38)
+    assert not np.any(np.isfinite(got) & np.isinf(want))
+    assert np.array_equal(np.isnan(got[ok]), np.isnan(want[ok]))
+    _check(got[ok], want[ok], mass[ok], max(rb.n_pairs // rb.K, 1))
