@@ -1025,7 +1025,7 @@ constexpr int DW_ROUNDS = 4;
 
 struct BwdLayout {
   int64_t chp, maxc, nblk;
-  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, o_pad, pad, total;
+  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, o_pad, pad, o_few, total;
 };
 
 BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) {
@@ -1062,6 +1062,9 @@ BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) 
   L.o_pad = cur;
   L.pad = rb->s == 1 ? tile_pad_bytes(rb->a_out, Cout) : 0;
   cur += al(L.pad);
+  L.o_few = cur;
+  if (rb->s == 1 && few_channels(rb->K, Cin))
+    cur += al((size_t)few_groups(rb->a_out) * ((size_t)rb->K * Cin + 1) * Cout * 4);
   L.total = cur;
   return L;
 }
@@ -1100,7 +1103,9 @@ static FwdScratch fwd_scratch(const scn_rulebook* rb, int Cin, int Cout) {
   f.gw_bytes = ((size_t)(rb->K + 1) * f.NcP * sizeof(float) + 255) & ~size_t(255);
   f.total = f.bound = f.gw_bytes + (size_t)rb->K * f.NcP * f.RkP * sizeof(float);
   if (rb->s == 1)
-    f.total = f.gw_bytes + TILE_PAD * sizeof(float) + tile_pack_bytes(rb->K, Cin, Cout);
+    f.total = f.gw_bytes + TILE_PAD * sizeof(float) +
+              (few_channels(rb->K, Cin) ? tile_pack_bytes(1, rb->K * Cin, Cout)
+                                        : tile_pack_bytes(rb->K, Cin, Cout));
   return f;
 }
 
@@ -1131,8 +1136,10 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
   if (rb->s == 1) {
     float* const sub = Wp;  // the shifted rows' g_in, then the split weights
     uint32_t* const Ws = reinterpret_cast<uint32_t*>(Wp + TILE_PAD);
-    if (scn_status rc = tile_pack(W, (int64_t)Cin * Cout, Cout, 1, rb->K, Cin, Cout, g_in, bias,
-                                  relu, Ws, sub, gpre, g_out, st))
+    const bool few = few_channels(rb->K, Cin);
+    if (scn_status rc = tile_pack(W, (int64_t)Cin * Cout, Cout, 1, few ? 1 : rb->K,
+                                  few ? rb->K * Cin : Cin, Cout, g_in, Cin, bias, relu, Ws, sub,
+                                  gpre, g_out, st))
       return rc;
     TileArgs t{};
     t.src = x;
@@ -1163,7 +1170,8 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
     t.dst = y;
     scn_status rc;
     if (pad && (rc = tile_pad(t, pad, st))) return rc;
-    if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = launch_tile(t, st))) return rc;
+    if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = few ? few_forward(t, st) : launch_tile(t, st)))
+      return rc;
     return timer_mark(TK_FWD, 1, st);
   }
   hipLaunchKernelGGL(pack_w_kernel, dim3((unsigned)ceil_div((int64_t)rb->K * NcP * RkP, 256)),
@@ -1243,7 +1251,7 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
   const Allocator al = current_allocator();
   // without room for padded rows, the rows are gathered as they are
   const size_t at = (fs.total + 255) & ~size_t(255);
-  size_t pad = rb->s == 1 ? tile_pad_bytes(rb->a_in, Cin) : 0;
+  size_t pad = rb->s == 1 && !few_channels(rb->K, Cin) ? tile_pad_bytes(rb->a_in, Cin) : 0;
   scn_status rc = dalloc(reinterpret_cast<void**>(&gw), pad ? at + pad : fs.total, st, al);
   if (rc == SCN_ERR_NOMEM && pad) {
     clear_error();
@@ -1328,6 +1336,41 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
   float* gzero = reinterpret_cast<float*>(base + L.o_gz);
   const int K = rb->K;
 
+  // A first layer's weight and bias gradients (few channels, no dx, no dg_in)
+  // read dy and y once, with no masked copy and no gathers of their rows.
+  if (rb->s == 1 && dW && !dx && !dg_in && few_channels(K, Cin)) {
+    TileArgs t{};
+    t.src = x;
+    t.ld = Cin;
+    t.sub = g_in;
+    t.gidx = rb->in_rows;
+    t.aidx = rb->out_rows;
+    t.tpos = rb->otile;
+    t.nb = rb->fnb;
+    t.nb_off = rb->fnb_off;
+    t.fperm = rb->fperm;
+    t.fmask = rb->fmask;
+    t.nsrc = rb->a_in;
+    t.npairs = rb->n_pairs;
+    t.ntile = ceil_div(rb->a_out, TILE);
+    t.nrows = rb->a_out;
+    t.K = K;
+    t.Rk = Cin;
+    t.Nc = Cout;
+    const float* const mask = relu ? y : nullptr;
+    float* const fpart = reinterpret_cast<float*>(base + L.o_few);
+    float* const fS = fpart + (size_t)few_groups(rb->a_out) * K * Cin * Cout;
+    scn_status rc;
+    if ((rc = timer_mark(TK_DW, 0, st)) ||
+        (rc = few_partials(t, dy, mask, Cout, fpart, fS, st)) || (rc = timer_mark(TK_DW, 1, st)))
+      return rc;
+    hipLaunchKernelGGL(finish_vec_kernel, dim3((unsigned)Cout), dim3(NT), 0, st, fS,
+                       rb->a_out > 0 ? (int64_t)few_groups(rb->a_out) : 0, Cout, g_out, dg_out,
+                       relu, S, u0, dbias);
+    SCN_LAUNCH_CHECK();
+    return few_reduce(t, dy, mask, Cout, fpart, rb->off_dev, u0, dW, st);
+  }
+
   // dȳ and S (column sums over active outputs)
   if (rb->a_out > 0) {
     const bool v4 = (Cout % 4 == 0) && Cout <= 4 * NT &&
@@ -1350,7 +1393,7 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
   // input gradient: accumulate over input ranks with W_k^T
   if (dx && rb->a_in > 0 && rb->s == 1) {
     scn_status rc = tile_pack(W, (int64_t)Cin * Cout, 1, Cout, K, Cout, Cin, nullptr,
-                              nullptr, 0, reinterpret_cast<uint32_t*>(wpack), gzero, nullptr,
+                              1, nullptr, 0, reinterpret_cast<uint32_t*>(wpack), gzero, nullptr,
                               nullptr, st);
     if (rc) return rc;
     TileArgs a{};

@@ -45,11 +45,11 @@ constexpr int TILE_PAD = 256;  // floats of TileArgs::sub (Rk <= 256, padded to 
 int tile_steps(int Rk);
 size_t tile_pack_bytes(int K, int Rk, int Nc);
 
-// Splits W_k(j, n) into a.Wp's layout; fills sub[0 .. TILE_PAD) with g (zeros
-// if null or past Rk).  With g_pre (else null): g_pre = bias + sum_k g W_k and
+// Splits W_k(j, n) into a.Wp's layout; fills sub[0 .. TILE_PAD) with g[j % gm]
+// (zeros if g is null or past Rk).  With g_pre (else null): g_pre = bias + sum_k g W_k and
 // g_out = act(g_pre).
 scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
-                     const float* g, const float* bias, int relu, uint32_t* Wp, float* sub,
+                     const float* g, int gm, const float* bias, int relu, uint32_t* Wp, float* sub,
                      float* g_pre, float* g_out, hipStream_t st);
 
 // Rows whose channel count is no multiple of 16 are copied to a multiple
@@ -60,5 +60,20 @@ size_t tile_pad_bytes(int64_t rows, int Rk);
 scn_status tile_pad(TileArgs& a, float* out, hipStream_t st);
 
 scn_status launch_tile(const TileArgs& a, hipStream_t st);
+
+// Layers of few input channels, whose offsets join the reduction.  Arguments
+// as for launch_tile (gidx, aidx: the pair lists, also beside the dense view),
+// but Wp packed from W as one offset of K*Cin entries (gm = Cin).
+bool few_channels(int K, int Cin);
+scn_status few_forward(const TileArgs& a, hipStream_t st);
+// The weight gradient without dx and dg_in, from dy (times y > 0 unless y is
+// null): partials part [few_groups][K*Cin][Cout] and column sums partS
+// [few_groups][Cout], then dW = their sum + g_in u0.
+int few_groups(int64_t nrows);
+scn_status few_partials(const TileArgs& a, const float* dy, const float* y, int Cout, float* part,
+                        float* partS, hipStream_t st);
+scn_status few_reduce(const TileArgs& a, const float* dy, const float* y, int Cout,
+                      const float* part, const int64_t* off, const float* u0, float* dW,
+                      hipStream_t st);
 
 }  // namespace scn

@@ -51,7 +51,7 @@ constexpr int PRE_COLS = 8;
 __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__ W, int64_t wk,
                                                        int64_t wj, int64_t wn, int K, int Rk,
                                                        int Nc, int nst, int ncb,
-                                                       const float* __restrict__ g,
+                                                       const float* __restrict__ g, int gm,
                                                        const float* __restrict__ bias, int relu,
                                                        v4u* __restrict__ Wp,
                                                        float* __restrict__ sub, int np,
@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
 #pragma unroll 4
       for (int q = t; q < tot; q += NT / PRE_COLS) {
         const int k = q / Rk, j = q - k * Rk;
-        s = fma((double)g[j], (double)W[k * wk + j * wj + n * wn], s);
+        s = fma((double)g[j % gm], (double)W[k * wk + j * wj + n * wn], s);
       }
     }
     part[threadIdx.x] = s;
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
     return;
   }
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i < TILE_PAD) sub[i] = g && i < Rk ? g[i] : 0.f;
+  if (i < TILE_PAD) sub[i] = g && i < Rk ? g[i % gm] : 0.f;
   const int lane = (int)(i & 63), ct = (int)((i >> 6) & 1);
   const int64_t f = i >> 7;  // (k*ncb + cb)*nst + step
   if (f >= (int64_t)K * ncb * nst) return;
@@ -358,6 +358,37 @@ __device__ inline int64_t xcd_item(int64_t b, int64_t n) {
   return x * base + min(x, rem) + j;
 }
 
+// The accumulators leave through LDS (ob, the wave's own), 32 rows at a time,
+// so that a store instruction writes whole rows, 16 lanes each: 16-byte pieces
+// of 32 rows at a time cost the 1.1 GB output of the benchmark's layer 0.56 ms.
+constexpr int OUT_LD = 68;                 // floats per row
+constexpr int OUT_B = 32 * OUT_LD * 4;     // bytes of ob
+template <bool SUB, bool SORTED>
+__device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R, v16f (&acc)[2][2],
+                                  float* ob, int cb, int lane) {
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    wave_sync();
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      redo_if_special<SUB, SORTED>(a, R, acc[rt][ct], rt, ct, cb, lane);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<v4f*>(ob + (lane & 31) * OUT_LD + 32 * ct + 8 * j + 4 * (lane >> 5)) =
+            v4f{acc[rt][ct][4 * j], acc[rt][ct][4 * j + 1], acc[rt][ct][4 * j + 2],
+                acc[rt][ct][4 * j + 3]};
+    }
+    wave_sync();
+    const int col = 64 * cb + 4 * (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = 4 * i + (lane >> 4);
+      put4<SORTED, SORTED>(a, R.row0 + 32 * rt + r, col,
+                           *reinterpret_cast<const v4f*>(ob + r * OUT_LD + 4 * (lane & 15)));
+    }
+  }
+}
+
 // Large layers: four waves, a tile of 64 rows each, walk the same items; the
 // item's weights are loaded into LDS once for all of them, an item ahead, and
 // so are each step's rows into registers.  Two or three work-groups per CU:
@@ -368,8 +399,6 @@ __device__ inline int64_t xcd_item(int64_t b, int64_t n) {
 // 64-bit sums on the benchmark's layer, as before it 3.7e-7), the lists' in
 // two levels.
 constexpr int WGW = 4;              // waves per work-group
-constexpr int OUT_LD = 68;          // floats per row of the epilogue's LDS tile
-constexpr int OUT_B = 32 * OUT_LD * 4;
 constexpr size_t wg_lds(int tc) {
   return std::max<size_t>((size_t)tc * 12288 + WGW * 4096, (size_t)WGW * OUT_B);
 }
@@ -541,31 +570,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
     }
   }
   if (!live) return;
-  // The accumulators leave through LDS, 32 rows at a time, so that a store
-  // instruction writes whole rows (16 lanes each): 16-byte pieces of 32 rows
-  // at a time cost the 1.1 GB output of the benchmark's layer 0.56 ms.
-  float* const ob = reinterpret_cast<float*>(smem + w * OUT_B);
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    wave_sync();
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      redo_if_special<SUB, SORTED>(a, R, acc[rt][ct], rt, ct, cb, lane);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<v4f*>(ob + (lane & 31) * OUT_LD + 32 * ct + 8 * j + 4 * (lane >> 5)) =
-            v4f{acc[rt][ct][4 * j], acc[rt][ct][4 * j + 1], acc[rt][ct][4 * j + 2],
-                acc[rt][ct][4 * j + 3]};
-    }
-    wave_sync();
-    const int col = 64 * cb + 4 * (lane & 15);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = 4 * i + (lane >> 4);
-      put4<SORTED, SORTED>(a, R.row0 + 32 * rt + r, col,
-                   *reinterpret_cast<const v4f*>(ob + r * OUT_LD + 4 * (lane & 15)));
-    }
-  }
+  store_tile<SUB, SORTED>(a, R, acc, reinterpret_cast<float*>(smem + w * OUT_B), cb, lane);
 }
 
 // Small layers: the four waves of a work-group share one tile and take every
@@ -709,6 +714,284 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
                  v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
 }
 
+// ---------------------------------------------------------------------------
+// Few input channels (a network's first layer): the offsets join the
+// reduction.  A row's window values, x - g_in at j = k Cin + c and zero where
+// the offset is absent, make one reduction of J = K Cin entries (27 for a
+// 3x3x3 filter on one channel) against W as the J x Cout matrix it is; with
+// 16-channel steps per offset, 15 of 16 products were padding.  The forward is
+// then bound by its output (1.8M rows x 64: 0.46 GB), the weight gradient by
+// reading dy (and y), each once.
+// ---------------------------------------------------------------------------
+constexpr int FEW_C = 4, FEW_J = 96;
+
+// V(row, j) of the wave's tile: v[row * ldr + j * ldj], times sgn; zeroed first.
+template <bool SORTED>
+__device__ inline void few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
+                                  int ldj, int words, float sgn, int lane) {
+  for (int i = lane; i < words / 4; i += 64)
+    reinterpret_cast<v4f*>(v)[i] = v4f{0.f, 0.f, 0.f, 0.f};
+  wave_sync();
+  uint32_t rest = R.U;
+  while (rest) {
+    // eight offsets at a time, so that their loads overlap (past the last one
+    // it is repeated: the same value again)
+    int k[8], r[8];
+    Idx x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      k[i] = rest ? __builtin_ctz(rest) : k[i ? i - 1 : 0];
+      rest &= rest - 1;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = R.load(k[i], lane);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = R.row(x[i], k[i]);
+    for (int c = 0; c < a.Rk; ++c) {
+      float t[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i] = a.src[(int64_t)max(r[i], 0) * a.ld + c];
+      const float g = a.sub[c];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (r[i] >= 0) v[lane * ldr + (k[i] * a.Rk + c) * ldj] = sgn * (t[i] - g);
+    }
+  }
+  wave_sync();
+}
+
+__host__ __device__ constexpr int few_lds(int nst, int ncb) {
+  const int v = 256 * (16 * nst + 4);
+  return ncb > 1 ? v + OUT_B : v > OUT_B ? v : OUT_B;
+}
+
+template <bool SORTED>
+__global__ void __launch_bounds__(64 * WGW, 2) few_fwd_kernel(TileArgs a, int nst, int ncb) {
+  extern __shared__ char smem[];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ldr = 16 * nst + 4;
+  const int64_t tile = xcd_item(blockIdx.x, gridDim.x) * WGW + w;
+  if (tile >= a.ntile) return;
+  // one column block: the values' room is free when the tile leaves
+  float* const v = reinterpret_cast<float*>(smem + w * few_lds(nst, ncb));
+  float* const ob = ncb == 1 ? v : v + 64 * ldr;
+  Rows<SORTED> R;
+  R.init(a, tile, lane);
+  few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane);
+  const int n32 = lane & 31, h = lane >> 5;
+  for (int cb = 0; cb < ncb; ++cb) {
+    v16f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const v4u* wp = reinterpret_cast<const v4u*>(a.Wp) + (int64_t)cb * nst * 384 + lane;
+    for (int s = 0; s < nst; ++s) {
+      v4u Wf[2][3];
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) Wf[ct][q] = wp[(s * 6 + ct * 3 + q) * 64];
+      Frag3 X[2];
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        const float* p = v + (32 * rt + n32) * ldr + 16 * s + 8 * h;
+        const v4f p0 = *reinterpret_cast<const v4f*>(p), p1 = *reinterpret_cast<const v4f*>(p + 4);
+        const float e[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+        X[rt] = split8(e);
+      }
+      step_products<false>(acc, Wf, X);
+    }
+    store_tile<true, SORTED>(a, R, acc, ob, cb, lane);
+  }
+}
+
+// dW partials and column sums of dy (masked by y > 0 under ReLU) of one 64
+// column block: every wave takes tiles in turn, JT tiles of 32 reduction
+// entries by 64 columns in registers; a work-group adds its four waves' sums.
+// Odd waves sum the negated products (see dw_partial_kernel).
+struct FewArgs {
+  TileArgs t;          // rows of x; nrows, ntile of the outputs
+  const float *dy, *y; // [nrows][Cout]; y null without ReLU
+  int Cout, J;
+  float* part;         // [work-groups][J][Cout]
+  float* partS;        // [work-groups][Cout]
+};
+
+template <int JT, bool SORTED, bool V4>
+__global__ void __launch_bounds__(64 * WGW, 2) few_dw_kernel(FewArgs f) {
+  extern __shared__ char smem[];
+  const TileArgs& a = f.t;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pg = lane >> 4, cq = lane & 15, n32 = lane & 31, h = lane >> 5;
+  constexpr int LDJ = 68;  // floats per reduction entry: 64 rows and padding
+  float* const v = reinterpret_cast<float*>(smem) + w * (32 * JT * LDJ);
+  const int co0 = 64 * blockIdx.y;
+  const float sgn = w & 1 ? -1.f : 1.f;
+  int cd[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    cd[e] = V4 ? min(co0 + 4 * cq, f.Cout - 4) + e : min(co0 + 4 * cq + e, f.Cout - 1);
+  v16f acc[JT][2];
+#pragma unroll
+  for (int i = 0; i < JT; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  v4f tsum = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t tile = (int64_t)blockIdx.x * WGW + w; tile < a.ntile;
+       tile += (int64_t)gridDim.x * WGW) {
+    Rows<SORTED> R;
+    R.init(a, tile, lane);
+    wave_sync();
+    few_values<SORTED>(a, R, v, 1, LDJ, 32 * JT * LDJ, sgn, lane);
+    v4f d[4][4];
+    auto load = [&](int st) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t pos = R.row0 + 16 * st + 4 * pg + i;
+        const bool live = pos < a.nrows;
+        const int64_t p = live ? pos : a.nrows - 1;
+        const int64_t row = SORTED ? (int64_t)a.fperm[p] : p;
+        v4f t, m;
+        if (V4) {
+          t = *reinterpret_cast<const v4f*>(f.dy + row * f.Cout + cd[0]);
+          if (f.y) m = *reinterpret_cast<const v4f*>(f.y + row * f.Cout + cd[0]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            t[e] = f.dy[row * f.Cout + cd[e]];
+            if (f.y) m[e] = f.y[row * f.Cout + cd[e]];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          d[st][i][e] = live && (!f.y || m[e] > 0.f) ? t[e] : 0.f;
+      }
+    };
+#pragma unroll
+    for (int st = 0; st < 4; ++st) load(st);
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      // rows 16 st + 8 h + 0..7 of column 4 (m & 15) + 2 t + (m >> 4)
+      v4u D[2][3];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          uint32_t p[3], q[3];
+          split2(d[st][2 * j][2 * t], d[st][2 * j + 1][2 * t], p[0], p[1], p[2]);
+          split2(d[st][2 * j][2 * t + 1], d[st][2 * j + 1][2 * t + 1], q[0], q[1], q[2]);
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {
+            const auto r = __builtin_amdgcn_permlane16_swap(p[s], q[s], false, false);
+            D[t][s][j] = r[0];
+            D[t][s][2 + j] = r[1];
+          }
+        }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tsum += d[st][i];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        const float* p = v + (32 * jt + n32) * LDJ + 16 * st + 8 * h;
+        const v4f p0 = *reinterpret_cast<const v4f*>(p), p1 = *reinterpret_cast<const v4f*>(p + 4);
+        const float e[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+        const Frag3 X = split8(e);
+#pragma unroll
+        for (int q = 0; q < SPLIT_PROD; ++q)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            acc[jt][t] = mfma_bf16(X.s[split_a(q)], D[t][split_b(q)], acc[jt][t]);
+      }
+    }
+  }
+  // the four waves' sums, 32 reduction entries at a time
+  float* const red = reinterpret_cast<float*>(smem);  // [4][32][64]
+  float* const redT = red + 4 * 2048;                 // [4][64]
+  float* const out = f.part + (int64_t)blockIdx.x * f.J * f.Cout;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float t1 = __shfl_xor(tsum[e], 16, 64);
+    const float s1 = pg & 1 ? t1 + tsum[e] : tsum[e] + t1;
+    const float t2 = __shfl_xor(s1, 32, 64);
+    tsum[e] = s1 + t2;
+  }
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt) {
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        red[w * 2048 + (8 * (r >> 2) + 4 * h + (r & 3)) * 64 + 4 * (n32 & 15) + 2 * t +
+            (n32 >> 4)] = acc[jt][t][r];
+    if (jt == 0 && pg == 0)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) redT[w * 64 + 4 * cq + e] = tsum[e];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = u * 256 + tid, j = 32 * jt + e / 64, co = co0 + (tid & 63);
+      if (j < f.J && co < f.Cout)
+        out[(int64_t)j * f.Cout + co] =
+            (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+    }
+    if (jt == 0 && tid < 64 && co0 + tid < f.Cout)
+      f.partS[(int64_t)blockIdx.x * f.Cout + co0 + tid] =
+          (redT[tid] + redT[64 + tid]) + (redT[128 + tid] + redT[192 + tid]);
+  }
+}
+
+// dW[j][co] = sum of the partials + g_in[c] u0[co].  A block covers FR_E
+// elements; thread group g of FR_G sums the partials g (mod FR_G) in order,
+// then the group sums are added in order.  An element that is not finite is
+// summed again over its offset's pairs in fp32.
+constexpr int FR_E = 32, FR_G = 8;
+__global__ void __launch_bounds__(FR_E * FR_G) few_reduce_kernel(
+    FewArgs f, int nwg, const int64_t* __restrict__ off, const float* __restrict__ u0,
+    float* __restrict__ dW) {
+  __shared__ float red[FR_G][FR_E];
+  const int le = threadIdx.x % FR_E, g = threadIdx.x / FR_E;
+  const int64_t i = (int64_t)blockIdx.x * FR_E + le, n = (int64_t)f.J * f.Cout;
+  float s = 0.f;
+  if (i < n) {
+#pragma unroll 4
+    for (int c = g; c < nwg; c += FR_G) s += f.part[c * n + i];
+  }
+  red[g][le] = s;
+  __syncthreads();
+  float t = red[0][le];
+#pragma unroll
+  for (int h = 1; h < FR_G; ++h) t += red[h][le];
+  if (__syncthreads_or(i < n && !(t * 0.f == 0.f))) {
+    s = 0.f;
+    if (i < n && !(t * 0.f == 0.f)) {
+      const int j = (int)(i / f.Cout), co = (int)(i % f.Cout), k = j / f.t.Rk, c = j - k * f.t.Rk;
+      for (int64_t p = off[k] + g; p < off[k + 1]; p += FR_G) {
+        const int64_t o = f.t.aidx[p];
+        const float d = !f.y || f.y[o * f.Cout + co] > 0.f ? f.dy[o * f.Cout + co] : 0.f;
+        s = fmaf(f.t.src[(int64_t)f.t.gidx[p] * f.t.ld + c] - f.t.sub[c], d, s);
+      }
+    } else if (i < n && g == 0) {
+      s = t;
+    }
+    red[g][le] = s;
+    __syncthreads();
+    t = red[0][le];
+#pragma unroll
+    for (int h = 1; h < FR_G; ++h) t += red[h][le];
+  }
+  if (g == 0 && i < n) {
+    const int j = (int)(i / f.Cout);
+    dW[i] = t + f.t.sub[j % f.t.Rk] * u0[i % f.Cout];
+  }
+}
+
 typedef void (*TileFn)(TileArgs, int, int);
 
 template <int TC, bool VEC>
@@ -749,13 +1032,13 @@ size_t tile_pack_bytes(int K, int Rk, int Nc) {
 }
 
 scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
-                     const float* g, const float* bias, int relu, uint32_t* Wp, float* sub,
+                     const float* g, int gm, const float* bias, int relu, uint32_t* Wp, float* sub,
                      float* g_pre, float* g_out, hipStream_t st) {
   const int nst = tile_steps(Rk), ncb = (int)ceil_div(Nc, 64);
   const int64_t n = std::max<int64_t>((int64_t)K * ncb * nst * 128, TILE_PAD);
   const int64_t np = ceil_div(n, NT), ng = g_pre ? ceil_div(Nc, PRE_COLS) : 0;
   hipLaunchKernelGGL(tile_pack_kernel, dim3((unsigned)(np + ng)), dim3(NT), 0, st, W, wk, wj, wn,
-                     K, Rk, Nc, nst, ncb, g, bias, relu, reinterpret_cast<v4u*>(Wp), sub, (int)np,
+                     K, Rk, Nc, nst, ncb, g, gm, bias, relu, reinterpret_cast<v4u*>(Wp), sub, (int)np,
                      g_pre, g_out);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
@@ -799,6 +1082,73 @@ scn_status launch_tile(const TileArgs& a, hipStream_t st) {
   const int64_t nwg = split ? items : ceil_div(a.ntile, WGW) * ncb;
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(split ? NT : 64 * WGW), smem, st, a, nst / tc,
                      ncb);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+bool few_channels(int K, int Cin) { return Cin <= FEW_C && K * Cin <= FEW_J; }
+
+// raises a kernel's dynamic LDS limit, once per process and kernel
+static scn_status allow_lds(const void* fn, std::atomic<size_t>& had, size_t want) {
+  if (want <= 65536 || had.load(std::memory_order_acquire) >= want) return SCN_OK;
+  SCN_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want));
+  had.store(want, std::memory_order_release);
+  return SCN_OK;
+}
+
+scn_status few_forward(const TileArgs& a, hipStream_t st) {
+  if (a.nrows <= 0 || a.ntile <= 0) return SCN_OK;
+  const int nst = tile_steps(a.K * a.Rk), ncb = (int)ceil_div(a.Nc, 64);
+  const size_t smem = (size_t)WGW * few_lds(nst, ncb);  // at most 137 KB (6 steps)
+  auto fn = a.nb ? few_fwd_kernel<true> : few_fwd_kernel<false>;
+  static std::atomic<size_t> had[2];
+  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn), had[a.nb != nullptr], smem))
+    return rc;
+  hipLaunchKernelGGL(fn, dim3((unsigned)ceil_div(a.ntile, WGW)), dim3(64 * WGW), smem, st, a,
+                     nst, ncb);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+// Work-groups of the weight gradient: two per CU (a third spills), a tile per wave at least
+int few_groups(int64_t nrows) {
+  return (int)std::min<int64_t>(512, std::max<int64_t>(1, ceil_div(nrows, TILE * WGW)));
+}
+
+template <int JT>
+static scn_status few_dw_launch(const FewArgs& f, bool v4, int nwg, hipStream_t st) {
+  const size_t smem = std::max<size_t>((size_t)WGW * 32 * JT * 68 * 4, (4 * 2048 + 256) * 4);
+  auto fn = f.t.nb ? (v4 ? few_dw_kernel<JT, true, true> : few_dw_kernel<JT, true, false>)
+                   : (v4 ? few_dw_kernel<JT, false, true> : few_dw_kernel<JT, false, false>);
+  static std::atomic<size_t> had[4];
+  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn),
+                                had[(f.t.nb ? 2 : 0) + (v4 ? 1 : 0)], smem))
+    return rc;
+  hipLaunchKernelGGL(fn, dim3((unsigned)nwg, (unsigned)ceil_div(f.Cout, 64)), dim3(64 * WGW), smem,
+                     st, f);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+scn_status few_partials(const TileArgs& a, const float* dy, const float* y, int Cout, float* part,
+                        float* partS, hipStream_t st) {
+  if (a.nrows <= 0) return SCN_OK;
+  FewArgs f{a, dy, y, Cout, a.K * a.Rk, part, partS};
+  const bool v4 = (Cout & 3) == 0 && ((reinterpret_cast<uintptr_t>(dy) |
+                                       reinterpret_cast<uintptr_t>(y)) & 15) == 0;
+  const int nwg = few_groups(a.nrows);
+  if (f.J <= 32) return few_dw_launch<1>(f, v4, nwg, st);
+  if (f.J <= 64) return few_dw_launch<2>(f, v4, nwg, st);
+  return few_dw_launch<3>(f, v4, nwg, st);
+}
+
+scn_status few_reduce(const TileArgs& a, const float* dy, const float* y, int Cout,
+                      const float* part, const int64_t* off, const float* u0, float* dW,
+                      hipStream_t st) {
+  FewArgs f{a, dy, y, Cout, a.K * a.Rk, const_cast<float*>(part), nullptr};
+  hipLaunchKernelGGL(few_reduce_kernel, dim3((unsigned)ceil_div((int64_t)f.J * Cout, FR_E)),
+                     dim3(FR_E * FR_G), 0, st, f, a.nrows > 0 ? few_groups(a.nrows) : 0, off, u0,
+                     dW);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
 }

@@ -172,3 +172,51 @@ def test_weight_gradient_sizes(scn, case):
     assert not np.any(np.isfinite(got) & np.isinf(want))
     assert np.array_equal(np.isnan(got[ok]), np.isnan(want[ok]))
     _check(got[ok], want[ok], mass[ok], max(rb.n_pairs // rb.K, 1))
+
+
+@pytest.mark.parametrize("view", [False, True])
+@pytest.mark.parametrize("case", [
+    # f, m, n, cin, cout: reductions of 1, 8, 16, 27, 32, 54, 64.. entries (one
+    # to three tiles of 32), one tile, ragged tiles, more tiles than waves
+    (1, 9, 1, 1, 4), (2, 9, 40, 1, 64), (2, 12, 700, 2, 33), (3, 14, 900, 1, 130),
+    (2, 16, 1500, 4, 64), (3, 12, 500, 2, 64), (3, 14, 700, 3, 60), (2, 64, 60000, 1, 32),
+    (3, 30, 3000, 1, 64),
+])
+def test_few_channels(scn, case, view):
+    """First layers: the forward, and the weight and bias gradients alone
+    (which take another path than all gradients together)."""
+    f, m, n, cin, cout = case
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, f, m, n, cin, cout, 41)
+    y, go = scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b), relu=True)
+    want, mass = _forward(rb, ir, orr, x, g, W, b)
+    _check(host(y), np.maximum(want, 0), mass, rb.K * cin)
+    rng = stream_rng(43, 1)
+    dy = rng.uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+    dg = rng.uniform(-1, 1, cout).astype(np.float32)
+    for relu in (False, True):
+        args = (rb, dev(x), dev(g), dev(W), y, go, dev(dy), dev(dg))
+        got = scn.conv_bwd(*args, relu=relu, need=("dW", "dbias"))
+        again = scn.conv_bwd(*args, relu=relu, need=("dW", "dbias"))
+        assert torch.equal(got["dW"], again["dW"]) and torch.equal(got["dbias"], again["dbias"])
+        d = dy * (host(y) > 0) if relu else dy
+        dgr = dg * (host(go) > 0) if relu else dg
+        want, mass = _weight_gradient(rb, ir, orr, x, g, d)
+        gd = np.outer(g, dgr.astype(np.float64))
+        _check(host(got["dW"]), want + gd, mass + np.abs(gd), rb.a_out)
+        s64 = d.astype(np.float64)
+        _check(host(got["dbias"]), s64.sum(0) + dgr, np.abs(s64).sum(0) + np.abs(dgr), rb.a_out)
+    # special values
+    x[n // 2, cin - 1] = np.inf
+    dy[rb.a_out // 2, cout - 1] = np.nan
+    with np.errstate(all="ignore"):
+        want, mass = _forward(rb, ir, orr, x, g, W, b)
+        got = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+        want, mass = _weight_gradient(rb, ir, orr, x, g, dy)
+        got = host(scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy),
+                                need=("dW", "dbias"))["dW"])
+    ok = np.isfinite(want)
+    assert not np.any(np.isfinite(got) & ~ok)
+    _check(got[ok], want[ok], mass[ok], rb.a_out)
