@@ -293,39 +293,6 @@ __device__ inline void add_item(v16f (&acc)[2][2], const v16f (&part)[2][2], int
         acc[rt][ct][r] = fmaf(part[rt][ct][r], sgn, acc[rt][ct][r]);
 }
 
-// A 32 x 32 quarter of a tile: a lane holds row 32 rt + n32 and, in register
-// 4 j + z, column 64 cb + 32 ct + 8 j + 4 h + z.  If one of its sums is not
-// finite, the operands held an infinity, a NaN or a value past bf16's range
-// (or the sum itself overflows): it is computed again in plain fp32.
-template <bool SUB, bool SORTED>
-__device__ inline void redo_if_special(const TileArgs& a, const Rows<SORTED>& R, v16f& e, int rt,
-                                       int ct, int cb, int lane) {
-  float t = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) t = fmaf(e[r], 0.f, t);
-  if (!__ballot(!(t == 0.f))) return;
-  const int n32 = lane & 31, col0 = 64 * cb + 32 * ct + 4 * (lane >> 5);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) e[r] = 0.f;
-  uint32_t rest = R.U;
-  while (rest) {
-    const int k = __builtin_ctz(rest);
-    rest &= rest - 1;
-    const int row = __builtin_amdgcn_ds_bpermute((32 * rt + n32) * 4, R.row(R.load(k, lane), k));
-    if (row < 0) continue;
-    const float* xp = a.src + (int64_t)row * a.ld;
-    for (int j = 0; j < a.Rk; ++j) {
-      const float x = SUB ? xp[j] - a.sub[j] : xp[j];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int col = col0 + 8 * (r >> 2) + (r & 3);
-        if (col < a.Nc) e[r] = fmaf(x, a.W[k * a.wk + j * a.wj + col * a.wn], e[r]);
-      }
-    }
-  }
-}
-
-// Columns col .. col + 3 of accumulator row pos: dst = act(v + add).
 // STREAM: written past the caches (a large layer's output is read only by
 // later calls: 2.70 -> 2.60 ms for the forward of the benchmark's layer).
 template <bool SORTED, bool STREAM>
@@ -351,6 +318,54 @@ __device__ inline void put4(const TileArgs& a, int64_t pos, int col, v4f v) {
   }
 }
 
+// 0 if a quarter's sums are finite, else NaN
+__device__ inline float not_finite(const v16f& e) {
+  float t = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) t = fmaf(e[r], 0.f, t);
+  return t;
+}
+
+// Writes a 32 x 32 quarter of a tile again, computed in plain fp32: where a
+// sum is not finite, the operands held an infinity, a NaN or a value past
+// bf16's range (or the sum itself overflows).  Runs after the tile's own
+// stores, when its accumulators need no registers any more (kept beside them,
+// this seldom run code cost the kernels a third of their waves).  A lane holds
+// row 32 rt + n32 and, in register 4 j + z, column 64 cb + 32 ct + 8 j + 4 h + z.
+template <bool SUB, bool SORTED>
+__device__ inline void redo_quarter(const TileArgs& a, const Rows<SORTED>& R, int rt, int ct,
+                                    int cb, int lane) {
+  __threadfence();  // the stores it replaces come from other lanes
+  const int n32 = lane & 31, col0 = 64 * cb + 32 * ct + 4 * (lane >> 5);
+  float e[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) e[r] = 0.f;
+  uint32_t rest = R.U;
+  while (rest) {
+    const int k = __builtin_ctz(rest);
+    rest &= rest - 1;
+    const int row = __builtin_amdgcn_ds_bpermute((32 * rt + n32) * 4, R.row(R.load(k, lane), k));
+    if (row < 0) continue;
+    const float* xp = a.src + (int64_t)row * a.ld;
+    for (int j = 0; j < a.Rk; ++j) {
+      const float x = SUB ? xp[j] - a.sub[j] : xp[j];
+      // the addresses are formed here, not kept across the loop
+      int64_t wn = a.wn;
+      asm volatile("" : "+s"(wn));
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int col = col0 + 8 * (r >> 2) + (r & 3);
+        if (col < a.Nc) e[r] = fmaf(x, a.W[k * a.wk + j * a.wj + col * wn], e[r]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    put4<SORTED, false>(a, R.row0 + 32 * rt + n32, col0 + 8 * j,
+                        v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
+}
+
 // Work items are contiguous per XCD (work-groups are dispatched round-robin
 // over the eight), so that neighbouring tiles share its L2.
 __device__ inline int64_t xcd_item(int64_t b, int64_t n) {
@@ -364,20 +379,20 @@ __device__ inline int64_t xcd_item(int64_t b, int64_t n) {
 constexpr int OUT_LD = 68;                 // floats per row
 constexpr int OUT_B = 32 * OUT_LD * 4;     // bytes of ob
 template <bool SUB, bool SORTED>
-__device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R, v16f (&acc)[2][2],
-                                  float* ob, int cb, int lane) {
+__device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
+                                  const v16f (&acc)[2][2], float* ob, int cb, int lane) {
+  const bool redo = __ballot(!(not_finite(acc[0][0]) + not_finite(acc[0][1]) +
+                                   not_finite(acc[1][0]) + not_finite(acc[1][1]) == 0.f)) != 0;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
     wave_sync();
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      redo_if_special<SUB, SORTED>(a, R, acc[rt][ct], rt, ct, cb, lane);
+    for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         *reinterpret_cast<v4f*>(ob + (lane & 31) * OUT_LD + 32 * ct + 8 * j + 4 * (lane >> 5)) =
             v4f{acc[rt][ct][4 * j], acc[rt][ct][4 * j + 1], acc[rt][ct][4 * j + 2],
                 acc[rt][ct][4 * j + 3]};
-    }
     wave_sync();
     const int col = 64 * cb + 4 * (lane & 15);
 #pragma unroll
@@ -386,6 +401,10 @@ __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R, v16f
       put4<SORTED, SORTED>(a, R.row0 + 32 * rt + r, col,
                            *reinterpret_cast<const v4f*>(ob + r * OUT_LD + 4 * (lane & 15)));
     }
+  }
+  if (redo) {
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) redo_quarter<SUB, SORTED>(a, R, q >> 1, q & 1, cb, lane);
   }
 }
 
@@ -706,12 +725,13 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
 #pragma unroll
     for (int z = 0; z < 4; ++z) e[4 * r + z] = s[z];
   }
-  redo_if_special<SUB, SORTED>(a, R, e, w >> 1, w & 1, cb, lane);
+  const bool redo = __ballot(!(not_finite(e) == 0.f)) != 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     put4<SORTED, false>(a, R.row0 + 32 * (w >> 1) + (lane & 31),
                  64 * cb + 32 * (w & 1) + 8 * j + 4 * (lane >> 5),
                  v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
+  if (redo) redo_quarter<SUB, SORTED>(a, R, w >> 1, w & 1, cb, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -766,21 +786,22 @@ __host__ __device__ constexpr int few_lds(int nst, int ncb) {
 }
 
 template <bool SORTED>
-__global__ void __launch_bounds__(64 * WGW, 2) few_fwd_kernel(TileArgs a, int nst, int ncb) {
+__global__ void __launch_bounds__(64 * WGW, 3) few_fwd_kernel(TileArgs a, int nst, int ncb) {
   extern __shared__ char smem[];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ldr = 16 * nst + 4;
   const int64_t tile = xcd_item(blockIdx.x, gridDim.x) * WGW + w;
   if (tile >= a.ntile) return;
-  // one column block: the values' room is free when the tile leaves
   float* const v = reinterpret_cast<float*>(smem + w * few_lds(nst, ncb));
+  // one column block: the values' room is free when the tile leaves
   float* const ob = ncb == 1 ? v : v + 64 * ldr;
   Rows<SORTED> R;
   R.init(a, tile, lane);
   few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane);
   const int n32 = lane & 31, h = lane >> 5;
   for (int cb = 0; cb < ncb; ++cb) {
+    const v4u* wp = reinterpret_cast<const v4u*>(a.Wp) + (int64_t)cb * nst * 384 + lane;
     v16f acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -788,22 +809,26 @@ __global__ void __launch_bounds__(64 * WGW, 2) few_fwd_kernel(TileArgs a, int ns
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    const v4u* wp = reinterpret_cast<const v4u*>(a.Wp) + (int64_t)cb * nst * 384 + lane;
+#pragma unroll 1
     for (int s = 0; s < nst; ++s) {
       v4u Wf[2][3];
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
         for (int q = 0; q < 3; ++q) Wf[ct][q] = wp[(s * 6 + ct * 3 + q) * 64];
-      Frag3 X[2];
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
         const float* p = v + (32 * rt + n32) * ldr + 16 * s + 8 * h;
         const v4f p0 = *reinterpret_cast<const v4f*>(p), p1 = *reinterpret_cast<const v4f*>(p + 4);
         const float e[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
-        X[rt] = split8(e);
+        const Frag3 X = split8(e);
+#pragma unroll
+        for (int q = 0; q < SPLIT_PROD; ++q)
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct)
+            acc[rt][ct] = mfma_bf16(Wf[ct][split_a(q)], X.s[split_b(q)], acc[rt][ct]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      step_products<false>(acc, Wf, X);
     }
     store_tile<true, SORTED>(a, R, acc, ob, cb, lane);
   }
@@ -822,7 +847,7 @@ struct FewArgs {
 };
 
 template <int JT, bool SORTED, bool V4>
-__global__ void __launch_bounds__(64 * WGW, 2) few_dw_kernel(FewArgs f) {
+__global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewArgs f) {
   extern __shared__ char smem[];
   const TileArgs& a = f.t;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -850,52 +875,56 @@ __global__ void __launch_bounds__(64 * WGW, 2) few_dw_kernel(FewArgs f) {
     R.init(a, tile, lane);
     wave_sync();
     few_values<SORTED>(a, R, v, 1, LDJ, 32 * JT * LDJ, sgn, lane);
-    v4f d[4][4];
-    auto load = [&](int st) {
+    struct Dy {
+      v4f t[4], m[4];
+    };
+    auto load = [&](Dy& q, int st) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int64_t pos = R.row0 + 16 * st + 4 * pg + i;
-        const bool live = pos < a.nrows;
-        const int64_t p = live ? pos : a.nrows - 1;
-        const int64_t row = SORTED ? (int64_t)a.fperm[p] : p;
-        v4f t, m;
+        const int64_t p = min(R.row0 + 16 * st + 4 * pg + i, a.nrows - 1);
+        const int64_t at = (SORTED ? (int64_t)a.fperm[p] : p) * f.Cout;
         if (V4) {
-          t = *reinterpret_cast<const v4f*>(f.dy + row * f.Cout + cd[0]);
-          if (f.y) m = *reinterpret_cast<const v4f*>(f.y + row * f.Cout + cd[0]);
+          q.t[i] = *reinterpret_cast<const v4f*>(f.dy + at + cd[0]);
+          if (f.y) q.m[i] = *reinterpret_cast<const v4f*>(f.y + at + cd[0]);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            t[e] = f.dy[row * f.Cout + cd[e]];
-            if (f.y) m[e] = f.y[row * f.Cout + cd[e]];
+            q.t[i][e] = f.dy[at + cd[e]];
+            if (f.y) q.m[i][e] = f.y[at + cd[e]];
           }
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          d[st][i][e] = live && (!f.y || m[e] > 0.f) ? t[e] : 0.f;
       }
     };
-#pragma unroll
-    for (int st = 0; st < 4; ++st) load(st);
-#pragma unroll
+    Dy q;
+    load(q, 0);
+#pragma unroll 1
     for (int st = 0; st < 4; ++st) {
+      v4f d[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          d[i][e] = R.row0 + 16 * st + 4 * pg + i < a.nrows && (!f.y || q.m[i][e] > 0.f)
+                        ? q.t[i][e] : 0.f;
+      load(q, min(st + 1, 3));  // on its way during this stage's products
       // rows 16 st + 8 h + 0..7 of column 4 (m & 15) + 2 t + (m >> 4)
       v4u D[2][3];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          uint32_t p[3], q[3];
-          split2(d[st][2 * j][2 * t], d[st][2 * j + 1][2 * t], p[0], p[1], p[2]);
-          split2(d[st][2 * j][2 * t + 1], d[st][2 * j + 1][2 * t + 1], q[0], q[1], q[2]);
+          uint32_t p[3], u[3];
+          split2(d[2 * j][2 * t], d[2 * j + 1][2 * t], p[0], p[1], p[2]);
+          split2(d[2 * j][2 * t + 1], d[2 * j + 1][2 * t + 1], u[0], u[1], u[2]);
 #pragma unroll
           for (int s = 0; s < 3; ++s) {
-            const auto r = __builtin_amdgcn_permlane16_swap(p[s], q[s], false, false);
+            const auto r = __builtin_amdgcn_permlane16_swap(p[s], u[s], false, false);
             D[t][s][j] = r[0];
             D[t][s][2 + j] = r[1];
           }
         }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) tsum += d[st][i];
+      for (int i = 0; i < 4; ++i) tsum += d[i];
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         const float* p = v + (32 * jt + n32) * LDJ + 16 * st + 8 * h;
@@ -1110,9 +1139,9 @@ scn_status few_forward(const TileArgs& a, hipStream_t st) {
   return SCN_OK;
 }
 
-// Work-groups of the weight gradient: two per CU (a third spills), a tile per wave at least
+// Work-groups of the weight gradient: three per CU, a tile per wave at least
 int few_groups(int64_t nrows) {
-  return (int)std::min<int64_t>(512, std::max<int64_t>(1, ceil_div(nrows, TILE * WGW)));
+  return (int)std::min<int64_t>(768, std::max<int64_t>(1, ceil_div(nrows, TILE * WGW)));
 }
 
 template <int JT>
