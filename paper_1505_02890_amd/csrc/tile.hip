@@ -35,8 +35,10 @@ namespace {
 
 constexpr int NT = 256;  // threads per work-group (4 waves)
 
-// Fewer (tile, column block) items than this: four waves share each.
-constexpr int64_t TILE_SPLIT = 2048;
+// Fewer (tile, column block) items than this, one per SIMD: four waves share
+// each.  (35 -> 50 channels on 1.8k tiles: 66 us shared, 54 not; the networks and
+// the stack are within 1% from 512 to 4096.)
+constexpr int64_t TILE_SPLIT = 1024;
 
 // Channels go in chunks of one or two 16-channel steps, none of them padded.
 // (Longer chunks take registers that a third or second work-group per CU
