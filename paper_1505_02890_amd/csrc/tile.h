@@ -19,7 +19,7 @@ struct TileArgs {
   // [64t, 64t + 64).
   const int32_t* gidx;   // per pair: row of src
   const int32_t* aidx;   // per pair: accumulator row
-  const int64_t* tpos;   // [K*ntile + 1]
+  const int64_t* tpos;   // [K*ntile + 1]; null beside the dense forward view
   // Rows from the dense forward view: position p of the mask-sorted order is
   // output row fperm[p], its inputs nb[nb_off[row] ..] in offset order.
   const int32_t* nb;
@@ -62,7 +62,8 @@ scn_status tile_pad(TileArgs& a, float* out, hipStream_t st);
 scn_status launch_tile(const TileArgs& a, hipStream_t st);
 
 // Layers of few input channels, whose offsets join the reduction.  Arguments
-// as for launch_tile (gidx, aidx: the pair lists, also beside the dense view),
+// as for launch_tile (gidx, aidx: the pair lists, also beside the dense view,
+// where few_reduce alone reads them: they have no tile starts there),
 // but Wp packed from W as one offset of K*Cin entries (gm = Cin).
 bool few_channels(int K, int Cin);
 scn_status few_forward(const TileArgs& a, hipStream_t st);
