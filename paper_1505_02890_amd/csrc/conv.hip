@@ -1023,9 +1023,13 @@ int dw_slots() {
 // instead of holding a few stragglers that would take a round's time alone.
 constexpr int DW_ROUNDS = 4;
 
+// Which kernel takes the input gradient: the tile kernels read rows of at least
+// four channels.
+bool tile_dx(const scn_rulebook* rb, int Cout) { return rb->s == 1 && Cout >= 4; }
+
 struct BwdLayout {
   int64_t chp, maxc, nblk;
-  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, o_pad, pad, o_few, total;
+  size_t o_dyb, o_part, o_partT, o_partS, o_S, o_u0, o_T, o_wp, o_gz, o_few, total;
 };
 
 BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) {
@@ -1055,13 +1059,10 @@ BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) 
   L.o_T = cur;
   cur += al((size_t)rb->K * Cout * 4);
   L.o_wp = cur;
-  cur += al(rb->s == 1 ? tile_pack_bytes(rb->K, Cout, Cin)
+  cur += al(tile_dx(rb, Cout) ? tile_pack_bytes(rb->K, Cout, Cin)
                        : (size_t)rb->K * ceil_div(Cin, 64) * 64 * ceil_div(Cout, 16) * 16 * 4);
   L.o_gz = cur;
   cur += al(std::max((size_t)rb->K * ceil_div(Cin, 64) * 64, (size_t)TILE_PAD) * 4);
-  L.o_pad = cur;
-  L.pad = rb->s == 1 ? tile_pad_bytes(rb->a_out, Cout) : 0;
-  cur += al(L.pad);
   L.o_few = cur;
   if (rb->s == 1 && few_channels(rb->K, Cin))
     cur += al((size_t)few_groups(rb->a_out) * ((size_t)rb->K * Cin + 1) * Cout * 4);
@@ -1128,7 +1129,7 @@ static scn_status fwd_check(const char* who, const scn_rulebook* rb, const float
 static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g_in,
                           const float* W, const float* bias, int32_t Cin, int32_t Cout,
                           uint32_t flags, float* y, float* g_out, hipStream_t st,
-                          const FwdScratch& fs, float* gw, float* pad) {
+                          const FwdScratch& fs, float* gw) {
   const int relu = (flags & SCN_RELU) ? 1 : 0;
   const int RkP = fs.RkP, NcP = fs.NcP;
   float* const gpre = gw + (size_t)rb->K * NcP;
@@ -1138,12 +1139,11 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
     uint32_t* const Ws = reinterpret_cast<uint32_t*>(Wp + TILE_PAD);
     const bool few = few_channels(rb->K, Cin);
     if (scn_status rc = tile_pack(W, (int64_t)Cin * Cout, Cout, 1, few ? 1 : rb->K,
-                                  few ? rb->K * Cin : Cin, Cout, g_in, Cin, bias, relu, Ws, sub,
-                                  gpre, g_out, st))
+                                  few ? rb->K * Cin : Cin, Cout, !few, g_in, Cin, bias, relu, Ws,
+                                  sub, gpre, g_out, st))
       return rc;
     TileArgs t{};
     t.src = x;
-    t.ld = Cin;
     t.sub = sub;
     t.subtract = 1;
     t.Wp = Ws;
@@ -1169,7 +1169,6 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
     t.relu = relu;
     t.dst = y;
     scn_status rc;
-    if (pad && (rc = tile_pad(t, pad, st))) return rc;
     if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = few ? few_forward(t, st) : launch_tile(t, st)))
       return rc;
     return timer_mark(TK_FWD, 1, st);
@@ -1249,15 +1248,7 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
   const FwdScratch fs = fwd_scratch(rb, Cin, Cout);
   float* gw = nullptr;
   const Allocator al = current_allocator();
-  // without room for padded rows, the rows are gathered as they are
-  const size_t at = (fs.total + 255) & ~size_t(255);
-  size_t pad = rb->s == 1 && !few_channels(rb->K, Cin) ? tile_pad_bytes(rb->a_in, Cin) : 0;
-  scn_status rc = dalloc(reinterpret_cast<void**>(&gw), pad ? at + pad : fs.total, st, al);
-  if (rc == SCN_ERR_NOMEM && pad) {
-    clear_error();
-    pad = 0;
-    rc = dalloc(reinterpret_cast<void**>(&gw), fs.total, st, al);
-  }
+  scn_status rc = dalloc(reinterpret_cast<void**>(&gw), fs.total, st, al);
   if (rc) return rc;
   struct Free {
     float* p;
@@ -1265,8 +1256,7 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
     Allocator al;
     ~Free() { dfree(p, s, al); }
   } free_gw{gw, st, al};
-  return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs, gw,
-                 pad ? reinterpret_cast<float*>(reinterpret_cast<char*>(gw) + at) : nullptr);
+  return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs, gw);
 }
 
 size_t scn_conv_fwd_noalloc_max_bytes(void) { return NOALLOC_MAX_BYTES; }
@@ -1293,7 +1283,7 @@ scn_status scn_conv_fwd_noalloc(const scn_rulebook* rb, const float* x, const fl
   void* base = nullptr;
   if (scn_status rc0 = noalloc_scratch(&base)) return rc0;
   return fwd_run(rb, x, g_in, W, bias, Cin, Cout, flags, y, g_out, st, fs,
-                 static_cast<float*>(base), nullptr);
+                 static_cast<float*>(base));
 }
 
 size_t scn_conv_bwd_workspace_bytes(const scn_rulebook* rb, int32_t Cin, int32_t Cout,
@@ -1341,7 +1331,6 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
   if (rb->s == 1 && dW && !dx && !dg_in && few_channels(K, Cin)) {
     TileArgs t{};
     t.src = x;
-    t.ld = Cin;
     t.sub = g_in;
     t.gidx = rb->in_rows;
     t.aidx = rb->out_rows;
@@ -1391,14 +1380,13 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
   SCN_LAUNCH_CHECK();
 
   // input gradient: accumulate over input ranks with W_k^T
-  if (dx && rb->a_in > 0 && rb->s == 1) {
-    scn_status rc = tile_pack(W, (int64_t)Cin * Cout, 1, Cout, K, Cout, Cin, nullptr,
+  if (dx && rb->a_in > 0 && tile_dx(rb, Cout)) {
+    scn_status rc = tile_pack(W, (int64_t)Cin * Cout, 1, Cout, K, Cout, Cin, true, nullptr,
                               1, nullptr, 0, reinterpret_cast<uint32_t*>(wpack), gzero, nullptr,
                               nullptr, st);
     if (rc) return rc;
     TileArgs a{};
     a.src = dyb;
-    a.ld = Cout;
     a.sub = gzero;
     a.Wp = reinterpret_cast<uint32_t*>(wpack);
     a.W = W;
@@ -1417,7 +1405,6 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
     a.Nc = Cin;
     a.dst = dx;
     a.wmap = rb->input_sorted ? nullptr : rb->perm;
-    if (L.pad && (rc = tile_pad(a, reinterpret_cast<float*>(base + L.o_pad), st))) return rc;
     if ((rc = timer_mark(TK_DX, 0, st)) || (rc = launch_tile(a, st)) ||
         (rc = timer_mark(TK_DX, 1, st)))
       return rc;

@@ -8,8 +8,7 @@
 namespace scn {
 
 struct TileArgs {
-  const float* src;      // gathered rows [nsrc][ld], Rk channels each
-  int ld;
+  const float* src;      // gathered rows [nsrc][Rk], Rk >= 4 (launch_tile)
   const float* sub;      // [TILE_PAD] subtracted from every row (zero past Rk); 16-byte aligned
   const uint32_t* Wp;    // split weights (tile_pack)
   const float* W;        // the weights themselves: W_k(j, n) = W[k*wk + j*wj + n*wn]
@@ -47,17 +46,11 @@ size_t tile_pack_bytes(int K, int Rk, int Nc);
 
 // Splits W_k(j, n) into a.Wp's layout; fills sub[0 .. TILE_PAD) with g[j % gm]
 // (zeros if g is null or past Rk).  With g_pre (else null): g_pre = bias + sum_k g W_k and
-// g_out = act(g_pre).
+// g_out = act(g_pre).  chunks: entries as launch_tile reads rows, else in
+// channel order (few_forward).
 scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
-                     const float* g, int gm, const float* bias, int relu, uint32_t* Wp, float* sub,
-                     float* g_pre, float* g_out, hipStream_t st);
-
-// Rows whose channel count is no multiple of 16 are copied to a multiple
-// first where there is room (tile_pad_bytes, 0 if none is needed): a's rows
-// become out's.  (Gathered as they are, float by float, a 35 -> 50 layer on
-// 60k tetrahedral sites took 89 us.)
-size_t tile_pad_bytes(int64_t rows, int Rk);
-scn_status tile_pad(TileArgs& a, float* out, hipStream_t st);
+                     bool chunks, const float* g, int gm, const float* bias, int relu,
+                     uint32_t* Wp, float* sub, float* g_pre, float* g_out, hipStream_t st);
 
 scn_status launch_tile(const TileArgs& a, hipStream_t st);
 

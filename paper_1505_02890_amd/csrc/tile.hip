@@ -40,19 +40,40 @@ constexpr int NT = 256;  // threads per work-group (4 waves)
 // the stack are within 1% from 512 to 4096.)
 constexpr int64_t TILE_SPLIT = 1024;
 
-// Channels go in chunks of one or two 16-channel steps, none of them padded.
+// Channels go in chunks of one or two 16-channel steps, few of them padded.
 // (Longer chunks take registers that a third or second work-group per CU
 // needs: four steps per item, two work-groups, 2.71 ms for the forward of the
-// benchmark's layer against 2.60.)
-int chunk_steps(int Rk) { return ceil_div(Rk, 16) % 2 ? 1 : 2; }
+// benchmark's layer against 2.60.  An odd number of steps rounded up for
+// chunks of two: 48 and 80 channels 4 to 14% slower but for single cases.)
+int chunk_steps(int Rk) { return Rk >= 32 && ceil_div(Rk, 16) % 2 == 0 ? 2 : 1; }
 
 constexpr int PRE_COLS = 8;
 
+// The channel that entry j of the reduction holds, of a row of Rk >= 4 read in
+// chunks of C = 16 TC entries.  A last chunk that the row does not fill starts
+// earlier and overlaps the one before (in a row shorter than one chunk, its
+// last piece of four does, and pieces past the row repeat it), so that every
+// piece of four entries is four channels in a row, of any alignment, and none
+// leaves it.  Entries that repeat a channel carry zero weights.
+__host__ __device__ inline int entry_channel(int j, int Rk, int C) {
+  const int c0 = Rk >= C ? j - j % C : j & ~3;
+  return (c0 < Rk - (Rk >= C ? C : 4) ? c0 : Rk - (Rk >= C ? C : 4)) + (j - c0);
+}
+__device__ inline bool entry_repeats(int j, int Rk, int C) {
+  return entry_channel(j, Rk, C) < (Rk >= C ? j - j % C : j & ~3);
+}
+// Where piece `piece` of the first step of chunk ch starts is
+// min(C ch + 4 piece, piece_limit); the second step's is 16 channels on.
+__device__ inline int piece_limit(int piece, int Rk, int C) {
+  return Rk >= C ? Rk - C + 4 * piece : Rk - 4;
+}
+
 // Wp[k][cb][step][ct][part][lane][4 words]: the eight reduction entries
 // j = 16 step + 8 (lane >> 5) + 0..7 of column n = 64 cb + 32 ct + (lane & 31).
+// C: entries as entry_channel places them; 0: entry j is channel j.
 __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__ W, int64_t wk,
                                                        int64_t wj, int64_t wn, int K, int Rk,
-                                                       int Nc, int nst, int ncb,
+                                                       int Nc, int nst, int ncb, int C,
                                                        const float* __restrict__ g, int gm,
                                                        const float* __restrict__ bias, int relu,
                                                        v4u* __restrict__ Wp,
@@ -99,8 +120,11 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
   const int n = 64 * cb + 32 * ct + (lane & 31), j0 = 16 * step + 8 * (lane >> 5);
   float v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e)
-    v[e] = n < Nc && j0 + e < Rk ? W[k * wk + (j0 + e) * wj + n * wn] : 0.f;
+  for (int e = 0; e < 8; ++e) {
+    const int j = C ? entry_channel(j0 + e, Rk, C) : j0 + e;
+    v[e] = n < Nc && j < Rk && !(C && entry_repeats(j0 + e, Rk, C))
+               ? W[k * wk + j * wj + n * wn] : 0.f;
+  }
   if (k & 1) {  // odd offsets negated (add_item)
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = -v[e];
@@ -200,29 +224,24 @@ struct Item {
   }
 };
 
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // Gather of an item's 64 rows.  Load layout: lane 4 rl + cq takes 16 bytes of
 // row 16 g + rl, so four adjacent lanes read 64 contiguous bytes (in the MFMA
 // layout adjacent lanes hold different rows, and the L1 would serve each
 // 16-byte piece on its own).
 template <int TC, bool VEC>
-__device__ inline void gather_rows(v4f (&nx)[4][TC], const float* src, int Rk, int ld,
-                                   int64_t absent, int row, int ch, int rl, int piece) {
-  const int c0 = 16 * TC * ch;
+__device__ inline void gather_rows(v4f (&nx)[4][TC], const float* src, int Rk, int64_t absent,
+                                   int row, int ch, int rl, int piece) {
+  const int c0 = min(16 * TC * ch + 4 * piece, piece_limit(piece, Rk, 16 * TC));
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     const int r = __builtin_amdgcn_ds_bpermute((16 * g + rl) * 4, row);
-    const float* const p = src + (r >= 0 ? (int64_t)r * ld : absent);
+    const float* const p = src + (r >= 0 ? (int64_t)r * Rk : absent) + c0;
 #pragma unroll
-    for (int s = 0; s < TC; ++s) {
-      const int c = c0 + 16 * s + 4 * piece;
-      if (VEC) {
-        nx[g][s] = *reinterpret_cast<const v4f*>(p + c);
-      } else {
-        // channels past Rk read channel 0; their weights are zero
-#pragma unroll
-        for (int z = 0; z < 4; ++z) nx[g][s][z] = p[c + z < Rk ? c + z : 0];
-      }
-    }
+    for (int s = 0; s < TC; ++s)
+      nx[g][s] = VEC ? *reinterpret_cast<const v4f*>(p + 16 * s)
+                     : *reinterpret_cast<const v4f_any*>(p + 16 * s);
   }
 }
 
@@ -348,7 +367,7 @@ __device__ inline void redo_quarter(const TileArgs& a, const Rows<SORTED>& R, in
     rest &= rest - 1;
     const int row = __builtin_amdgcn_ds_bpermute((32 * rt + n32) * 4, R.row(R.load(k, lane), k));
     if (row < 0) continue;
-    const float* xp = a.src + (int64_t)row * a.ld;
+    const float* xp = a.src + (int64_t)row * a.Rk;
     for (int j = 0; j < a.Rk; ++j) {
       const float x = SUB ? xp[j] - a.sub[j] : xp[j];
       // the addresses are formed here, not kept across the loop
@@ -414,7 +433,7 @@ __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
 // item's weights are loaded into LDS once for all of them, an item ahead, and
 // so are each step's rows into registers.  Two or three work-groups per CU:
 // one's splits, waits, prologue and stores run under the others' products.
-// TC: 16-channel steps per item.  VEC: rows of src are whole steps, 16-byte
+// TC: 16-channel steps per item.  VEC: pieces of rows are 16-byte
 // aligned.  SUB: rows are shifted by a.sub.  SORTED: rows from the dense
 // forward view, else from pair lists; its sums run in one chain (3.1e-7 off
 // 64-bit sums on the benchmark's layer, as before it 3.7e-7), the lists' in
@@ -438,7 +457,8 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
   const int rl = lane >> 2, piece = (lane & 3) ^ ((rl >> 1) & 3);
   const int nst = nchunk * TC;
   if (SUB)
-    for (int c = tid; c < 16 * nst; c += 64 * WGW) gsh[c] = a.sub[c];
+    for (int c = tid; c < 16 * nst; c += 64 * WGW)
+      gsh[c] = a.sub[entry_channel(c, a.Rk, 16 * TC)];
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
   const int64_t grp = u / ncb;
   const int cb = (int)(u - grp * ncb);
@@ -454,7 +474,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
   U = (uint32_t)__builtin_amdgcn_readfirstlane((int)U);
 
   const float* const src = a.src;
-  const int Rk = a.Rk, ld = a.ld;
+  const int Rk = a.Rk;
   const Turn turn(lane);
   const v4u* const Wb = reinterpret_cast<const v4u*>(a.Wp);
   v4u wr[NR + (NX > 0)];  // weights on their way to LDS
@@ -470,36 +490,31 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
       *reinterpret_cast<v4u*>(b + (tid + 64 * WGW * i) * 16) = wr[i];
     if (NX && tid < NX) *reinterpret_cast<v4u*>(b + (tid + 64 * WGW * NR) * 16) = wr[NR];
   };
-  // Where the lane gathers from, in the load layout: the row's start, or `sub`
-  // for a row without the offset.  The product is taken where a lane knows one
+  // Where the lane gathers from, in the load layout: the row's piece, or that of
+  // `sub` for a row without the offset.  The product is taken where a lane knows one
   // row, not after the spread, where it knows four (VEC: in 16-byte units).
   struct From {
     const float* p[4];
   };
+  const int limit = piece_limit(piece, Rk, 16 * TC);
   auto spread = [&](int row, int ch) -> From {
     From q;
-    const int at = VEC ? (row < 0 ? -1 : (int)((uint32_t)row * (uint32_t)(ld >> 2))) : row;
+    const int c0 = min(16 * TC * ch + 4 * piece, limit);
+    const int at = VEC ? (row < 0 ? -1 : (int)((uint32_t)row * (uint32_t)(Rk >> 2))) : row;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int v = __builtin_amdgcn_ds_bpermute((16 * g + rl) * 4, at);
-      const float* const f = VEC ? src + ((int64_t)(uint32_t)v << 2) : src + (int64_t)v * ld;
-      q.p[g] = (v == -1 ? a.sub : f) + 16 * TC * ch + (VEC ? 4 * piece : 0);
+      const float* const f = VEC ? src + ((int64_t)(uint32_t)v << 2) : src + (int64_t)v * Rk;
+      q.p[g] = (v == -1 ? a.sub : f) + c0;
     }
     return q;
   };
   v4f nx[4][TC];  // rows on their way to LDS
-  auto gather = [&](const From& q, int s, int ch) {
+  auto gather = [&](const From& q, int s) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (VEC) {
-        nx[g][s] = *reinterpret_cast<const v4f*>(q.p[g] + 16 * s);
-      } else {
-        // channels past Rk read channel 0; their weights are zero
-        const int c0 = 16 * TC * ch, c = 16 * s + 4 * piece;
-#pragma unroll
-        for (int z = 0; z < 4; ++z) nx[g][s][z] = q.p[g][c0 + c + z < Rk ? c + z : -c0];
-      }
-    }
+    for (int g = 0; g < 4; ++g)
+      nx[g][s] = VEC ? *reinterpret_cast<const v4f*>(q.p[g] + 16 * s)
+                     : *reinterpret_cast<const v4f_any*>(q.p[g] + 16 * s);
   };
   auto commit = [&](int s) {
     wave_sync();
@@ -529,7 +544,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
     {
       const From q = spread(R.row(xc, c.k), c.ch);
 #pragma unroll
-      for (int s = 0; s < TC; ++s) gather(q, s, c.ch);
+      for (int s = 0; s < TC; ++s) gather(q, s);
     }
     wstore(wbuf);
     wload(n);
@@ -550,7 +565,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 #pragma unroll
       for (int s = 0; s < TC; ++s) {
         commit(s);
-        gather(qn, s, n.ch);
+        gather(qn, s);
         v4f g0 = {}, g1 = {};
         if (SUB) {
           const float* gp = gsh + 16 * (TC * c.ch + s) + 8 * (lane >> 5);
@@ -598,7 +613,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 // fourth item, with their own weights from L2; their sums are added in wave
 // order.
 template <int TC, bool VEC, bool SUB, bool SORTED>
-__global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a, int nchunk,
+__global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchunk,
                                                                      int ncb) {
   extern __shared__ char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -610,7 +625,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
   const float* const gsh = reinterpret_cast<const float*>(smem + GOFF);
   if (SUB) {
     for (int c = tid; c < 16 * nst; c += NT)
-      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[c];
+      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[entry_channel(c, a.Rk, 16 * TC)];
     __syncthreads();
   }
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
@@ -620,7 +635,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
   R.init(a, tile, lane);
   const uint32_t U = R.U;
   const float* const src = a.src;
-  const int Rk = a.Rk, ld = a.ld;
+  const int Rk = a.Rk;
   const int64_t absent = a.sub - a.src;  // where rows without the offset read
   const Turn turn(lane);
 
@@ -672,7 +687,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
     v4f nx[4][TC];
     const Idx xc = R.load(c.k, lane);
     Idx xn = R.load(n.k, lane);
-    gather_rows<TC, VEC>(nx, src, Rk, ld, absent, R.row(xc, c.k), c.ch, rl, piece);
+    gather_rows<TC, VEC>(nx, src, Rk, absent, R.row(xc, c.k), c.ch, rl, piece);
 #pragma unroll
     for (int s = 0; s < TC; ++s) wload(c, s, A[s]);
     __builtin_amdgcn_sched_barrier(0);
@@ -688,7 +703,7 @@ __global__ void __launch_bounds__(NT, VEC ? 2 : 1) tile_split_kernel(TileArgs a,
       // next item's rows and the indices after them are issued ahead of its
       // weights, so that no wait for weights drains them early.
       __builtin_amdgcn_sched_barrier(0);
-      gather_rows<TC, VEC>(nx, src, Rk, ld, absent, R.row(xn, n.k), n.ch, rl, piece);
+      gather_rows<TC, VEC>(nx, src, Rk, absent, R.row(xn, n.k), n.ch, rl, piece);
       xn = R.load(nn.k, lane);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -772,7 +787,7 @@ __device__ inline void few_values(const TileArgs& a, const Rows<SORTED>& R, floa
     for (int c = 0; c < a.Rk; ++c) {
       float t[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = a.src[(int64_t)max(r[i], 0) * a.ld + c];
+      for (int i = 0; i < 8; ++i) t[i] = a.src[(int64_t)max(r[i], 0) * a.Rk + c];
       const float g = a.sub[c];
 #pragma unroll
       for (int i = 0; i < 8; ++i)
@@ -1006,7 +1021,7 @@ __global__ void __launch_bounds__(FR_E * FR_G) few_reduce_kernel(
       for (int64_t p = off[k] + g; p < off[k + 1]; p += FR_G) {
         const int64_t o = f.t.aidx[p];
         const float d = !f.y || f.y[o * f.Cout + co] > 0.f ? f.dy[o * f.Cout + co] : 0.f;
-        s = fmaf(f.t.src[(int64_t)f.t.gidx[p] * f.t.ld + c] - f.t.sub[c], d, s);
+        s = fmaf(f.t.src[(int64_t)f.t.gidx[p] * f.t.Rk + c] - f.t.sub[c], d, s);
       }
     } else if (i < n && g == 0) {
       s = t;
@@ -1040,20 +1055,6 @@ TileFn tile_fn(int tc, bool vec, bool sub, bool sorted, bool split) {
   return vec ? pick_rows<2, true>(sub, sorted, split) : pick_rows<2, false>(sub, sorted, split);
 }
 
-// out[r][0 .. 16 ceil(C/16)) = row r of x, zeros past C
-__global__ void __launch_bounds__(NT) tile_pad_kernel(const float* __restrict__ x, int64_t rows,
-                                                      int C, int q4, v4f* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  const int64_t r = i / q4;
-  if (r >= rows) return;
-  const int c = 4 * (int)(i - r * q4);
-  const float* p = x + r * C + c;
-  v4f v;
-#pragma unroll
-  for (int z = 0; z < 4; ++z) v[z] = c + z < C ? p[z] : 0.f;
-  out[i] = v;
-}
-
 }  // namespace
 
 int tile_steps(int Rk) { return (int)ceil_div(Rk, 16); }
@@ -1063,40 +1064,28 @@ size_t tile_pack_bytes(int K, int Rk, int Nc) {
 }
 
 scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
-                     const float* g, int gm, const float* bias, int relu, uint32_t* Wp, float* sub,
-                     float* g_pre, float* g_out, hipStream_t st) {
+                     bool chunks, const float* g, int gm, const float* bias, int relu,
+                     uint32_t* Wp, float* sub, float* g_pre, float* g_out, hipStream_t st) {
   const int nst = tile_steps(Rk), ncb = (int)ceil_div(Nc, 64);
   const int64_t n = std::max<int64_t>((int64_t)K * ncb * nst * 128, TILE_PAD);
   const int64_t np = ceil_div(n, NT), ng = g_pre ? ceil_div(Nc, PRE_COLS) : 0;
   hipLaunchKernelGGL(tile_pack_kernel, dim3((unsigned)(np + ng)), dim3(NT), 0, st, W, wk, wj, wn,
-                     K, Rk, Nc, nst, ncb, g, gm, bias, relu, reinterpret_cast<v4u*>(Wp), sub, (int)np,
-                     g_pre, g_out);
+                     K, Rk, Nc, nst, ncb, chunks ? 16 * chunk_steps(Rk) : 0, g, gm, bias, relu,
+                     reinterpret_cast<v4u*>(Wp), sub, (int)np, g_pre, g_out);
   SCN_LAUNCH_CHECK();
-  return SCN_OK;
-}
-
-size_t tile_pad_bytes(int64_t rows, int Rk) {
-  return Rk % 16 ? (size_t)rows * ceil_div(Rk, 16) * 64 : 0;
-}
-
-scn_status tile_pad(TileArgs& a, float* out, hipStream_t st) {
-  const int q4 = 4 * tile_steps(a.Rk);
-  if (a.nsrc > 0) {
-    hipLaunchKernelGGL(tile_pad_kernel, dim3((unsigned)ceil_div(a.nsrc * q4, NT)), dim3(NT), 0, st,
-                       a.src, a.nsrc, a.Rk, q4, reinterpret_cast<v4f*>(out));
-    SCN_LAUNCH_CHECK();
-  }
-  a.src = out;
-  a.ld = 4 * q4;
   return SCN_OK;
 }
 
 scn_status launch_tile(const TileArgs& a, hipStream_t st) {
   if (a.nrows <= 0 || a.ntile <= 0) return SCN_OK;
+  if (a.Rk < 4) {  // pieces of four channels
+    set_error("tile contraction of %d channels", a.Rk);
+    return SCN_ERR_INVALID;
+  }
   const int nst = tile_steps(a.Rk), ncb = (int)ceil_div(a.Nc, 64);
-  // whole aligned steps, and row starts in 16-byte units below 2^32 - 1
-  const bool vec = (a.ld & 15) == 0 && (reinterpret_cast<uintptr_t>(a.src) & 15) == 0 &&
-                   a.nsrc * (a.ld >> 2) < (int64_t)0xffffffff;
+  // aligned pieces, and row starts in 16-byte units below 2^32 - 1
+  const bool vec = (a.Rk & 3) == 0 && (reinterpret_cast<uintptr_t>(a.src) & 15) == 0 &&
+                   a.nsrc * (a.Rk >> 2) < (int64_t)0xffffffff;
   const int64_t items = a.ntile * ncb;
   const bool split = items < TILE_SPLIT;
   const int tc = chunk_steps(a.Rk);

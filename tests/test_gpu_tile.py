@@ -220,3 +220,90 @@ def test_few_channels(scn, case, view):
     ok = np.isfinite(want)
     assert not np.any(np.isfinite(got) & ~ok)
     _check(got[ok], want[ok], mass[ok], rb.a_out)
+
+
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("view", [False, True])
+@pytest.mark.parametrize("c", [4, 5, 7, 19, 20, 31, 33, 35, 60, 61])
+def test_ragged_rows(scn, c, view, big):
+    """Rows whose channels divide nothing, from pointers that are 4-byte
+    aligned only: forward (with and without allocations: the same bits) and
+    input gradient.  The next row's channels are NaN at the ends, so a read
+    past a row shows."""
+    n, m = (70000, 60) if big else (700, 14)
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, m, n, c, 24, 51)
+    buf = torch.full((n * c + 8,), float("nan"), device="cuda")
+    for at in (1, 4):
+        xd = buf[at:at + n * c].view(n, c)
+        xd.copy_(dev(x))
+        assert xd.is_contiguous()
+        y, _ = scn.conv_fwd(rb, xd, dev(g), dev(W), dev(b))
+        again, _ = scn.conv_fwd(rb, xd, dev(g), dev(W), dev(b), noalloc=True)
+        assert torch.equal(y, again)
+        want, mass = _forward(rb, ir, orr, x, g, W, b)
+        _check(host(y), want, mass, rb.K * c)
+        buf.fill_(float("nan"))
+    Wt = np.ascontiguousarray(W.transpose(0, 2, 1))  # [K][24][c]: dy has c channels
+    dy = stream_rng(53, 1).uniform(-1, 1, (rb.a_out, c)).astype(np.float32)
+    dbuf = torch.full((rb.a_out * c + 8,), float("nan"), device="cuda")
+    dyd = dbuf[3:3 + rb.a_out * c].view(rb.a_out, c)
+    dyd.copy_(dev(dy))
+    x24 = torch.zeros(n, 24, device="cuda")
+    dx = scn.conv_bwd(rb, x24, torch.zeros(24, device="cuda"), dev(Wt), None, None, dyd,
+                      need=("dx",))["dx"]
+    dy64, W64 = torch.from_numpy(dy).double(), torch.from_numpy(Wt).double()
+    want, mass = torch.zeros(n, 24, dtype=torch.float64), torch.zeros(n, 24, dtype=torch.float64)
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        want.index_add_(0, i, dy64[o] @ W64[k].t())
+        mass.index_add_(0, i, dy64[o].abs() @ W64[k].t().abs())
+    _check(host(dx), want.numpy(), mass.numpy(), rb.K * c)
+
+
+@pytest.mark.parametrize("cout", [1, 2, 3])
+def test_input_gradient_of_few_outputs(scn, cout):
+    """Output gradients of one to three channels."""
+    n = 3000
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, 20, n, 40, cout, 55)
+    dy = stream_rng(56, 1).uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+    dx = scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=("dx",))["dx"]
+    dy64, W64 = torch.from_numpy(dy).double(), torch.from_numpy(W).double()
+    want, mass = torch.zeros(n, 40, dtype=torch.float64), torch.zeros(n, 40, dtype=torch.float64)
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        want.index_add_(0, i, dy64[o] @ W64[k].t())
+        mass.index_add_(0, i, dy64[o].abs() @ W64[k].t().abs())
+    _check(host(dx), want.numpy(), mass.numpy(), rb.K * cout)
+
+
+def test_ragged_channels_take_no_more_memory(scn):
+    """A channel count that is no multiple of 16 asks for no more device
+    memory than the next one that is: rows are not copied to be padded."""
+    rb, *_ = _layer(scn, 2, 60, 30000, 1, 1, 57)
+    from paper_1505_02890_amd import _lib
+    for c in (5, 35, 50, 100):
+        up = -(-c // 16) * 16
+        ws = [_lib.lib().scn_conv_bwd_workspace_bytes(rb.handle, 64, v, 0) for v in (c, up)]
+        assert ws[0] <= ws[1], (c, ws)
+    asked = []
+
+    def alloc(nbytes, stream):
+        asked.append(nbytes)
+        return torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream))
+
+    def free(ptr, stream):
+        torch.cuda.caching_allocator_delete(int(ptr))
+
+    try:
+        scn.set_allocator(alloc, free)
+        for c in (35, 48):
+            z = torch.zeros(c, device="cuda")
+            scn.conv_fwd(rb, torch.zeros(rb.a_in, c, device="cuda"), z,
+                         torch.zeros(rb.K, c, 48, device="cuda"))
+            asked.append(0)
+    finally:
+        torch.cuda.synchronize()
+        scn.set_allocator()
+    cut = asked.index(0)
+    assert sum(asked[:cut]) <= sum(asked[cut:])
