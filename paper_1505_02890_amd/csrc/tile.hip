@@ -54,14 +54,15 @@ constexpr int PRE_COLS = 8;
 // earlier and overlaps the one before (in a row shorter than one chunk, its
 // last piece of four does, and pieces past the row repeat it), so that every
 // piece of four entries is four channels in a row, of any alignment, and none
-// leaves it.  Entries that repeat a channel carry zero weights.
-__host__ __device__ inline int entry_channel(int j, int Rk, int C) {
-  const int c0 = Rk >= C ? j - j % C : j & ~3;
-  return (c0 < Rk - (Rk >= C ? C : 4) ? c0 : Rk - (Rk >= C ? C : 4)) + (j - c0);
-}
-__device__ inline bool entry_repeats(int j, int Rk, int C) {
-  return entry_channel(j, Rk, C) < (Rk >= C ? j - j % C : j & ~3);
-}
+// leaves it.  Entries that repeat a channel (one below their unit's start) carry
+// zero weights.
+struct Entries {
+  int mask, last;  // start of entry j's unit: j & mask; where the last unit starts
+  __host__ __device__ Entries(int Rk, int C)  // C = 1: entry j is channel j
+      : mask(-(Rk >= C ? C : 4)), last(Rk - (Rk >= C ? C : 4)) {}
+  __device__ int channel(int j) const { return min(j & mask, last) + (j & ~mask); }
+  __device__ bool repeats(int j) const { return channel(j) < (j & mask); }
+};
 // Where piece `piece` of the first step of chunk ch starts is
 // min(C ch + 4 piece, piece_limit); the second step's is 16 channels on.
 __device__ inline int piece_limit(int piece, int Rk, int C) {
@@ -70,10 +71,9 @@ __device__ inline int piece_limit(int piece, int Rk, int C) {
 
 // Wp[k][cb][step][ct][part][lane][4 words]: the eight reduction entries
 // j = 16 step + 8 (lane >> 5) + 0..7 of column n = 64 cb + 32 ct + (lane & 31).
-// C: entries as entry_channel places them; 0: entry j is channel j.
 __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__ W, int64_t wk,
                                                        int64_t wj, int64_t wn, int K, int Rk,
-                                                       int Nc, int nst, int ncb, int C,
+                                                       int Nc, int nst, int ncb, Entries E,
                                                        const float* __restrict__ g, int gm,
                                                        const float* __restrict__ bias, int relu,
                                                        v4u* __restrict__ Wp,
@@ -109,29 +109,26 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
     }
     return;
   }
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  const int i = blockIdx.x * NT + threadIdx.x;
   if (i < TILE_PAD) sub[i] = g && i < Rk ? g[i % gm] : 0.f;
-  const int lane = (int)(i & 63), ct = (int)((i >> 6) & 1);
-  const int64_t f = i >> 7;  // (k*ncb + cb)*nst + step
-  if (f >= (int64_t)K * ncb * nst) return;
-  const int step = (int)(f % nst);
-  const int64_t kc = f / nst;
-  const int cb = (int)(kc % ncb), k = (int)(kc / ncb);
+  const int lane = i & 63, ct = (i >> 6) & 1;
+  const int f = i >> 7;  // (k*ncb + cb)*nst + step
+  if (f >= K * ncb * nst) return;
+  const int step = f % nst, kc = f / nst, cb = kc % ncb, k = kc / ncb;
   const int n = 64 * cb + 32 * ct + (lane & 31), j0 = 16 * step + 8 * (lane >> 5);
+  const float* const Wn = W + k * wk + min(n, Nc - 1) * wn;
   float v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = C ? entry_channel(j0 + e, Rk, C) : j0 + e;
-    v[e] = n < Nc && j < Rk && !(C && entry_repeats(j0 + e, Rk, C))
-               ? W[k * wk + j * wj + n * wn] : 0.f;
-  }
+  for (int e = 0; e < 8; ++e) v[e] = Wn[E.channel(j0 + e) * wj];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = (n < Nc) & !E.repeats(j0 + e) ? v[e] : 0.f;
   if (k & 1) {  // odd offsets negated (add_item)
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = -v[e];
   }
   const Frag3 s = split8(v);
 #pragma unroll
-  for (int p = 0; p < 3; ++p) Wp[((f * 2 + ct) * 3 + p) * 64 + lane] = s.s[p];
+  for (int p = 0; p < 3; ++p) Wp[(((int64_t)f * 2 + ct) * 3 + p) * 64 + lane] = s.s[p];
 }
 
 // Orders the wave's LDS accesses: a lane reads what other lanes wrote, which
@@ -458,7 +455,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
   const int nst = nchunk * TC;
   if (SUB)
     for (int c = tid; c < 16 * nst; c += 64 * WGW)
-      gsh[c] = a.sub[entry_channel(c, a.Rk, 16 * TC)];
+      gsh[c] = a.sub[Entries(a.Rk, 16 * TC).channel(c)];
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
   const int64_t grp = u / ncb;
   const int cb = (int)(u - grp * ncb);
@@ -625,7 +622,7 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
   const float* const gsh = reinterpret_cast<const float*>(smem + GOFF);
   if (SUB) {
     for (int c = tid; c < 16 * nst; c += NT)
-      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[entry_channel(c, a.Rk, 16 * TC)];
+      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[Entries(a.Rk, 16 * TC).channel(c)];
     __syncthreads();
   }
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
@@ -1070,7 +1067,7 @@ scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, 
   const int64_t n = std::max<int64_t>((int64_t)K * ncb * nst * 128, TILE_PAD);
   const int64_t np = ceil_div(n, NT), ng = g_pre ? ceil_div(Nc, PRE_COLS) : 0;
   hipLaunchKernelGGL(tile_pack_kernel, dim3((unsigned)(np + ng)), dim3(NT), 0, st, W, wk, wj, wn,
-                     K, Rk, Nc, nst, ncb, chunks ? 16 * chunk_steps(Rk) : 0, g, gm, bias, relu,
+                     K, Rk, Nc, nst, ncb, Entries(Rk, chunks ? 16 * chunk_steps(Rk) : 1), g, gm, bias, relu,
                      reinterpret_cast<v4u*>(Wp), sub, (int)np, g_pre, g_out);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
