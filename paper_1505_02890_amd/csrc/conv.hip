@@ -1,5 +1,7 @@
 // Sparse convolution, steps 2 and 3 of section 1.3 (gather the rows of Q, then
-// Q W + B) and the gradients, on fp32 matrix cores (v_mfma_f32_16x16x4f32).
+// Q W + B) and the gradients: the entry points, the contractions on the fp32
+// matrix instruction (v_mfma_f32_16x16x4f32), and the weight gradient on the
+// bf16 one (split.h).
 //
 // Q is never formed.  Its row for output o holds, per offset k, either an
 // input row or the ground state g_in.  Writing v_k(o) = g_in + (x[r] - g_in)
@@ -8,10 +10,11 @@
 //     g_pre   = B + sum_k g_in W_k,
 // so only the active blocks are gathered and multiplied.
 //
-// Stride-1 rulebooks (forward and input gradient) go to tile.hip.
+// Most stride-1 layers go to tile.hip (fwd_route, tile_dx); the others take the
+// gather kernel or, with the mask-sorted view, the dense-block forward.
 //
-// Gather kernel (forward and input gradient of strided rulebooks).  A work-group of four waves owns
-// a tile of accumulator rows (output rows for the forward, input ranks for the
+// Gather kernel (forward and input gradient of strided rulebooks, forwards of
+// sparse lists).  A work-group of four waves owns a tile of accumulator rows (output rows for the forward, input ranks for the
 // input gradient) and 64 columns; the accumulators live in LDS and each wave
 // owns 16 of the columns.  For each offset k the tile's pairs form one
 // contiguous range of list k (lists ascend by output row and by input key).
@@ -198,8 +201,9 @@ __device__ inline WFrag<NKT> load_w(const GatherArgs& a, int k, int cb, int w, i
 // Per-thread share of one stage's gather: row tid/8, channel quads
 // (tid%8) + 8u, and the row's accumulator index.  Positions past the stage's
 // pairs are clamped to its last pair (loads stay in bounds; those rows are
-// never scattered).  Reduction slots j >= Rk read some channel of the row;
-// the matching W entries are zero.
+// never scattered).  Reduction slots j >= Rk read some channel of the row and
+// are stored as zero (the matching W entries are zero, but that channel may be
+// infinite).
 template <int NKT>
 struct StageRegs {
   static constexpr int NQ = (4 * NKT + 7) / 8;  // float4 per thread
@@ -228,12 +232,16 @@ __device__ inline StageRegs<NKT> load_stage(const GatherArgs& a, int gi, int ai,
 }
 
 template <int NKT>
-__device__ inline void store_stage(float* xs, int tid, const StageRegs<NKT>& R) {
+__device__ inline void store_stage(float* xs, int tid, int Rk, StageRegs<NKT> R) {
   constexpr int XLD = 16 * NKT + 4;
   const int row = tid >> 3, part = tid & 7;
 #pragma unroll
   for (int u = 0; u < StageRegs<NKT>::NQ; ++u) {
     const int quad = part + 8 * u;
+    if (8 * u + 7 >= 4 * (NKT - 1)) {  // the last 16 channels may end in the quad
+#pragma unroll
+      for (int z = 0; z < 4; ++z) R.v[u][z] = 4 * quad + z < Rk ? R.v[u][z] : 0.f;
+    }
     if (quad < 4 * NKT) *reinterpret_cast<v4f*>(xs + row * XLD + 4 * quad) = R.v[u];
   }
   reinterpret_cast<int*>(xs)[row * XLD + 16 * NKT] = R.acc_row;  // same value from all 8
@@ -401,7 +409,7 @@ __global__ void __launch_bounds__(NT, MINB) gather_mfma_kernel(GatherArgs a) {
     Pos s1 = next_stage(sc, s0), s2 = next_stage(sc, s1), s3 = next_stage(sc, s2);
     Pos s4 = next_stage(sc, s3), s5 = next_stage(sc, s4);
 
-    store_stage<NKT>(xsb, tid, load_stage<NKT, VEC>(a, gidx_of(s0), aidx_of(s0), tid));
+    store_stage<NKT>(xsb, tid, a.Rk, load_stage<NKT, VEC>(a, gidx_of(s0), aidx_of(s0), tid));
     StageRegs<NKT> R0 = load_stage<NKT, VEC>(a, gidx_of(s1), aidx_of(s1), tid);
     StageRegs<NKT> R1 = load_stage<NKT, VEC>(a, gidx_of(s2), aidx_of(s2), tid);
     int G0 = gidx_of(s3), G1 = gidx_of(s4);
@@ -421,7 +429,7 @@ __global__ void __launch_bounds__(NT, MINB) gather_mfma_kernel(GatherArgs a) {
       Onew = stage_mfma<NKT>(xs_cur, B, min(s0.n, SROWS), T, n16, q);
       stage_scatter(Oprev, acc, cq);
       // rows of s_{i+1} -> the other buffer
-      store_stage<NKT>(xs_nxt, tid, R);
+      store_stage<NKT>(xs_nxt, tid, a.Rk, R);
       // rows of s_{i+3} (index loaded two iterations ago), index of s_{i+5}
       R = load_stage<NKT, VEC>(a, G, aidx_of(s3), tid);
       G = gidx_of(s5);
@@ -544,6 +552,298 @@ scn_status launch_gather(GatherArgs a, hipStream_t st) {
     done = true;
   }
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg, ncb), dim3(NT), smem, st, a);
+  SCN_LAUNCH_CHECK();
+  return SCN_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Dense-block forward (narrow layers with the mask-sorted view)
+// ---------------------------------------------------------------------------
+// The rulebook sorts the output rows by neighbour mask; cut into blocks of 32
+// (DENSE_ROWS) the rows of a block mostly share one mask.  One wave owns a
+// block and 64 output columns, with its 32 x 64 accumulators in registers:
+// for each offset k of the union of the block's masks it gathers the block's
+// 32 input rows (a row without offset k contributes zero) and multiplies them
+// by W_k, 64 input channels at a time.  Lane (n16, q) gathers block rows n16
+// and 16 + n16; a row's input at offset k is entry popcount(mask & (2^k - 1))
+// of its output-major neighbour list.  There is no scatter: the rows of a
+// block are distinct outputs, and the epilogue writes each once.  Rows hold
+// x - g_in, so y = g_pre + sum over active offsets of (x - g_in) W_k.  The
+// next (offset, channel chunk)'s rows are loaded while the current one is
+// multiplied.
+struct DenseArgs {
+  const float* x;          // [a_in][Cin]
+  const float* g_in;       // [Cin]
+  const float* Wp;         // packed like GatherArgs::Wp (fragment order, transposed W)
+  const float* add;        // [Cout] g_pre
+  const int32_t* nb;       // rulebook fnb
+  const uint32_t* nb_off;  // rulebook fnb_off
+  const int32_t* fperm;    // rulebook fperm
+  const uint32_t* fmask;   // rulebook fmask
+  float* y;                // [a_out][Cout]
+  int64_t a_out, nblk;
+  int K, Cin, Cout, NcP, relu, dvec_ok;
+};
+
+// One block row as the lane sees it: its mask and the start of its list.
+struct DRow {
+  uint32_t m, off;
+};
+
+// The rows of one (offset, 64-channel chunk) item: lane (n16, q) holds
+// channels 64ch + 16t + 4q .. +3 of block rows n16 and 16 + n16.
+template <int TC>
+struct DRows {
+  float4 v[2][TC];
+  int r0, r1;
+};
+
+__device__ inline int dense_src(const DenseArgs& a, const DRow& w, int k) {
+  // the list entry is read unconditionally (the list has a spare entry)
+  const int r = a.nb[w.off + __popc(w.m & ((1u << k) - 1u))];
+  return (w.m >> k) & 1u ? r : -1;
+}
+
+// Channels past Cin read channel 0 (multiply takes zeros in their place: their
+// weights are zero, but channel 0 may be infinite).
+template <int NKT, bool VEC>
+__device__ inline DRows<(NKT < 4 ? NKT : 4)> dense_rows_i(const DenseArgs& a, int r0, int r1,
+                                                          int ch, int q) {
+  constexpr int TC = NKT < 4 ? NKT : 4;
+  DRows<TC> R;
+  R.r0 = r0;
+  R.r1 = r1;
+  const float* p0 = a.x + (int64_t)(r0 >= 0 ? r0 : 0) * a.Cin;
+  const float* p1 = a.x + (int64_t)(r1 >= 0 ? r1 : 0) * a.Cin;
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    const int c = 64 * ch + 16 * t + 4 * q;
+    if (VEC) {
+      const int cc = c < a.Cin ? c : 0;
+      R.v[0][t] = *reinterpret_cast<const float4*>(p0 + cc);
+      R.v[1][t] = *reinterpret_cast<const float4*>(p1 + cc);
+    } else {
+      float e0[4], e1[4];
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        const int cz = c + z < a.Cin ? c + z : 0;
+        e0[z] = p0[cz];
+        e1[z] = p1[cz];
+      }
+      R.v[0][t] = make_float4(e0[0], e0[1], e0[2], e0[3]);
+      R.v[1][t] = make_float4(e1[0], e1[1], e1[2], e1[3]);
+    }
+  }
+  return R;
+}
+
+template <int NKT, bool VEC>
+__global__ void __launch_bounds__(NT) dense_fwd_kernel(DenseArgs a) {
+  constexpr int TC = NKT < 4 ? NKT : 4;        // 16-channel steps per chunk
+  constexpr int NCH = (NKT + 3) / 4;           // 64-channel chunks
+  __shared__ float gsh[16 * NKT];  // g_in, zero past Cin (those weights are zero)
+  for (int c = threadIdx.x; c < 16 * NKT; c += NT) gsh[c] = c < a.Cin ? a.g_in[c] : 0.f;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int64_t b = (int64_t)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (b >= a.nblk) return;
+  const int cb = blockIdx.y;
+  // Two lane layouts.  MFMA layout: lane (n16, q) = n16 + 16q holds row n16
+  // (and 16 + n16), channels 4q .. 4q + 3 of each 16; the operand fixes it.
+  // Load layout: lane (rl, cq) = 4rl + cq loads row rl (and 16 + rl),
+  // channels 4cq .. 4cq + 3, so four adjacent lanes read one row's 64
+  // contiguous bytes (in the MFMA layout four adjacent lanes read four
+  // rows, and the L1 serves each 16-byte piece on its own).  The rows are
+  // gathered in the load layout and moved to the MFMA layout by ds_bpermute.
+  const int n16 = lane & 15, q = lane >> 4;
+  const int rl = lane >> 2, cq = lane & 3;
+  const int from = (n16 * 4 + q) * 4;  // bpermute address: MFMA lane <- load lane 4 n16 + q
+  const int ncb = a.NcP >> 6;
+  const int64_t pos0 = b * DENSE_ROWS + n16, pos1 = pos0 + 16;      // MFMA layout
+  const int64_t lpos0 = b * DENSE_ROWS + rl, lpos1 = lpos0 + 16;    // load layout
+  const int o0 = pos0 < a.a_out ? a.fperm[pos0] : 0, o1 = pos1 < a.a_out ? a.fperm[pos1] : 0;
+  const int lo0 = lpos0 < a.a_out ? a.fperm[lpos0] : 0, lo1 = lpos1 < a.a_out ? a.fperm[lpos1] : 0;
+  DRow w0, w1;
+  w0.m = lpos0 < a.a_out ? a.fmask[lpos0] : 0u;
+  w1.m = lpos1 < a.a_out ? a.fmask[lpos1] : 0u;
+  w0.off = a.nb_off[lo0];
+  w1.off = a.nb_off[lo1];
+  uint32_t u = w0.m | w1.m;
+#pragma unroll
+  for (int d = 4; d < 64; d <<= 1) u |= (uint32_t)__shfl_xor((int)u, d, 64);
+  const uint32_t U = (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
+  v4f acc[2][4];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[r][g] = v4f{0.f, 0.f, 0.f, 0.f};
+  if (U) {
+    // item = (offset k, channel chunk ch), in order; `rest` holds the offsets
+    // after k; past the last item an item stays where it is (its loads are in
+    // bounds and unused)
+    struct Item {
+      int k, ch;
+      uint32_t rest;
+    };
+    auto advance = [&](Item& t) {
+      if (t.ch + 1 < NCH) {
+        ++t.ch;
+      } else if (t.rest) {
+        t.k = __builtin_ctz(t.rest);
+        t.rest &= t.rest - 1;
+        t.ch = 0;
+      }
+    };
+    Item c{__builtin_ctz(U), 0, U & (U - 1)};
+    Item n = c;
+    advance(n);
+    Item nn = n;
+    advance(nn);
+    const int nit = __builtin_popcount(U) * NCH;
+    int n0 = dense_src(a, w0, n.k), n1 = dense_src(a, w1, n.k);
+    DRows<TC> cur = dense_rows_i<NKT, VEC>(a, dense_src(a, w0, c.k), dense_src(a, w1, c.k), 0, cq);
+    DRows<TC> nxt;
+    int nn0 = 0, nn1 = 0;
+    for (int it = 0; it < nit; ++it) {
+      const int ch = c.ch;
+      const float* wp = a.Wp + (((int64_t)c.k * ncb + cb) * 4) * (NKT * 256) + lane * 4;
+      auto wload = [&](int t, float4 (&A)[4]) {
+        const int tg = 4 * ch + t < NKT ? 4 * ch + t : NKT - 1;  // past NKT: never used
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          A[g] = *reinterpret_cast<const float4*>(wp + (int64_t)g * (NKT * 256) + tg * 256);
+      };
+      // the next item's rows and the indices after it: issued after this
+      // item's last weight load, so the waits for the weights leave them in
+      // flight
+      auto prefetch = [&]() {
+        nxt = dense_rows_i<NKT, VEC>(a, n0, n1, n.ch, cq);
+        nn0 = dense_src(a, w0, nn.k);
+        nn1 = dense_src(a, w1, nn.k);
+      };
+      auto mult = [&](int t, const float4 (&A)[4]) {
+        const int tg = 4 * ch + t;
+        // x - g_in, zero for an absent row, in the load layout; then to the
+        // MFMA layout
+        const float4 gq = *reinterpret_cast<const float4*>(&gsh[16 * tg + 4 * cq]);
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 d0 = cur.v[0][t], d1 = cur.v[1][t];
+        if (!VEC) {  // one piece, cut short
+          if (a.Cin < 2) d0.y = d1.y = 0.f;
+          if (a.Cin < 3) d0.z = d1.z = 0.f;
+          if (a.Cin < 4) d0.w = d1.w = 0.f;
+        }
+        d0.x -= gq.x; d0.y -= gq.y; d0.z -= gq.z; d0.w -= gq.w;
+        d1.x -= gq.x; d1.y -= gq.y; d1.z -= gq.z; d1.w -= gq.w;
+        const int left = a.Cin - (16 * tg + 4 * cq);  // channels of the lane's piece and after
+        const float4 L0 = cur.r0 >= 0 && left > 0 ? d0 : z, L1 = cur.r1 >= 0 && left > 0 ? d1 : z;
+        auto perm = [&](float v) {
+          return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
+        };
+        const float4 B0 = make_float4(perm(L0.x), perm(L0.y), perm(L0.z), perm(L0.w));
+        const float4 B1 = make_float4(perm(L1.x), perm(L1.y), perm(L1.z), perm(L1.w));
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          acc[0][g] = mfma4(A[g].x, B0.x, acc[0][g]);
+          acc[1][g] = mfma4(A[g].x, B1.x, acc[1][g]);
+          acc[0][g] = mfma4(A[g].y, B0.y, acc[0][g]);
+          acc[1][g] = mfma4(A[g].y, B1.y, acc[1][g]);
+          acc[0][g] = mfma4(A[g].z, B0.z, acc[0][g]);
+          acc[1][g] = mfma4(A[g].z, B1.z, acc[1][g]);
+          acc[0][g] = mfma4(A[g].w, B0.w, acc[0][g]);
+          acc[1][g] = mfma4(A[g].w, B1.w, acc[1][g]);
+        }
+      };
+      // weights two 16-channel steps ahead of their products (two register
+      // sets, alternating)
+      float4 A0[4], A1[4];
+      wload(0, A0);
+      if (TC > 1) wload(1, A1);
+      if (TC <= 2) prefetch();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < TC; ++t) {
+        if (NCH > 1 && 4 * ch + t >= NKT) {
+          // a last chunk shorter than the step that issues the prefetch
+          // (t = TC - 3) issues it here, so the next item's rows are loaded
+          if (t <= TC - 3) prefetch();
+          break;
+        }
+        // step t's products, then step t + 2's weights into the set just read
+        if (t & 1) mult(t, A1); else mult(t, A0);
+        if (t + 2 < TC) {
+          if (t & 1) wload(t + 2, A1); else wload(t + 2, A0);
+          if (t + 2 == TC - 1) prefetch();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      c = n;
+      n = nn;
+      advance(nn);
+      n0 = nn0;
+      n1 = nn1;
+      cur = nxt;
+    }
+  }
+  // epilogue: rows n16 and 16 + n16 of the block, columns 64cb + 16g + 4q .. +3
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int64_t pos = r ? pos1 : pos0;
+    if (pos >= a.a_out) continue;
+    float* dp = a.y + (int64_t)(r ? o1 : o0) * a.Cout;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int col = 64 * cb + 16 * g + 4 * q;
+      if (col >= a.Cout) continue;
+      float e[4] = {acc[r][g][0], acc[r][g][1], acc[r][g][2], acc[r][g][3]};
+#pragma unroll
+      for (int u2 = 0; u2 < 4; ++u2) {
+        if (col + u2 < a.Cout) e[u2] += a.add[col + u2];
+        if (a.relu) e[u2] = e[u2] > 0.f ? e[u2] : 0.f;
+      }
+      if (a.dvec_ok && col + 3 < a.Cout) {
+        // a streaming store: y is read only by later calls (kernel 2.669 ->
+        // 2.653 ms on the 1M-site layer)
+        __builtin_nontemporal_store(v4f{e[0], e[1], e[2], e[3]}, reinterpret_cast<v4f*>(dp + col));
+      } else {
+#pragma unroll
+        for (int u2 = 0; u2 < 4; ++u2)
+          if (col + u2 < a.Cout) dp[col + u2] = e[u2];
+      }
+    }
+  }
+}
+
+typedef void (*DenseFn)(DenseArgs);
+
+constexpr int DENSE_STEPS = 7;  // 16-channel steps of the longest reduction (fwd_route)
+
+DenseFn dense_fn(int nkt, bool vec) {
+  switch (nkt) {
+    case 1: return vec ? dense_fwd_kernel<1, true> : dense_fwd_kernel<1, false>;
+    case 2: return dense_fwd_kernel<2, true>;
+    case 3: return dense_fwd_kernel<3, true>;
+    case 4: return dense_fwd_kernel<4, true>;
+    case 5: return dense_fwd_kernel<5, true>;
+    case 6: return dense_fwd_kernel<6, true>;
+    case 7: return dense_fwd_kernel<7, true>;
+    default: return nullptr;
+  }
+}
+
+scn_status launch_dense(DenseArgs a, hipStream_t st) {
+  if (a.a_out <= 0 || a.nblk <= 0) return SCN_OK;
+  const bool vec = ((a.Cin & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0);
+  a.dvec_ok = ((a.Cout & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0);
+  const int nkt = (int)ceil_div(a.Cin, 16);
+  const DenseFn fn = dense_fn(nkt, vec);
+  if (!fn || (!vec && nkt > 1)) {
+    set_error("dense-block forward of %d channels", a.Cin);
+    return SCN_ERR_INVALID;
+  }
+  const int64_t nwg = ceil_div(a.nblk, NT / 64);
+  hipLaunchKernelGGL(fn, dim3((unsigned)nwg, (unsigned)(a.NcP / 64)), dim3(NT), 0,
+                     st, a);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
 }
@@ -1091,22 +1391,68 @@ static scn_status timer_mark(TimedKernel k, int end, hipStream_t st) {
 // The forward's scratch: gw [K][NcP] and g_pre [NcP] (256-byte aligned),
 // then the packed weights [K][NcP][RkP].  Every element is written by the
 // forward's first kernels before any is read.
+// Which kernel takes a forward.
+enum class Fwd { few, tile, dense, gather };
+
+// The tile kernels multiply every row of a tile at every offset of any of its
+// rows, on the split products; the fp32 kernels multiply fewer rows that lack
+// the offset.  All lines below are measured, the tile kernels against the fp32
+// kernels, on shells, walks, patches and pooled shells of 1k to 3.6M outputs.
+// `fill` is the active share of the (output, offset) entries.
+//  - few_forward: Cin <= 2 takes 0.39 to 0.98 of the fp32 kernels' time, but
+//    with the mask-sorted view more channels win only where masks repeat (3 ->
+//    32: 0.6 to 0.9 from a fill of 0.5, 1.07 to 1.18 below; past 64 entries its
+//    window values leave one work-group per CU: 1.2 to 1.7).
+//  - View: a tile's rows share their masks, so the tile kernel wins where it
+//    has products to do (64 -> 64: 0.83 to 1.01, 96 -> 128: 0.66 to 0.82) or
+//    a fill of 0.7 (0.6 to 0.99).  The 32-row fp32 kernel, without a barrier per
+//    item, wins with one column block and little to multiply per item: items
+//    of one step (16 -> 64: tile 1.04 to 1.24, 48 -> 64: 1.02 to 1.31, 20 -> 64:
+//    1.2 to 1.5, 112 -> 64: 0.98 to 1.38), rows not on 64 bytes (56 -> 64: 0.9 to
+//    1.14), 32 channels and few offsets (32 -> 64: 0.97 to 1.1; 0.96 to 0.99 at
+//    27).  It reads rows 16 bytes at a time.
+//  - Lists: tiles of consecutive outputs are about as full as the list, and the
+//    gather kernel multiplies active pairs alone, at 0.4 of the rate.  What it
+//    saves of the tile kernel's steps (64 rows x 64 columns x 16 channels) has
+//    to pay its three more launches, about 5500 steps of full tiles.  3x3x3
+//    shells (fill 0.22): 64 -> 64 on 453k outputs 547 us in tiles, 373 from
+//    pairs; on 14k 49 and 69.
+Fwd fwd_route(const scn_rulebook* rb, const float* x, int Cin, int Cout) {
+  if (rb->s != 1) return Fwd::gather;
+  const double fill = (double)rb->n_pairs / ((double)rb->K * std::max<int64_t>(rb->a_out, 1));
+  const int nst = tile_steps(Cin);
+  if (rb->fnb) {
+    if (few_channels(rb->K, Cin) && (Cin <= 2 || (fill >= 0.5 && rb->K * Cin <= 64)))
+      return Fwd::few;
+    if (Cin < 4) return Fwd::dense;
+    const bool vec = Cin % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+    const bool thin = Cin < 32 || (Cin == 32 && rb->K < 16) || (nst % 2 && nst <= DENSE_STEPS) ||
+                      (nst == 4 && Cin < 64);
+    return vec && thin && Cout <= 64 && fill < 0.7 ? Fwd::dense : Fwd::tile;
+  }
+  if (few_channels(rb->K, Cin)) return Fwd::few;
+  const double steps = (double)ceil_div(rb->a_out, TILE) * ceil_div(Cout, 64) * rb->K * nst;
+  return steps * (0.4 - fill) >= 5500. ? Fwd::gather : Fwd::tile;
+}
+
 struct FwdScratch {
+  Fwd route;
   int RkP, NcP;
   size_t gw_bytes, total;
   size_t bound;  // what scn_conv_fwd_noalloc limits: fp32 weights on padded tiles
 };
 
-static FwdScratch fwd_scratch(const scn_rulebook* rb, int Cin, int Cout) {
+static FwdScratch fwd_scratch(const scn_rulebook* rb, const float* x, int Cin, int Cout) {
   FwdScratch f;
   f.RkP = (int)ceil_div(Cin, 16) * 16;
   f.NcP = (int)ceil_div(Cout, 64) * 64;
   f.gw_bytes = ((size_t)(rb->K + 1) * f.NcP * sizeof(float) + 255) & ~size_t(255);
+  f.route = fwd_route(rb, x, Cin, Cout);
   f.total = f.bound = f.gw_bytes + (size_t)rb->K * f.NcP * f.RkP * sizeof(float);
-  if (rb->s == 1)
+  if (f.route == Fwd::few || f.route == Fwd::tile)
     f.total = f.gw_bytes + TILE_PAD * sizeof(float) +
-              (few_channels(rb->K, Cin) ? tile_pack_bytes(1, rb->K * Cin, Cout)
-                                        : tile_pack_bytes(rb->K, Cin, Cout));
+              (f.route == Fwd::few ? tile_pack_bytes(1, rb->K * Cin, Cout)
+                                   : tile_pack_bytes(rb->K, Cin, Cout));
   return f;
 }
 
@@ -1134,10 +1480,10 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
   const int RkP = fs.RkP, NcP = fs.NcP;
   float* const gpre = gw + (size_t)rb->K * NcP;
   float* Wp = reinterpret_cast<float*>(reinterpret_cast<char*>(gw) + fs.gw_bytes);
-  if (rb->s == 1) {
+  if (fs.route == Fwd::few || fs.route == Fwd::tile) {
     float* const sub = Wp;  // the shifted rows' g_in, then the split weights
     uint32_t* const Ws = reinterpret_cast<uint32_t*>(Wp + TILE_PAD);
-    const bool few = few_channels(rb->K, Cin);
+    const bool few = fs.route == Fwd::few;
     if (scn_status rc = tile_pack(W, (int64_t)Cin * Cout, Cout, 1, few ? 1 : rb->K,
                                   few ? rb->K * Cin : Cin, Cout, !few, g_in, Cin, bias, relu, Ws,
                                   sub, gpre, g_out, st))
@@ -1182,6 +1528,28 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
   hipLaunchKernelGGL(ground_pre_kernel, dim3((unsigned)ceil_div(Cout, 64)), dim3(64), 0, st, gw,
                      NcP, bias, rb->K, Cout, relu, gpre, g_out);
   SCN_LAUNCH_CHECK();
+  if (fs.route == Fwd::dense) {
+    DenseArgs d{};
+    d.x = x;
+    d.g_in = g_in;
+    d.Wp = Wp;
+    d.add = gpre;
+    d.nb = rb->fnb;
+    d.nb_off = rb->fnb_off;
+    d.fperm = rb->fperm;
+    d.fmask = rb->fmask;
+    d.y = y;
+    d.a_out = rb->a_out;
+    d.nblk = rb->n_fblocks;
+    d.K = rb->K;
+    d.Cin = Cin;
+    d.Cout = Cout;
+    d.NcP = NcP;
+    d.relu = relu;
+    scn_status rc;
+    if ((rc = timer_mark(TK_FWD, 0, st)) || (rc = launch_dense(d, st))) return rc;
+    return timer_mark(TK_FWD, 1, st);
+  }
   GatherArgs a{};
   a.src = x;
   a.gidx = rb->in_rows;
@@ -1245,7 +1613,7 @@ scn_status scn_conv_fwd(const scn_rulebook* rb, const float* x, const float* g_i
   if (scn_status rc0 = after_build(rb, st)) return rc0;
   if (scn_status rc0 = fwd_check("scn_conv_fwd", rb, x, g_in, W, Cin, Cout, y, g_out))
     return rc0;
-  const FwdScratch fs = fwd_scratch(rb, Cin, Cout);
+  const FwdScratch fs = fwd_scratch(rb, x, Cin, Cout);
   float* gw = nullptr;
   const Allocator al = current_allocator();
   scn_status rc = dalloc(reinterpret_cast<void**>(&gw), fs.total, st, al);
@@ -1273,7 +1641,7 @@ scn_status scn_conv_fwd_noalloc(const scn_rulebook* rb, const float* x, const fl
   if (scn_status rc0 = after_build(rb, st)) return rc0;
   if (scn_status rc0 = fwd_check("scn_conv_fwd_noalloc", rb, x, g_in, W, Cin, Cout, y, g_out))
     return rc0;
-  const FwdScratch fs = fwd_scratch(rb, Cin, Cout);
+  const FwdScratch fs = fwd_scratch(rb, x, Cin, Cout);
   if (fs.bound > NOALLOC_MAX_BYTES || fs.total > NOALLOC_SCRATCH_BYTES) {
     set_error("scn_conv_fwd_noalloc: K=%d Cin=%d Cout=%d needs %zu bytes of scratch, more than "
               "the %zu the library holds",

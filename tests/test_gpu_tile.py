@@ -307,3 +307,47 @@ def test_ragged_channels_take_no_more_memory(scn):
         scn.set_allocator()
     cut = asked.index(0)
     assert sum(asked[:cut]) <= sum(asked[cut:])
+
+
+@pytest.mark.parametrize("case", [
+    # f, m, n, cin, cout, view: sparse lists from pairs (fill below 0.4, past
+    # 5500 full steps) and, just short of that, in tiles; the view's narrow
+    # layers (odd steps, rows off 64 bytes, 32 channels and few offsets) and
+    # their neighbours; full masks
+    (3, 40, 5000, 64, 64, False), (3, 40, 1200, 64, 64, False), (3, 24, 9000, 40, 70, False),
+    (2, 40, 20000, 61, 128, False), (2, 12, 1728, 64, 64, False),
+    (2, 30, 3000, 16, 64, True), (2, 30, 3000, 20, 33, True), (2, 30, 3000, 32, 64, True),
+    (3, 20, 700, 32, 64, True), (2, 30, 3000, 32, 65, True), (2, 30, 3000, 48, 64, True),
+    (2, 30, 3000, 60, 20, True), (2, 30, 3000, 64, 64, True), (2, 30, 3000, 68, 8, True),
+    (2, 30, 3000, 84, 8, True), (2, 30, 3000, 100, 64, True), (2, 30, 3000, 112, 64, True),
+    (2, 30, 3000, 132, 64, True), (2, 30, 3000, 19, 64, True), (3, 20, 700, 3, 32, True),
+    (3, 20, 700, 3, 65, True), (3, 20, 700, 4, 64, True), (3, 10, 1000, 3, 40, True),
+    (2, 12, 1728, 16, 64, True), (2, 12, 1728, 3, 64, True), (2, 12, 1728, 4, 40, True),
+])
+def test_routes(scn, case):
+    """Forwards on either side of the lines between the kernels, from aligned
+    rows and from rows that are not."""
+    f, m, n, cin, cout, view = case
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, f, m, n, cin, cout, 61)
+    assert rb.dense_view == view
+    want, mass = _forward(rb, ir, orr, x, g, W, b)
+    buf = torch.empty(n * cin + 4, device="cuda")
+    gbuf = torch.empty(cin + 1, device="cuda")
+    gd = gbuf[1:]
+    gd.copy_(dev(g))
+    for at in (0, 1):
+        xd = buf[at:at + n * cin].view(n, cin)
+        xd.copy_(dev(x))
+        for relu in (False, True):
+            y, go = scn.conv_fwd(rb, xd, gd, dev(W), dev(b), relu=relu)
+            again, _ = scn.conv_fwd(rb, xd, gd, dev(W), dev(b), relu=relu, noalloc=True)
+            assert torch.equal(y, again)
+            _check(host(y), np.maximum(want, 0) if relu else want, mass, rb.K * cin)
+    # an infinite first channel (padding of short rows may read it)
+    x[n // 2, 0] = np.inf
+    with np.errstate(all="ignore"):
+        want, _ = _forward(rb, ir, orr, x, g, W, b)
+    got = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
