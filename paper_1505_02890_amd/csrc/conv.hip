@@ -1021,8 +1021,24 @@ struct DwArgs {
 };
 
 typedef int32_t v4i_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool V4>
+// A lane's four channels of a row of C: 4 cq .. + 3 of the block that starts at
+// c0.  QUAD (C >= 4): the last ones of a layer start earlier, so that they are
+// four in a row (of any alignment) and repeat channels of the quad before; past
+// the layer they repeat its last four.  A block's slot (its row or column 0 ..
+// 63) holds slot_channel, and is written unless another slot holds that.
+template <bool QUAD>
+__device__ inline int slot_channel(int slot, int c0, int C) {
+  const int q = c0 + (slot & ~3);
+  return QUAD ? min(q, C - 4) + (slot & 3) : min(q + (slot & 3), C - 1);
+}
+template <bool QUAD>
+__device__ inline bool slot_live(int slot, int c0, int C) {
+  return QUAD ? slot_channel<true>(slot, c0, C) >= c0 + (slot & ~3) : c0 + slot < C;
+}
+
+template <bool QUAD>
 __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   __shared__ __align__(16) float red[4 * 32 * 64];
   __shared__ float redT[4 * 64];
@@ -1043,13 +1059,11 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   const int pg = lane >> 4, cq = lane & 15;
   const int64_t ldx = a.Cin, ldd = a.Cout;
   const uint32_t bx = 4u * (uint32_t)a.Cin, bd = 4u * (uint32_t)a.Cout;  // bytes per row
-  // the lane's channels; past the layer they repeat its last ones (those rows
-  // and columns of the block are not written)
   int cx[4], cd[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    cx[e] = V4 ? min(ci0 + 4 * cq, a.Cin - 4) + e : min(ci0 + 4 * cq + e, a.Cin - 1);
-    cd[e] = V4 ? min(co0 + 4 * cq, a.Cout - 4) + e : min(co0 + 4 * cq + e, a.Cout - 1);
+    cx[e] = slot_channel<QUAD>(4 * cq + e, ci0, a.Cin);
+    cd[e] = slot_channel<QUAD>(4 * cq + e, co0, a.Cout);
   }
   // The matrix core drops the bits of small addends below its adder, always
   // downwards: over a million pairs the drift of every sum was 2.4e-6 of dW's
@@ -1059,8 +1073,8 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   v4f gs;
 #pragma unroll
   for (int e = 0; e < 4; ++e) gs[e] = -sgn * a.g_in[cx[e]];
-  const float* const x = V4 ? a.x + cx[0] : a.x;
-  const float* const dyb = V4 ? a.dyb + cd[0] : a.dyb;
+  const float* const x = QUAD ? a.x + cx[0] : a.x;
+  const float* const dyb = QUAD ? a.dyb + cd[0] : a.dyb;
 
   struct Idx {
     int r[4], o[4];
@@ -1089,11 +1103,11 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   auto load = [&](Stage& S, const Idx& I) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (V4) {
-        S.x[i] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(x) +
-                                               (uint64_t)(uint32_t)I.r[i] * bx);
-        S.d[i] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(dyb) +
-                                               (uint64_t)(uint32_t)I.o[i] * bd);
+      if (QUAD) {
+        S.x[i] = *reinterpret_cast<const v4f_any*>(reinterpret_cast<const char*>(x) +
+                                                   (uint64_t)(uint32_t)I.r[i] * bx);
+        S.d[i] = *reinterpret_cast<const v4f_any*>(reinterpret_cast<const char*>(dyb) +
+                                                   (uint64_t)(uint32_t)I.o[i] * bd);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1197,15 +1211,16 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = u * NT + tid;  // operand row e / 64, column e % 64
-        v[u] = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+      v[u] = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
       odd = odd || !(v[u] * 0.f == 0.f);
     }
     // sums that are not finite (operands the split cannot hold): in plain fp32
     if (__syncthreads_or(odd)) {
       for (int u = 0; u < 8; ++u) {
-        const int m = (u * NT + tid) / 64;
-        const int ci = ci0 + 4 * (m & 15) + 2 * i + (m >> 4), co = co0 + (tid & 63);
-        if (ci >= a.Cin || co >= a.Cout) continue;
+        const int m = (u * NT + tid) / 64, sx = 4 * (m & 15) + 2 * i + (m >> 4);
+        if (!slot_live<QUAD>(sx, ci0, a.Cin) || !slot_live<QUAD>(tid & 63, co0, a.Cout)) continue;
+        const int ci = slot_channel<QUAD>(sx, ci0, a.Cin);
+        const int co = slot_channel<QUAD>(tid & 63, co0, a.Cout);
         const float g = a.g_in[ci];
         float s = 0.f;
         for (int64_t p = p_begin; p < p_end; ++p)
@@ -1217,13 +1232,14 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int m = (u * NT + tid) / 64;
-      const int ci = ci0 + 4 * (m & 15) + 2 * i + (m >> 4), co = co0 + (tid & 63);
-      if (ci < a.Cin && co < a.Cout) out[(int64_t)ci * a.Cout + co] = v[u];
+      const int m = (u * NT + tid) / 64, sx = 4 * (m & 15) + 2 * i + (m >> 4);
+      if (slot_live<QUAD>(sx, ci0, a.Cin) && slot_live<QUAD>(tid & 63, co0, a.Cout))
+        out[(int64_t)slot_channel<QUAD>(sx, ci0, a.Cin) * a.Cout +
+            slot_channel<QUAD>(tid & 63, co0, a.Cout)] = v[u];
     }
   }
-  if (ci0 == 0 && tid < 64 && co0 + tid < a.Cout)
-    a.partT[((int64_t)k * a.maxc + c) * a.Cout + co0 + tid] =
+  if (ci0 == 0 && tid < 64 && slot_live<QUAD>(tid, co0, a.Cout))
+    a.partT[((int64_t)k * a.maxc + c) * a.Cout + slot_channel<QUAD>(tid, co0, a.Cout)] =
         ((redT[tid] + redT[64 + tid]) + redT[128 + tid]) + redT[192 + tid];
 }
 
@@ -1828,10 +1844,7 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
     if (rb->n_pairs > 0) {
       const int64_t nwg = L.maxc * K * d.nblk;
       if (scn_status rc = timer_mark(TK_DW, 0, st)) return rc;
-      const bool v4 = Cin % 4 == 0 && Cout % 4 == 0 &&
-                      ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dyb)) & 15) ==
-                          0;
-      if (v4)
+      if (Cin >= 4 && Cout >= 4)
         hipLaunchKernelGGL(dw_partial_kernel<true>, dim3((unsigned)nwg), dim3(NT), 0, st, d);
       else
         hipLaunchKernelGGL(dw_partial_kernel<false>, dim3((unsigned)nwg), dim3(NT), 0, st, d);

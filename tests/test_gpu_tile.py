@@ -378,3 +378,23 @@ def test_few_channels_rounding(scn, view):
         got = scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=("dW", "dbias"))
         want, _ = _weight_gradient(rb, ir, orr, x, g, dy)
         assert _rms(host(got["dW"]) - want) <= U * _rms(want), (f, n, cin)
+
+
+@pytest.mark.parametrize("case", [(4, 4), (5, 61), (35, 50), (64, 66), (67, 129), (130, 7)])
+def test_weight_gradient_ragged(scn, case):
+    """Channel counts that divide nothing, from pointers that are 4-byte aligned
+    only, with NaN around the tensors."""
+    cin, cout = case
+    n = 2100
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, 22, n, cin, cout, 81)
+    dy = stream_rng(82, 1).uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+    want, mass = _weight_gradient(rb, ir, orr, x, g, dy)
+
+    def odd(a):
+        buf = torch.full((a.size + 8,), float("nan"), device="cuda")
+        v = buf[3:3 + a.size].view(*a.shape)
+        v.copy_(dev(a))
+        return v
+
+    got = scn.conv_bwd(rb, odd(x), odd(g), dev(W), None, None, odd(dy))
+    _check(host(got["dW"]), want, mass, max(rb.n_pairs // rb.K, 1))
