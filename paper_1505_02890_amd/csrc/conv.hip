@@ -1337,7 +1337,12 @@ int dw_slots() {
 // the concurrent work-groups: each offset's list is cut into at most
 // DW_ROUNDS * slots / (K * blocks) chunks, so the last round is nearly full
 // instead of holding a few stragglers that would take a round's time alone.
+// Chunks of up to DW_SMALL pairs grow first until one round holds them all: a
+// work-group's sums over its waves and its share of the reduction cost as much
+// as four stages (3x3x3, 16 -> 32 channels, 14k outputs: 37 us in 64-pair
+// chunks, 29 so; the whole gradient without dx).
 constexpr int DW_ROUNDS = 4;
+constexpr int64_t DW_SMALL = 256;
 
 // Which kernel takes the input gradient: the tile kernels read rows of at least
 // four channels.
@@ -1355,7 +1360,9 @@ BwdLayout bwd_layout(const scn_rulebook* rb, int Cin, int Cout, uint32_t flags) 
   const int64_t blocks = ceil_div(Cin, 64) * ceil_div(Cout, 64);
   const int64_t target = std::max<int64_t>(1, DW_ROUNDS * (int64_t)dw_slots() / (rb->K * blocks));
   const int64_t per = ceil_div(std::max<int64_t>(pmax, 1), target);
-  L.chp = std::max<int64_t>(DW_SC, ceil_div(per, DW_SC) * DW_SC);
+  const int64_t fit = std::max<int64_t>(1, (int64_t)dw_slots() / (rb->K * blocks));
+  const int64_t one = std::min(DW_SMALL, ceil_div(std::max<int64_t>(pmax, 1), fit));
+  L.chp = ceil_div(std::max(per, one), DW_SC) * DW_SC;
   L.maxc = std::max<int64_t>(1, ceil_div(pmax, L.chp));
   L.nblk = std::max<int64_t>(1, ceil_div(rb->a_out, RB_ROWS));
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
