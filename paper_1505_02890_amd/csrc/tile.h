@@ -55,9 +55,7 @@ scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, 
 scn_status launch_tile(const TileArgs& a, hipStream_t st);
 
 // Layers of few input channels, whose offsets join the reduction.  Arguments
-// as for launch_tile (gidx, aidx: the pair lists, also beside the dense view,
-// where few_reduce alone reads them: they have no tile starts there),
-// but Wp packed from W as one offset of K*Cin entries (gm = Cin).
+// as for launch_tile, but Wp packed from W as one offset of K*Cin entries (gm = Cin).
 bool few_channels(int K, int Cin);
 scn_status few_forward(const TileArgs& a, hipStream_t st);
 // The weight gradient without dx and dg_in, from dy (times y > 0 unless y is
@@ -66,8 +64,7 @@ scn_status few_forward(const TileArgs& a, hipStream_t st);
 int few_groups(int64_t nrows);
 scn_status few_partials(const TileArgs& a, const float* dy, const float* y, int Cout, float* part,
                         float* partS, hipStream_t st);
-scn_status few_reduce(const TileArgs& a, const float* dy, const float* y, int Cout,
-                      const float* part, const int64_t* off, const float* u0, float* dW,
+scn_status few_reduce(const TileArgs& a, int Cout, const float* part, const float* u0, float* dW,
                       hipStream_t st);
 
 }  // namespace scn

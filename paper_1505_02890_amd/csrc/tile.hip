@@ -343,19 +343,31 @@ __device__ inline float not_finite(const v16f& e) {
   for (int r = 0; r < 16; ++r) t = fmaf(e[r], 0.f, t);
   return t;
 }
+// the registers of a quarter that are not finite
+__device__ inline uint32_t bad_sums(const v16f& e) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) m |= e[r] * 0.f == 0.f ? 0u : 1u << r;
+  return m;
+}
 
-// Writes a 32 x 32 quarter of a tile again, computed in plain fp32: where a
-// sum is not finite, the operands held an infinity, a NaN or a value past
-// bf16's range (or the sum itself overflows).  Runs after the tile's own
-// stores, when its accumulators need no registers any more (kept beside them,
-// this seldom run code cost the kernels a third of their waves).  A lane holds
-// row 32 rt + n32 and, in register 4 j + z, column 64 cb + 32 ct + 8 j + 4 h + z.
+// Computes sums of a 32 x 32 quarter of a tile again on the fp32 matrix
+// instruction and writes those that `bad` names: where a sum is not finite, the
+// operands held an infinity, a NaN or a value past bf16's range (or the sum
+// itself overflows).  A lane holds row 32 rt + n32 and, in register 4 j + z,
+// column 64 cb + 32 ct + 8 j + 4 h + z; each offset's products are summed by
+// themselves and added for the rows that have it, so that a weight that is not
+// finite reaches those rows only.  Runs after the tile's own stores, when its
+// accumulators need no registers any more (kept beside them, this seldom run
+// code cost the kernels a third of their waves).  An input gradient (64 ->
+// 64, 90k sites) whose every sum is NaN takes 590 us, a finite one 97, one with
+// a NaN weight 350; a first layer's forward (1M outputs) 1.26 ms, 0.15, 0.75.
 template <bool SUB, bool SORTED>
 __device__ inline void redo_quarter(const TileArgs& a, const Rows<SORTED>& R, int rt, int ct,
-                                    int cb, int lane) {
-  __threadfence();  // the stores it replaces come from other lanes
-  const int n32 = lane & 31, col0 = 64 * cb + 32 * ct + 4 * (lane >> 5);
-  float e[16];
+                                    int cb, int lane, uint32_t bad) {
+  const int n32 = lane & 31, h = lane >> 5, col0 = 64 * cb + 32 * ct;
+  const float* const Wc = a.W + min(col0 + n32, a.Nc - 1) * a.wn;
+  v16f e;
 #pragma unroll
   for (int r = 0; r < 16; ++r) e[r] = 0.f;
   uint32_t rest = R.U;
@@ -363,25 +375,42 @@ __device__ inline void redo_quarter(const TileArgs& a, const Rows<SORTED>& R, in
     const int k = __builtin_ctz(rest);
     rest &= rest - 1;
     const int row = __builtin_amdgcn_ds_bpermute((32 * rt + n32) * 4, R.row(R.load(k, lane), k));
-    if (row < 0) continue;
-    const float* xp = a.src + (int64_t)row * a.Rk;
-    for (int j = 0; j < a.Rk; ++j) {
-      const float x = SUB ? xp[j] - a.sub[j] : xp[j];
-      // the addresses are formed here, not kept across the loop
-      int64_t wn = a.wn;
-      asm volatile("" : "+s"(wn));
+    const float* const xp = a.src + (int64_t)max(row, 0) * a.Rk;
+    const float* const wp = Wc + k * a.wk;
+    v16f part;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int col = col0 + 8 * (r >> 2) + (r & 3);
-        if (col < a.Nc) e[r] = fmaf(x, a.W[k * a.wk + j * a.wj + col * wn], e[r]);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int r = 0; r < 16; ++r) part[r] = 0.f;
+#pragma unroll 1
+    for (int j0 = 0; j0 < a.Rk; j0 += 8) {
+      float x[4], w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + 2 * u + h, jj = min(j, a.Rk - 1);
+        x[u] = SUB ? xp[jj] - a.sub[jj] : xp[jj];
+        w[u] = wp[jj * a.wj];
+        x[u] = j < a.Rk ? x[u] : 0.f;
+        w[u] = j < a.Rk ? w[u] : 0.f;
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        part = __builtin_amdgcn_mfma_f32_32x32x2f32(w[u], x[u], part, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) e[r] = row >= 0 ? e[r] + part[r] : e[r];
+  }
+  const int64_t pos = R.row0 + 32 * rt + n32;
+  if (pos >= a.nrows) return;
+  float* const dp = a.dst + (SORTED ? (int64_t)a.fperm[pos] : a.wmap ? (int64_t)a.wmap[pos] : pos) *
+                                a.Nc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int col = col0 + 8 * (r >> 2) + 4 * h + (r & 3);
+    if (col < a.Nc && (bad >> r & 1)) {
+      float v = e[r];
+      if (a.add) v += a.add[col];
+      dp[col] = a.relu && !(v > 0.f) ? 0.f : v;
     }
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    put4<SORTED, false>(a, R.row0 + 32 * rt + n32, col0 + 8 * j,
-                        v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
 }
 
 // Work items are contiguous per XCD (work-groups are dispatched round-robin
@@ -401,6 +430,11 @@ __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
                                   const v16f (&acc)[2][2], float* ob, int cb, int lane) {
   const bool redo = __ballot(!(not_finite(acc[0][0]) + not_finite(acc[0][1]) +
                                    not_finite(acc[1][0]) + not_finite(acc[1][1]) == 0.f)) != 0;
+  uint32_t bad0 = 0, bad1 = 0;  // 16 bits per quarter
+  if (redo) {
+    bad0 = bad_sums(acc[0][0]) | bad_sums(acc[0][1]) << 16;
+    bad1 = bad_sums(acc[1][0]) | bad_sums(acc[1][1]) << 16;
+  }
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
     wave_sync();
@@ -421,8 +455,12 @@ __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
     }
   }
   if (redo) {
+    __threadfence();  // the stores that are replaced come from other lanes
 #pragma unroll 1
-    for (int q = 0; q < 4; ++q) redo_quarter<SUB, SORTED>(a, R, q >> 1, q & 1, cb, lane);
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t bad = ((q >> 1 ? bad1 : bad0) >> 16 * (q & 1)) & 0xffffu;
+      if (__ballot(bad != 0)) redo_quarter<SUB, SORTED>(a, R, q >> 1, q & 1, cb, lane, bad);
+    }
   }
 }
 
@@ -739,13 +777,16 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
 #pragma unroll
     for (int z = 0; z < 4; ++z) e[4 * r + z] = s[z];
   }
-  const bool redo = __ballot(!(not_finite(e) == 0.f)) != 0;
+  const uint32_t bad = bad_sums(e);
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     put4<SORTED, false>(a, R.row0 + 32 * (w >> 1) + (lane & 31),
                  64 * cb + 32 * (w & 1) + 8 * j + 4 * (lane >> 5),
                  v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
-  if (redo) redo_quarter<SUB, SORTED>(a, R, w >> 1, w & 1, cb, lane);
+  if (__ballot(bad != 0)) {
+    __threadfence();  // as in store_tile
+    redo_quarter<SUB, SORTED>(a, R, w >> 1, w & 1, cb, lane, bad);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -763,7 +804,9 @@ constexpr int FEW_C = 4, FEW_J = 96;
 // All channels of eight offsets' rows are on their way together: with a round
 // of loads for each channel, a layer of three channels waited three times
 // (3 -> 32 channels on 1.4M tetrahedral outputs, ten offsets: 350 -> 247 us).
-template <bool SORTED, int C>
+// REDO: a NaN is stored as any but ABSENT, which few_values fills in first.
+constexpr uint32_t ABSENT = 0xffffffffu;
+template <bool SORTED, int C, bool REDO>
 __device__ inline void few_rows(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
                                 int ldj, float sgn, int lane) {
   float g[C];
@@ -793,22 +836,25 @@ __device__ inline void few_rows(const TileArgs& a, const Rows<SORTED>& R, float*
     for (int i = 0; i < 8; ++i)
       if (r[i] >= 0) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) v[lane * ldr + (k[i] * C + c) * ldj] = sgn * (t[i][c] - g[c]);
+        for (int c = 0; c < C; ++c) {
+          const float d = sgn * (t[i][c] - g[c]);
+          v[lane * ldr + (k[i] * C + c) * ldj] = REDO && d != d ? __uint_as_float(0x7fc00000u) : d;
+        }
       }
   }
 }
 
-template <bool SORTED>
+template <bool SORTED, bool REDO = false>
 __device__ inline void few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
                                   int ldj, int words, float sgn, int lane) {
   for (int i = lane; i < words / 4; i += 64)
-    reinterpret_cast<v4f*>(v)[i] = v4f{0.f, 0.f, 0.f, 0.f};
+    reinterpret_cast<v4u*>(v)[i] = REDO ? v4u{ABSENT, ABSENT, ABSENT, ABSENT} : v4u{0, 0, 0, 0};
   wave_sync();
   switch (a.Rk) {
-    case 1: few_rows<SORTED, 1>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 2: few_rows<SORTED, 2>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 3: few_rows<SORTED, 3>(a, R, v, ldr, ldj, sgn, lane); break;
-    default: few_rows<SORTED, 4>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 1: few_rows<SORTED, 1, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 2: few_rows<SORTED, 2, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 3: few_rows<SORTED, 3, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    default: few_rows<SORTED, 4, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
   }
   wave_sync();
 }
@@ -1008,6 +1054,7 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
   float* const red = reinterpret_cast<float*>(smem);  // [4][32][64]
   float* const redT = red + 4 * 2048;                 // [4][64]
   float* const out = f.part + (int64_t)blockIdx.x * f.J * f.Cout;
+  bool odd = false;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float t1 = __shfl_xor(tsum[e], 16, 64);
@@ -1031,13 +1078,54 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = u * 256 + tid, j = 32 * jt + e / 64, co = co0 + (tid & 63);
-      if (j < f.J && co < f.Cout)
-        out[(int64_t)j * f.Cout + co] =
-            (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+      const float t = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+      if (j < f.J && co < f.Cout) {
+        out[(int64_t)j * f.Cout + co] = t;
+        odd = odd || !(t * 0.f == 0.f);
+      }
     }
     if (jt == 0 && tid < 64 && co0 + tid < f.Cout)
       f.partS[(int64_t)blockIdx.x * f.Cout + co0 + tid] =
           (redT[tid] + redT[64 + tid]) + (redT[128 + tid] + redT[192 + tid]);
+  }
+  // Sums that are not finite (operands that the split cannot hold) again, in
+  // fp32, a column per lane, from the rows that have the entry's offset.
+  if (!__syncthreads_or(odd)) return;
+  const int co = min(co0 + lane, f.Cout - 1);
+#pragma unroll 1
+  for (int jt = 0; jt < JT; ++jt) {
+    float s[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) s[j] = 0.f;
+#pragma unroll 1
+    for (int64_t tile = (int64_t)blockIdx.x * WGW + w; tile < a.ntile;
+         tile += (int64_t)gridDim.x * WGW) {
+      Rows<SORTED> R;
+      R.init(a, tile, lane);
+      wave_sync();
+      few_values<SORTED, true>(a, R, v, 1, LDJ, 32 * JT * LDJ, 1.f, lane);
+      const int rows = (int)min<int64_t>(TILE, a.nrows - R.row0);
+#pragma unroll 1
+      for (int r = 0; r < rows; ++r) {
+        const int64_t at = (SORTED ? (int64_t)a.fperm[R.row0 + r] : R.row0 + r) * f.Cout + co;
+        const float d = !f.y || f.y[at] > 0.f ? f.dy[at] : 0.f;
+        const float* const p = v + 32 * jt * LDJ + r;
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+          s[j] = __float_as_uint(p[j * LDJ]) == ABSENT ? s[j] : fmaf(p[j * LDJ], d, s[j]);
+      }
+    }
+    __syncthreads();  // every wave has read its values, or the sums before
+#pragma unroll
+    for (int j = 0; j < 32; ++j) red[w * 2048 + j * 64 + lane] = s[j];
+    __syncthreads();
+#pragma unroll 1
+    for (int u = 0; u < 8; ++u) {
+      const int e = u * 256 + tid, j = 32 * jt + e / 64, c = co0 + (tid & 63);
+      if (j < f.J && c < f.Cout && !(out[(int64_t)j * f.Cout + c] * 0.f == 0.f))
+        out[(int64_t)j * f.Cout + c] = (red[e] + red[2048 + e]) + (red[4096 + e] + red[6144 + e]);
+    }
+    __syncthreads();  // the next values are written where the sums stand
   }
 }
 
@@ -1045,48 +1133,25 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
 // elements; thread group g of FR_G sums the partials g (mod FR_G) in order,
 // then the group sums are added in order, in 64 bits (up to 96 partials a
 // thread: in 32 bits their roundings were most of dW's error on sums without
-// cancellation, 7.0e-8 against 64-bit sums, 3.1e-8 now).  An element that is not finite is
-// summed again over its offset's pairs in fp32.
+// cancellation, 7.0e-8 against 64-bit sums, 3.1e-8 now).
 constexpr int FR_E = 32, FR_G = 8;
 __global__ void __launch_bounds__(FR_E * FR_G) few_reduce_kernel(
-    FewArgs f, int nwg, const int64_t* __restrict__ off, const float* __restrict__ u0,
-    float* __restrict__ dW) {
-  __shared__ float red[FR_G][FR_E];
+    const float* __restrict__ part, int nwg, int64_t n, int Cout, int Cin,
+    const float* __restrict__ g_in, const float* __restrict__ u0, float* __restrict__ dW) {
   __shared__ double sums[FR_G][FR_E];
   const int le = threadIdx.x % FR_E, g = threadIdx.x / FR_E;
-  const int64_t i = (int64_t)blockIdx.x * FR_E + le, n = (int64_t)f.J * f.Cout;
+  const int64_t i = (int64_t)blockIdx.x * FR_E + le;
   double d = 0.;
   if (i < n) {
 #pragma unroll 4
-    for (int c = g; c < nwg; c += FR_G) d += f.part[c * n + i];
+    for (int c = g; c < nwg; c += FR_G) d += part[c * n + i];
   }
   sums[g][le] = d;
   __syncthreads();
+  if (g || i >= n) return;
 #pragma unroll
-  for (int h = 1; h < FR_G; ++h) d += sums[(g + h) % FR_G][le];
-  float s, t = (float)d;
-  if (__syncthreads_or(i < n && !(t * 0.f == 0.f))) {
-    s = 0.f;
-    if (i < n && !(t * 0.f == 0.f)) {
-      const int j = (int)(i / f.Cout), co = (int)(i % f.Cout), k = j / f.t.Rk, c = j - k * f.t.Rk;
-      for (int64_t p = off[k] + g; p < off[k + 1]; p += FR_G) {
-        const int64_t o = f.t.aidx[p];
-        const float d = !f.y || f.y[o * f.Cout + co] > 0.f ? f.dy[o * f.Cout + co] : 0.f;
-        s = fmaf(f.t.src[(int64_t)f.t.gidx[p] * f.t.Rk + c] - f.t.sub[c], d, s);
-      }
-    } else if (i < n && g == 0) {
-      s = t;
-    }
-    red[g][le] = s;
-    __syncthreads();
-    t = red[0][le];
-#pragma unroll
-    for (int h = 1; h < FR_G; ++h) t += red[h][le];
-  }
-  if (g == 0 && i < n) {
-    const int j = (int)(i / f.Cout);
-    dW[i] = t + f.t.sub[j % f.t.Rk] * u0[i % f.Cout];
-  }
+  for (int h = 1; h < FR_G; ++h) d += sums[h][le];
+  dW[i] = (float)d + g_in[i / Cout % Cin] * u0[i % Cout];
 }
 
 typedef void (*TileFn)(TileArgs, int, int);
@@ -1209,13 +1274,11 @@ scn_status few_partials(const TileArgs& a, const float* dy, const float* y, int 
   return few_dw_launch<3>(f, v4, nwg, st);
 }
 
-scn_status few_reduce(const TileArgs& a, const float* dy, const float* y, int Cout,
-                      const float* part, const int64_t* off, const float* u0, float* dW,
+scn_status few_reduce(const TileArgs& a, int Cout, const float* part, const float* u0, float* dW,
                       hipStream_t st) {
-  FewArgs f{a, dy, y, Cout, a.K * a.Rk, const_cast<float*>(part), nullptr};
-  hipLaunchKernelGGL(few_reduce_kernel, dim3((unsigned)ceil_div((int64_t)f.J * Cout, FR_E)),
-                     dim3(FR_E * FR_G), 0, st, f, a.nrows > 0 ? few_groups(a.nrows) : 0, off, u0,
-                     dW);
+  const int64_t n = (int64_t)a.K * a.Rk * Cout;
+  hipLaunchKernelGGL(few_reduce_kernel, dim3((unsigned)ceil_div(n, FR_E)), dim3(FR_E * FR_G), 0, st,
+                     part, a.nrows > 0 ? few_groups(a.nrows) : 0, n, Cout, a.Rk, a.sub, u0, dW);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
 }

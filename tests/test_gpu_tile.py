@@ -398,3 +398,116 @@ def test_weight_gradient_ragged(scn, case):
 
     got = scn.conv_bwd(rb, odd(x), odd(g), dev(W), None, None, odd(dy))
     _check(host(got["dW"]), want, mass, max(rb.n_pairs // rb.K, 1))
+
+
+# Near-full grids: lists full enough for the tile kernels, 2000 rows for the one
+# that shares a tile among four waves, 68000 for the one that shares weights.
+GRIDS = {"split": (13, 2000), "wg": (41, 68000)}
+
+
+def _dx_reference(rb, ir, orr, W, dy):
+    d, W64 = torch.from_numpy(dy).double(), torch.from_numpy(W).double()
+    dx = torch.zeros(rb.a_in, W.shape[1], dtype=torch.float64)
+    for k in range(rb.K):
+        i, o = ir[rb.offsets[k]:rb.offsets[k + 1]], orr[rb.offsets[k]:rb.offsets[k + 1]]
+        dx.index_add_(0, i, d[o] @ W64[k].t())
+    return dx.numpy()
+
+
+@pytest.mark.parametrize("grid", ["split", "wg"])
+@pytest.mark.parametrize("view", [False, True])
+@pytest.mark.parametrize("c", [35, 64])
+def test_special_values_stay_local(scn, c, grid, view):
+    """An infinity, a NaN and a value past bf16's range in the rows or weights of
+    each contraction: the results that they enter are as in fp32, all others
+    keep their bits."""
+    m, n = GRIDS[grid]
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, m, n, c, 64, 95)
+    g[:] = 0
+    special = ((n // 7, 3, np.inf), (n // 3, c - 1, np.nan), (n // 2, 0, 3.4e38))
+    W = (np.abs(W) + 0.01).astype(np.float32) * np.float32(0.01)
+
+    def same(got, plain, want, reached):
+        f32 = want.astype(np.float32)
+        assert np.array_equal(got[~reached], plain[~reached])
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(got[np.isinf(got)], f32[np.isinf(f32)])
+        ok = reached & np.isfinite(f32)
+        # what is finite here has 3.4e38 in it, which dwarfs its other terms
+        assert np.allclose(got[ok], want[ok], rtol=1e-5, atol=0)
+
+    def hit(rows_in, rows_out, num):
+        """outputs that take any of the special rows"""
+        r = np.zeros(num, bool)
+        src = np.zeros(max(rb.a_in, rb.a_out), bool)
+        src[[s[0] for s in special]] = True
+        r[rows_out.numpy()[src[rows_in.numpy()]]] = True
+        return r
+
+    with np.errstate(all="ignore"):
+        plain = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+        xs = x.copy()
+        for r, ch, v in special:
+            xs[r, ch] = v
+        want, _ = _forward(rb, ir, orr, xs, g, W, b)
+        got = host(scn.conv_fwd(rb, dev(xs), dev(g), dev(W), dev(b))[0])
+        same(got, plain, want, np.repeat(hit(ir, orr, rb.a_out)[:, None], 64, 1))
+
+        Wt = np.ascontiguousarray(W.transpose(0, 2, 1))
+        x64 = stream_rng(96, 1).standard_normal((n, 64)).astype(np.float32)
+        z = np.zeros(64, np.float32)
+        dy = stream_rng(97, 1).uniform(-1, 1, (rb.a_out, c)).astype(np.float32)
+        ds = dy.copy()
+        for r, ch, v in special:
+            ds[r, ch] = v
+        plain = scn.conv_bwd(rb, dev(x64), dev(z), dev(Wt), None, None, dev(dy), need=("dx", "dW"))
+        got = scn.conv_bwd(rb, dev(x64), dev(z), dev(Wt), None, None, dev(ds), need=("dx", "dW"))
+        same(host(got["dx"]), host(plain["dx"]), _dx_reference(rb, ir, orr, Wt, ds),
+             np.repeat(hit(orr, ir, rb.a_in)[:, None], 64, 1))
+        want, _ = _weight_gradient(rb, ir, orr, x64, z, ds)
+        a, p = host(got["dW"]), host(plain["dW"])
+        chans = np.zeros(c, bool)
+        chans[[s[1] for s in special]] = True
+        assert np.array_equal(a[:, :, ~chans], p[:, :, ~chans])
+        ok = np.isfinite(want)
+        assert not np.any(np.isfinite(a) & ~ok)
+        assert np.array_equal(np.isnan(a[ok]), np.isnan(want[ok]))
+        # weights of the input gradient: one NaN reaches the inputs' column alone,
+        # and there the inputs with that offset
+        Wn = Wt.copy()
+        Wn[1, 5, 2] = np.nan
+        got = host(scn.conv_bwd(rb, dev(x64), dev(z), dev(Wn), None, None, dev(dy),
+                                need=("dx",))["dx"])
+        reached = np.zeros((rb.a_in, 64), bool)
+        reached[ir[rb.offsets[1]:rb.offsets[2]].numpy(), 5] = True
+        assert np.array_equal(np.isnan(got), reached)
+        rest, was = np.delete(got, 5, 1), np.delete(host(plain["dx"]), 5, 1)
+        assert np.array_equal(rest, was)
+        # inputs of the column without that offset may be summed again in fp32
+        ref = _dx_reference(rb, ir, orr, Wt, dy)[:, 5]
+        keep = ~reached[:, 5]
+        assert _rms(got[keep, 5] - ref[keep]) <= 8 * U * _rms(ref)
+
+
+@pytest.mark.parametrize("view", [False, True])
+def test_few_channels_special_values_stay_local(scn, view):
+    """As above for the first layers' weight gradient, whose sums run over all
+    outputs: one infinite output gradient changes its column alone."""
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    for cin, cout in ((1, 64), (3, 70)):
+        rb, x, g, W, b, ir, orr = _layer(scn, 3, 30, 3000, cin, cout, 98)
+        dy = stream_rng(99, 1).uniform(-1, 1, (rb.a_out, cout)).astype(np.float32)
+        need = ("dW", "dbias")
+        plain = host(scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=need)["dW"])
+        dy[rb.a_out // 3, 9] = np.inf
+        x[5, cin - 1] = np.nan
+        got = host(scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=need)["dW"])
+        with np.errstate(all="ignore"):
+            want, _ = _weight_gradient(rb, ir, orr, x, g, dy)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+        reached = np.zeros_like(got, bool)
+        reached[:, cin - 1] = True
+        reached[:, :, 9] = True
+        assert np.array_equal(got[~reached], plain[~reached])
