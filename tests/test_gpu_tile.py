@@ -414,6 +414,30 @@ def _dx_reference(rb, ir, orr, W, dy):
     return dx.numpy()
 
 
+@pytest.mark.parametrize("c", [16, 32, 35, 64, 80, 96])
+@pytest.mark.parametrize("grid", ["split", "wg"])
+@pytest.mark.parametrize("view", [False, True])
+def test_tile_precision(scn, c, grid, view):
+    """Forward, input gradient and weight gradient against 64-bit sums, as rms:
+    within eight units of 2^-24.  A kernel that lost one of the six products
+    would be off by 30 or more (test_split_products)."""
+    m, n = GRIDS[grid]
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, m, n, c, 64, 91)
+    want, _ = _forward(rb, ir, orr, x, g, W, b)
+    y = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+    assert _rms(y - want) <= 8 * U * _rms(want)
+    Wt = np.ascontiguousarray(W.transpose(0, 2, 1))  # dy has c channels
+    x64 = stream_rng(92, 1).standard_normal((n, 64)).astype(np.float32)
+    dy = stream_rng(93, 1).standard_normal((rb.a_out, c)).astype(np.float32)
+    z = np.zeros(64, np.float32)
+    got = scn.conv_bwd(rb, dev(x64), dev(z), dev(Wt), None, None, dev(dy))
+    want = _dx_reference(rb, ir, orr, Wt, dy)
+    assert _rms(host(got["dx"]) - want) <= 8 * U * _rms(want)
+    want, _ = _weight_gradient(rb, ir, orr, x64, z, dy)
+    assert _rms(host(got["dW"]) - want) <= 8 * U * _rms(want)
+
+
 @pytest.mark.parametrize("grid", ["split", "wg"])
 @pytest.mark.parametrize("view", [False, True])
 @pytest.mark.parametrize("c", [35, 64])
