@@ -274,6 +274,16 @@ void scn_rulebook_free(scn_rulebook* rb);
  * which is the same sum regrouped.  act is ReLU if (flags & SCN_RELU), else
  * the identity.
  *
+ * Arithmetic, here and in scn_conv_bwd: fp32 sums of fp32 products, on the
+ * fp32 matrix instruction or, for most stride-1 contractions and the weight
+ * gradient, on the bf16 one with every operand split into three bf16 values
+ * (each product within 2^-24 of its value).  Sums whose operands the split
+ * cannot hold (infinities, NaN, values past bf16's largest) are formed on the
+ * fp32 instruction, and so are those of an operand row (a row of x - g_in or dy,
+ * a column of weights, a channel of the weight gradient's operands) whose
+ * largest value is below 2^-95.  A smaller value beside a larger one keeps what
+ * of it lies above 2^-134; a row that holds nothing above that is taken as zero.
+ *
  *  x     [a_in][Cin];  g_in [Cin];  W [K][Cin][Cout];  bias [Cout] or NULL (= 0)
  *  y     [a_out][Cout] (written);  g_out [Cout] (written)
  * Errors: SCN_ERR_INVALID (null, Cin or Cout < 1, rb NULL), SCN_ERR_HIP.

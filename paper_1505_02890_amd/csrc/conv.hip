@@ -1042,6 +1042,7 @@ template <bool QUAD>
 __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   __shared__ __align__(16) float red[4 * 32 * 64];
   __shared__ float redT[4 * 64];
+  __shared__ uint32_t seen[4][2][4];  // [x 0, x 1, dy 0, dy 1][any, big][wave]
   // flattened (chunk, offset, block) work item, blocks then offsets fastest,
   // contiguous per XCD
   const int64_t item = xcd_remap(blockIdx.x, gridDim.x);
@@ -1118,7 +1119,8 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
     }
   };
   // the MFMA operands of the two tiles
-  auto operands = [&](const v4f (&v)[4], v4u (&f)[2][3]) {
+  Seen tiles[4];  // x's and dy's operand tiles (split.h)
+  auto operands = [&](const v4f (&v)[4], v4u (&f)[2][3], int o) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -1133,6 +1135,8 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
           f[t][s][2 + j] = r[1];
         }
       }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) tiles[o + t].add(f[t][0]);
   };
   v16f acc[2][2];
 #pragma unroll
@@ -1166,8 +1170,8 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
           S.x[i][e] = fmaf(S.x[i][e], sgn, gs[e]);  // +-(x - g_in), rounded once
           tsum[e] += S.d[i][e];
         }
-      operands(S.x, X);
-      operands(S.d, D);
+      operands(S.x, X, 0);
+      operands(S.d, D, 2);
       // the next stage's rows, and the indices after them, are on their way
       // during this one's products (past the chunk: its last pairs, unused)
       load(S, I);
@@ -1196,6 +1200,18 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
     const float t2 = __shfl_xor(s1, 32, 64);
     if (pg == 0) redT[w * 64 + 4 * cq + e] = s1 + t2;
   }
+  if (lane == 0) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      seen[t][0][w] = tiles[t].any32();
+      seen[t][1][w] = tiles[t].big32();
+    }
+  }
+  auto tiny = [&](int t, int row) {  // row of operand tile t
+    const uint32_t(&s)[2][4] = seen[t];
+    return ((s[0][0] | s[0][1] | s[0][2] | s[0][3]) & ~(s[1][0] | s[1][1] | s[1][2] | s[1][3])) >>
+               row & 1;
+  };
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (i) __syncthreads();
@@ -1207,18 +1223,19 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
             (n32 >> 4)] = acc[i][j][r];
     __syncthreads();
     float v[8];
-    bool odd = false;
+    uint32_t bad = 0;
+    const bool td = tiny(2 + (tid >> 1 & 1), ((tid & 63) >> 2) + 16 * (tid & 1));
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = u * NT + tid;  // operand row e / 64, column e % 64
       v[u] = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
-      odd = odd || !(v[u] * 0.f == 0.f);
+      if (td || !(v[u] * 0.f == 0.f) || tiny(i, e / 64)) bad |= 1u << u;
     }
-    // Sums that are not finite (operands that the split cannot hold) again, on
-    // the fp32 matrix instruction: waves 0 and 1 take the columns' halves of the
-    // first half of the pairs, 2 and 3 of the second.  (All of them NaN, 64 -> 64
-    // on 90k sites: 395 us, 112 finite.)
-    if (__syncthreads_or(odd)) {
+    // Sums of operands that the split cannot hold again, on the fp32 matrix
+    // instruction: waves 0 and 1 take the columns' halves of the first half of the
+    // pairs, 2 and 3 of the second.  (All of them NaN, 64 -> 64 on 90k sites: 395
+    // us, 112 finite.)
+    if (__syncthreads_or(bad != 0)) {
       const int64_t half = (p_end - p_begin + 1) / 2;
       const int64_t p1 = w >> 1 ? p_end : p_begin + half;
       const int ci = slot_channel<QUAD>(4 * (n32 & 15) + 2 * i + (n32 >> 4), ci0, a.Cin);
@@ -1248,7 +1265,7 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (!(v[u] * 0.f == 0.f)) v[u] = red[u * NT + tid] + red[2048 + u * NT + tid];
+        if (bad >> u & 1) v[u] = red[u * NT + tid] + red[2048 + u * NT + tid];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -1536,6 +1553,7 @@ static scn_status fwd_run(const scn_rulebook* rb, const float* x, const float* g
     t.sub = sub;
     t.subtract = 1;
     t.Wp = Ws;
+    t.wtiny = tile_wtiny(Ws, few ? 1 : rb->K, few ? rb->K * Cin : Cin, Cout);
     t.W = W;
     t.wk = (int64_t)Cin * Cout;
     t.wj = Cout;
@@ -1800,6 +1818,7 @@ scn_status scn_conv_bwd(const scn_rulebook* rb, const float* x, const float* g_i
     a.src = dyb;
     a.sub = gzero;
     a.Wp = reinterpret_cast<uint32_t*>(wpack);
+    a.wtiny = tile_wtiny(a.Wp, K, Cout, Cin);
     a.W = W;
     a.wk = (int64_t)Cin * Cout;
     a.wj = 1;

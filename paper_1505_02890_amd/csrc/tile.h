@@ -11,6 +11,7 @@ struct TileArgs {
   const float* src;      // gathered rows [nsrc][Rk], Rk >= 4 (launch_tile)
   const float* sub;      // [TILE_PAD] subtracted from every row (zero past Rk); 16-byte aligned
   const uint32_t* Wp;    // split weights (tile_pack)
+  const uint32_t* wtiny; // ... and whether a column of them is tiny (tile_wtiny)
   const float* W;        // the weights themselves: W_k(j, n) = W[k*wk + j*wj + n*wn]
   int64_t wk, wj, wn;
   // Rows from pair lists (nb == null): list k of the rulebook ascends by
@@ -43,6 +44,7 @@ constexpr int TILE_PAD = 256;  // floats of TileArgs::sub (Rk <= 256, padded to 
 // weights.
 int tile_steps(int Rk);
 size_t tile_pack_bytes(int K, int Rk, int Nc);
+const uint32_t* tile_wtiny(const uint32_t* Wp, int K, int Rk, int Nc);
 
 // Splits W_k(j, n) into a.Wp's layout; fills sub[0 .. TILE_PAD) with g[j % gm]
 // (zeros if g is null or past Rk).  With g_pre (else null): g_pre = bias + sum_k g W_k and

@@ -47,7 +47,7 @@ constexpr int64_t TILE_SPLIT = 1024;
 // chunks of two: 48 and 80 channels 4 to 14% slower but for single cases.)
 int chunk_steps(int Rk) { return Rk >= 32 && ceil_div(Rk, 16) % 2 == 0 ? 2 : 1; }
 
-constexpr int PRE_COLS = 8;
+constexpr int PRE_COLS = 4;
 
 // The channel that entry j of the reduction holds, of a row of Rk >= 4 read in
 // chunks of C = 16 TC entries.  A last chunk that the row does not fill starts
@@ -77,27 +77,40 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
                                                        const float* __restrict__ g, int gm,
                                                        const float* __restrict__ bias, int relu,
                                                        v4u* __restrict__ Wp,
+                                                       uint32_t* __restrict__ wtiny,
                                                        float* __restrict__ sub, int np,
                                                        float* __restrict__ g_pre,
                                                        float* __restrict__ g_out) {
   if ((int)blockIdx.x >= np) {
-    // g_pre[n] = B[n] + sum_k g W_k(., n) and g_out = act(g_pre): PRE_COLS
-    // columns per block, NT / PRE_COLS threads each, in 64 bits (few products,
-    // and every output starts from them)
+    // Per column n whether it is tiny (split.h), and, if asked for, g_pre[n] = B[n] +
+    // sum_k g W_k(., n) and g_out = act(g_pre): PRE_COLS columns per block, NT /
+    // PRE_COLS threads each, in 64 bits (few products, and every output starts
+    // from them)
     __shared__ double part[NT];
+    __shared__ uint32_t obits[NT / 64][PRE_COLS];
     const int c = threadIdx.x % PRE_COLS, t = threadIdx.x / PRE_COLS;
     const int n = ((int)blockIdx.x - np) * PRE_COLS + c;
+    const float* const gs = g ? g : W;  // without g (gm = 1) some sum, not used
     double s = 0.;
+    uint32_t o = 0;
     if (n < Nc) {
       const int tot = K * Rk;
-#pragma unroll 4
+#pragma unroll 8
       for (int q = t; q < tot; q += NT / PRE_COLS) {
         const int k = q / Rk, j = q - k * Rk;
-        s = fma((double)g[j % gm], (double)W[k * wk + j * wj + n * wn], s);
+        const float v = W[k * wk + j * wj + n * wn];
+        o |= __float_as_uint(v);
+        s = fma((double)gs[j % gm], (double)v, s);
       }
     }
     part[threadIdx.x] = s;
+#pragma unroll
+    for (int d = PRE_COLS; d < 64; d <<= 1) o |= (uint32_t)__shfl_xor((int)o, d, 64);
+    if ((threadIdx.x & 63) < PRE_COLS) obits[threadIdx.x >> 6][c] = o;
     __syncthreads();
+    if (t == 0 && n < Nc)
+      wtiny[n] = tiny_floats(obits[0][c] | obits[1][c] | obits[2][c] | obits[3][c]);
+    if (!g_pre) return;
     for (int q = NT / 2; q >= PRE_COLS; q >>= 1) {
       if ((int)threadIdx.x < q) part[threadIdx.x] += part[threadIdx.x + q];
       __syncthreads();
@@ -343,6 +356,18 @@ __device__ inline float not_finite(const v16f& e) {
   for (int r = 0; r < 16; ++r) t = fmaf(e[r], 0.f, t);
   return t;
 }
+// Whether column `lane` of a column block is tiny.
+__device__ inline bool column_tiny(const TileArgs& a, int cb, int lane) {
+  return a.wtiny[min(64 * cb + lane, a.Nc - 1)] != 0;
+}
+
+// The registers of a quarter whose row (the lane's) or column is tiny; cols:
+// bit c of column 32 ct + c.
+__device__ inline uint32_t tiny_sums(bool row, uint32_t cols, int lane) {
+  uint32_t m = cols >> 4 * (lane >> 5) & 0x0f0f0f0fu;  // columns 8 j + 4 h + z
+  m = (m | m >> 4) & 0x00ff00ffu;
+  return row ? 0xffffu : (m | m >> 8) & 0xffffu;
+}
 // the registers of a quarter that are not finite
 __device__ inline uint32_t bad_sums(const v16f& e) {
   uint32_t m = 0;
@@ -354,7 +379,8 @@ __device__ inline uint32_t bad_sums(const v16f& e) {
 // Computes sums of a 32 x 32 quarter of a tile again on the fp32 matrix
 // instruction and writes those that `bad` names: where a sum is not finite, the
 // operands held an infinity, a NaN or a value past bf16's range (or the sum
-// itself overflows).  A lane holds row 32 rt + n32 and, in register 4 j + z,
+// itself overflows); where a row or a column is tiny, its low parts are lost
+// (split.h).  A lane holds row 32 rt + n32 and, in register 4 j + z,
 // column 64 cb + 32 ct + 8 j + 4 h + z; each offset's products are summed by
 // themselves and added for the rows that have it, so that a weight that is not
 // finite reaches those rows only.  Runs after the tile's own stores, when its
@@ -427,13 +453,19 @@ constexpr int OUT_LD = 68;                 // floats per row
 constexpr int OUT_B = 32 * OUT_LD * 4;     // bytes of ob
 template <bool SUB, bool SORTED>
 __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
-                                  const v16f (&acc)[2][2], float* ob, int cb, int lane) {
-  const bool redo = __ballot(!(not_finite(acc[0][0]) + not_finite(acc[0][1]) +
+                                  const v16f (&acc)[2][2], uint64_t tiny_rows, uint64_t tiny_cols,
+                                  float* ob, int cb, int lane) {
+  const bool redo = tiny_rows || tiny_cols ||
+                    __ballot(!(not_finite(acc[0][0]) + not_finite(acc[0][1]) +
                                    not_finite(acc[1][0]) + not_finite(acc[1][1]) == 0.f)) != 0;
   uint32_t bad0 = 0, bad1 = 0;  // 16 bits per quarter
   if (redo) {
-    bad0 = bad_sums(acc[0][0]) | bad_sums(acc[0][1]) << 16;
-    bad1 = bad_sums(acc[1][0]) | bad_sums(acc[1][1]) << 16;
+    const bool row0 = tiny_rows >> (lane & 31) & 1, row1 = tiny_rows >> (32 + (lane & 31)) & 1;
+    const uint32_t col0 = (uint32_t)tiny_cols, col1 = (uint32_t)(tiny_cols >> 32);
+    bad0 = bad_sums(acc[0][0]) | tiny_sums(row0, col0, lane) |
+           (bad_sums(acc[0][1]) | tiny_sums(row0, col1, lane)) << 16;
+    bad1 = bad_sums(acc[1][0]) | tiny_sums(row1, col0, lane) |
+           (bad_sums(acc[1][1]) | tiny_sums(row1, col1, lane)) << 16;
   }
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
@@ -499,8 +531,10 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
   const int cb = (int)(u - grp * ncb);
   const int64_t tile = min(grp * WGW + w, a.ntile - 1);
   const bool live = grp * WGW + w < a.ntile;
+  const bool wtiny = column_tiny(a, cb, lane);
   Rows<SORTED> R;
   R.init(a, tile, lane);
+  const uint64_t tiny_cols = __ballot(wtiny);
   if (lane == 0) ush[w] = R.U;
   __syncthreads();
   uint32_t U = 0;
@@ -566,6 +600,9 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+  // Bits of the rows' high parts, or'ed (split.h; Seen's branch spills here and
+  // doubles the kernel's time).
+  uint32_t ro[2] = {0, 0};
   const int nit = __builtin_popcount(U) * nchunk;
   if (nit > 0) {
     Item c{__builtin_ctz(U), 0, U & (U - 1)};
@@ -621,6 +658,8 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 #pragma unroll
           for (int q = 0; q < 3; ++q)
             Wf[s][ct][q] = *reinterpret_cast<const v4u*>(wl + ((s * 2 + ct) * 3 + q) * 1024);
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) ro[rt] = or_bits(ro[rt], X[s][rt].s[0]);
         if (SORTED)
           step_products<false>(acc, Wf[s], X[s]);
         else if (s == 0 && first)
@@ -641,7 +680,15 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
     }
   }
   if (!live) return;
-  store_tile<SUB, SORTED>(a, R, acc, reinterpret_cast<float*>(smem + w * OUT_B), cb, lane);
+  uint64_t tiny_rows = 0;
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    const uint64_t any = __ballot((ro[rt] & 0x7fff7fffu) != 0);
+    const uint64_t big = __ballot((ro[rt] & 0x70007000u) != 0);
+    tiny_rows |= (uint64_t)((uint32_t)(any | any >> 32) & ~(uint32_t)(big | big >> 32)) << 32 * rt;
+  }
+  store_tile<SUB, SORTED>(a, R, acc, tiny_rows, tiny_cols, reinterpret_cast<float*>(smem + w * OUT_B), cb,
+                          lane);
 }
 
 // Small layers: the four waves of a work-group share one tile and take every
@@ -657,17 +704,18 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
   constexpr int GOFF = 65536;
   char* const buf = smem + w * 16384;
   const int nst = nchunk * TC;
-  const float* const gsh = reinterpret_cast<const float*>(smem + GOFF);
+  float* const gsh = reinterpret_cast<float*>(smem + GOFF);
   if (SUB) {
-    for (int c = tid; c < 16 * nst; c += NT)
-      reinterpret_cast<float*>(smem + GOFF)[c] = a.sub[Entries(a.Rk, 16 * TC).channel(c)];
+    for (int c = tid; c < 16 * nst; c += NT) gsh[c] = a.sub[Entries(a.Rk, 16 * TC).channel(c)];
     __syncthreads();
   }
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
   const int64_t tile = u / ncb;
   const int cb = (int)(u - tile * ncb);
+  const bool wtiny = column_tiny(a, cb, lane);
   Rows<SORTED> R;
   R.init(a, tile, lane);
+  const uint64_t tiny_cols = __ballot(wtiny);
   const uint32_t U = R.U;
   const float* const src = a.src;
   const int Rk = a.Rk;
@@ -692,6 +740,7 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  Seen rows[2];  // (split.h)
   auto mult = [&](int s, int ch, const WSet& A) {
     Frag3 X[2];
     v4f g0 = {0.f, 0.f, 0.f, 0.f}, g1 = g0;
@@ -701,7 +750,10 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
       g1 = *reinterpret_cast<const v4f*>(gp + 4);
     }
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB, false>(buf + s * 4096, turn, rt, g0, g1, 1.f);
+    for (int rt = 0; rt < 2; ++rt) {
+      X[rt] = turn_read<SUB, false>(buf + s * 4096, turn, rt, g0, g1, 1.f);
+      rows[rt].add(X[rt].s[0]);
+    }
     if (s == 0)
       step_products<true>(part, A.f, X);
     else
@@ -758,6 +810,14 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
   // quarter j = 2 rt + ct of the tile goes to wave j, which adds the four
   // waves' sums in wave order
   __syncthreads();
+  uint32_t* const seen = reinterpret_cast<uint32_t*>(smem + GOFF);  // [row tile][any, big][wave]
+  if (lane == 0) {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      seen[8 * rt + w] = rows[rt].any32();
+      seen[8 * rt + 4 + w] = rows[rt].big32();
+    }
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -777,7 +837,11 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
 #pragma unroll
     for (int z = 0; z < 4; ++z) e[4 * r + z] = s[z];
   }
-  const uint32_t bad = bad_sums(e);
+  const uint32_t* const sn = seen + 8 * (w >> 1);
+  const uint32_t tiny_rows =
+      (sn[0] | sn[1] | sn[2] | sn[3]) & ~(sn[4] | sn[5] | sn[6] | sn[7]);
+  const uint32_t bad = bad_sums(e) | tiny_sums(tiny_rows >> (lane & 31) & 1,
+                                               (uint32_t)(tiny_cols >> 32 * (w & 1)), lane);
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     put4<SORTED, false>(a, R.row0 + 32 * (w >> 1) + (lane & 31),
@@ -801,18 +865,19 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
 constexpr int FEW_C = 4, FEW_J = 96;
 
 // V(row, j) of the wave's tile: v[row * ldr + j * ldj], times sgn; zeroed first.
+// Returns the bits of the lane's row's values.
 // All channels of eight offsets' rows are on their way together: with a round
 // of loads for each channel, a layer of three channels waited three times
 // (3 -> 32 channels on 1.4M tetrahedral outputs, ten offsets: 350 -> 247 us).
 // REDO: a NaN is stored as any but ABSENT, which few_values fills in first.
 constexpr uint32_t ABSENT = 0xffffffffu;
 template <bool SORTED, int C, bool REDO>
-__device__ inline void few_rows(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
-                                int ldj, float sgn, int lane) {
+__device__ inline uint32_t few_rows(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
+                                    int ldj, float sgn, int lane) {
   float g[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) g[c] = a.sub[c];
-  uint32_t rest = R.U;
+  uint32_t rest = R.U, bits = 0;
   while (rest) {
     // eight offsets at a time, so that their loads overlap (past the last one
     // it is repeated: the same value again)
@@ -839,24 +904,28 @@ __device__ inline void few_rows(const TileArgs& a, const Rows<SORTED>& R, float*
         for (int c = 0; c < C; ++c) {
           const float d = sgn * (t[i][c] - g[c]);
           v[lane * ldr + (k[i] * C + c) * ldj] = REDO && d != d ? __uint_as_float(0x7fc00000u) : d;
+          bits |= __float_as_uint(d);
         }
       }
   }
+  return bits;
 }
 
 template <bool SORTED, bool REDO = false>
-__device__ inline void few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
+__device__ inline uint32_t few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
                                   int ldj, int words, float sgn, int lane) {
   for (int i = lane; i < words / 4; i += 64)
     reinterpret_cast<v4u*>(v)[i] = REDO ? v4u{ABSENT, ABSENT, ABSENT, ABSENT} : v4u{0, 0, 0, 0};
   wave_sync();
+  uint32_t bits;
   switch (a.Rk) {
-    case 1: few_rows<SORTED, 1, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 2: few_rows<SORTED, 2, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 3: few_rows<SORTED, 3, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    default: few_rows<SORTED, 4, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 1: bits = few_rows<SORTED, 1, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 2: bits = few_rows<SORTED, 2, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 3: bits = few_rows<SORTED, 3, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    default: bits = few_rows<SORTED, 4, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
   }
   wave_sync();
+  return bits;
 }
 
 __host__ __device__ constexpr int few_lds(int nst, int ncb) {
@@ -877,7 +946,8 @@ __global__ void __launch_bounds__(64 * WGW, 3) few_fwd_kernel(TileArgs a, int ns
   float* const ob = ncb == 1 ? v : v + 64 * ldr;
   Rows<SORTED> R;
   R.init(a, tile, lane);
-  few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane);
+  const uint64_t tiny_rows =
+      __ballot(tiny_floats(few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane)));
   const int n32 = lane & 31, h = lane >> 5;
   for (int cb = 0; cb < ncb; ++cb) {
     const v4u* wp = reinterpret_cast<const v4u*>(a.Wp) + (int64_t)cb * nst * 384 + lane;
@@ -941,7 +1011,8 @@ __global__ void __launch_bounds__(64 * WGW, 3) few_fwd_kernel(TileArgs a, int ns
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    store_tile<true, SORTED>(a, R, acc, ob, cb, lane);
+    store_tile<true, SORTED>(a, R, acc, tiny_rows, __ballot(column_tiny(a, cb, lane)), ob, cb,
+                             lane);
   }
 }
 
@@ -980,6 +1051,7 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   v4f tsum = {0.f, 0.f, 0.f, 0.f};
+  Seen entries[JT], cols[2];  // (split.h)
   for (int64_t tile = (int64_t)blockIdx.x * WGW + w; tile < a.ntile;
        tile += (int64_t)gridDim.x * WGW) {
     Rows<SORTED> R;
@@ -1037,11 +1109,14 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
 #pragma unroll
       for (int i = 0; i < 4; ++i) tsum += d[i];
 #pragma unroll
+      for (int t = 0; t < 2; ++t) cols[t].add(D[t][0]);
+#pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         const float* p = v + (32 * jt + n32) * LDJ + 16 * st + 8 * h;
         const v4f p0 = *reinterpret_cast<const v4f*>(p), p1 = *reinterpret_cast<const v4f*>(p + 4);
         const float e[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
         const Frag3 X = split8(e);
+        entries[jt].add(X.s[0]);
 #pragma unroll
         for (int q = 0; q < SPLIT_PROD; ++q)
 #pragma unroll
@@ -1054,6 +1129,7 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
   float* const red = reinterpret_cast<float*>(smem);  // [4][32][64]
   float* const redT = red + 4 * 2048;                 // [4][64]
   float* const out = f.part + (int64_t)blockIdx.x * f.J * f.Cout;
+  uint32_t* const seen = reinterpret_cast<uint32_t*>(redT + 256);  // [cols, entries][any, big][wave]
   bool odd = false;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1074,22 +1150,35 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
     if (jt == 0 && pg == 0)
 #pragma unroll
       for (int e = 0; e < 4; ++e) redT[w * 64 + 4 * cq + e] = tsum[e];
+    if (jt == 0 && lane == 0) {
+#pragma unroll
+      for (int t = 0; t < 2 + JT; ++t) {
+        seen[8 * t + w] = t < 2 ? cols[t & 1].any32() : entries[t < 2 ? 0 : t - 2].any32();
+        seen[8 * t + 4 + w] = t < 2 ? cols[t & 1].big32() : entries[t < 2 ? 0 : t - 2].big32();
+      }
+    }
     __syncthreads();
+    auto tiny = [&](int t, int row) {
+      const uint32_t* const sn = seen + 8 * t;
+      return ((sn[0] | sn[1] | sn[2] | sn[3]) & ~(sn[4] | sn[5] | sn[6] | sn[7])) >> row & 1;
+    };
+    const bool tc = tiny(tid >> 1 & 1, ((tid & 63) >> 2) + 16 * (tid & 1));
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = u * 256 + tid, j = 32 * jt + e / 64, co = co0 + (tid & 63);
       const float t = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
       if (j < f.J && co < f.Cout) {
-        out[(int64_t)j * f.Cout + co] = t;
-        odd = odd || !(t * 0.f == 0.f);
+        // a sum to be redone is marked by a NaN
+        const bool bad = !(t * 0.f == 0.f) || tc || tiny(2 + jt, e / 64);
+        out[(int64_t)j * f.Cout + co] = bad ? __uint_as_float(0x7fc00000u) : t;
+        odd = odd || bad;
       }
     }
     if (jt == 0 && tid < 64 && co0 + tid < f.Cout)
       f.partS[(int64_t)blockIdx.x * f.Cout + co0 + tid] =
           (redT[tid] + redT[64 + tid]) + (redT[128 + tid] + redT[192 + tid]);
   }
-  // Sums that are not finite (operands that the split cannot hold) again, in
-  // fp32, a column per lane, from the rows that have the entry's offset.
+  // Sums of operands that the split cannot hold again, in fp32, a column per lane, from the rows that have the entry's offset.
   if (!__syncthreads_or(odd)) return;
   const int co = min(co0 + lane, f.Cout - 1);
 #pragma unroll 1
@@ -1175,8 +1264,13 @@ TileFn tile_fn(int tc, bool vec, bool sub, bool sorted, bool split) {
 
 int tile_steps(int Rk) { return (int)ceil_div(Rk, 16); }
 
-size_t tile_pack_bytes(int K, int Rk, int Nc) {
-  return (size_t)K * ceil_div(Nc, 64) * tile_steps(Rk) * 6144;
+// Split weights, then a word per column (wtiny).
+static size_t pack_words(int K, int Rk, int Nc) {
+  return (size_t)K * ceil_div(Nc, 64) * tile_steps(Rk) * 1536;
+}
+size_t tile_pack_bytes(int K, int Rk, int Nc) { return (pack_words(K, Rk, Nc) + Nc) * 4; }
+const uint32_t* tile_wtiny(const uint32_t* Wp, int K, int Rk, int Nc) {
+  return Wp + pack_words(K, Rk, Nc);
 }
 
 scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, int Rk, int Nc,
@@ -1184,10 +1278,10 @@ scn_status tile_pack(const float* W, int64_t wk, int64_t wj, int64_t wn, int K, 
                      float* g_pre, float* g_out, hipStream_t st) {
   const int nst = tile_steps(Rk), ncb = (int)ceil_div(Nc, 64);
   const int64_t n = std::max<int64_t>((int64_t)K * ncb * nst * 128, TILE_PAD);
-  const int64_t np = ceil_div(n, NT), ng = g_pre ? ceil_div(Nc, PRE_COLS) : 0;
+  const int64_t np = ceil_div(n, NT), ng = ceil_div(Nc, PRE_COLS);
   hipLaunchKernelGGL(tile_pack_kernel, dim3((unsigned)(np + ng)), dim3(NT), 0, st, W, wk, wj, wn,
-                     K, Rk, Nc, nst, ncb, Entries(Rk, chunks ? 16 * chunk_steps(Rk) : 1), g, gm, bias, relu, reinterpret_cast<v4u*>(Wp), sub, (int)np,
-                     g_pre, g_out);
+                     K, Rk, Nc, nst, ncb, Entries(Rk, chunks ? 16 * chunk_steps(Rk) : 1), g, gm, bias, relu, reinterpret_cast<v4u*>(Wp),
+                     Wp + pack_words(K, Rk, Nc), sub, (int)np, g_pre, g_out);
   SCN_LAUNCH_CHECK();
   return SCN_OK;
 }
@@ -1249,7 +1343,8 @@ int few_groups(int64_t nrows) {
 
 template <int JT>
 static scn_status few_dw_launch(const FewArgs& f, bool v4, int nwg, hipStream_t st) {
-  const size_t smem = std::max<size_t>((size_t)WGW * 32 * JT * 68 * 4, (4 * 2048 + 256) * 4);
+  const size_t smem = std::max<size_t>((size_t)WGW * 32 * JT * 68 * 4,
+                                       (4 * 2048 + 256 + 8 * (2 + JT)) * 4);
   auto fn = f.t.nb ? (v4 ? few_dw_kernel<JT, true, true> : few_dw_kernel<JT, true, false>)
                    : (v4 ? few_dw_kernel<JT, false, true> : few_dw_kernel<JT, false, false>);
   static std::atomic<size_t> had[4];

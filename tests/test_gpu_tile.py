@@ -535,3 +535,63 @@ def test_few_channels_special_values_stay_local(scn, view):
         reached[:, cin - 1] = True
         reached[:, :, 9] = True
         assert np.array_equal(got[~reached], plain[~reached])
+
+
+def _scaled(a, e):
+    """a * 2^e, rounded to float32 once (2^e itself may be subnormal)"""
+    return np.ldexp(a.astype(np.float64), e).astype(np.float32)
+
+
+@pytest.mark.parametrize("e", [-100, -112, -120, -126])
+@pytest.mark.parametrize("kind", ["split", "wg", "few"])
+@pytest.mark.parametrize("view", [False, True])
+def test_tiny_operands(scn, e, kind, view):
+    """Rows, weights and output gradients whose low parts lie below bf16's last
+    bit (2^-133): as close to 64-bit sums as at any other scale.  Whole tensors,
+    then single rows, columns and channels beside ordinary ones."""
+    m, n = GRIDS["wg" if kind == "wg" else "split"]
+    c = 3 if kind == "few" else 64
+    scn.set_dense_forward(0 if view else 1 << 40, 1)
+    rb, x, g, W, b, ir, orr = _layer(scn, 2, m, n, c, 64, 101)
+    g[:] = 0
+    b[:] = 0
+    dy = stream_rng(102, 1).standard_normal((rb.a_out, 64)).astype(np.float32)
+
+    def close(got, want, rows=Ellipsis):
+        got, want = got[rows], want[rows]
+        assert _rms(got - want) <= 8 * U * _rms(want) + 2.0 ** -148
+
+    def fwd(x, W):
+        y = host(scn.conv_fwd(rb, dev(x), dev(g), dev(W), dev(b))[0])
+        return y, _forward(rb, ir, orr, x, g, W, b)[0]
+
+    def bwd(x, W, dy):
+        need = ("dW", "dbias") if kind == "few" else ("dx", "dW")
+        r = scn.conv_bwd(rb, dev(x), dev(g), dev(W), None, None, dev(dy), need=need)
+        dx = None if kind == "few" else (host(r["dx"]), _dx_reference(rb, ir, orr, W, dy))
+        return dx, (host(r["dW"]), _weight_gradient(rb, ir, orr, x, g, dy)[0])
+
+    close(*fwd(_scaled(x, e), W))
+    close(*fwd(x, _scaled(W, e)))
+    for args in ((_scaled(x, e), W, dy), (x, _scaled(W, e), dy), (x, W, _scaled(dy, e))):
+        dx, dW = bwd(*args)
+        if dx is not None:
+            close(*dx)
+        close(*dW)
+    # every output of one batch of rows tiny: inputs in a corner of the grid
+    co = rb.export()[0].cpu().numpy()
+    far = (co[:, 1:] >= m // 2 + 1).all(1)
+    reach = np.zeros(n, bool)
+    reach[ir.numpy()[far[orr.numpy()]]] = True
+    xs = np.where(reach[:, None], _scaled(x, e), x)
+    near_only = far & ~np.isin(np.arange(rb.a_out), orr.numpy()[~reach[ir.numpy()]])
+    assert near_only.any()
+    close(*fwd(xs, W), rows=near_only)
+    # one column of weights, one channel of dy and x
+    Ws, ds, xc = W.copy(), dy.copy(), x.copy()
+    Ws[:, :, 37], ds[:, 37], xc[:, c - 1] = _scaled(W[:, :, 37], e), _scaled(dy[:, 37], e), \
+        _scaled(x[:, c - 1], e)
+    close(*fwd(x, Ws), rows=(slice(None), 37))
+    _, dW = bwd(xc, W, ds)
+    close(*dW, rows=(slice(None), slice(0, c - 1), 37))
+    close(*dW, rows=(slice(None), c - 1, slice(0, 37)))
