@@ -1469,8 +1469,9 @@ enum class Fwd { few, tile, dense, gather };
 //    item, wins with one column block and little to multiply per item: items
 //    of one step (16 -> 64: tile 1.04 to 1.24, 48 -> 64: 1.02 to 1.31, 20 -> 64:
 //    1.2 to 1.5, 112 -> 64: 0.98 to 1.38), rows not on 64 bytes (56 -> 64: 0.9 to
-//    1.14), 32 channels and few offsets (32 -> 64: 0.97 to 1.1; 0.96 to 0.99 at
-//    27).  It reads rows 16 bytes at a time.
+//    1.14), 32 channels, few offsets and outputs (32 -> 32: 1.07 to 1.18, 1.02 to
+//    1.05 at 27 offsets; 32 -> 64: 0.96 to 1.1).  It reads rows 16 bytes at a
+//    time.
 //  - Lists: tiles of consecutive outputs are about as full as the list, and the
 //    gather kernel multiplies active pairs alone, at 0.4 of the rate.  What it
 //    saves of the tile kernel's steps (64 rows x 64 columns x 16 channels) has
@@ -1482,12 +1483,14 @@ Fwd fwd_route(const scn_rulebook* rb, const float* x, int Cin, int Cout) {
   const double fill = (double)rb->n_pairs / ((double)rb->K * std::max<int64_t>(rb->a_out, 1));
   const int nst = tile_steps(Cin);
   if (rb->fnb) {
+    const bool vec = Cin % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     if (few_channels(rb->K, Cin) && (Cin <= 2 || (fill >= 0.5 && rb->K * Cin <= 64)))
       return Fwd::few;
-    if (Cin < 4) return Fwd::dense;
-    const bool vec = Cin % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
-    const bool thin = Cin < 32 || (Cin == 32 && rb->K < 16) || (nst % 2 && nst <= DENSE_STEPS) ||
-                      (nst == 4 && Cin < 64);
+    // four channels at 27 offsets: one chain over all of a row's products rounds
+    // more often than the fp32 kernel (9.8e-8 off 64-bit sums, 8.8e-8)
+    if (Cin < 4 || (Cin == 4 && rb->K * Cin > 96 && vec)) return Fwd::dense;
+    const bool thin = Cin < 32 || (Cin == 32 && rb->K < 16 && Cout <= 32) ||
+                      (nst % 2 && nst <= DENSE_STEPS) || (nst == 4 && Cin < 64);
     return vec && thin && Cout <= 64 && fill < 0.7 ? Fwd::dense : Fwd::tile;
   }
   if (few_channels(rb->K, Cin)) return Fwd::few;
