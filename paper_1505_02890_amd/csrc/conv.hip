@@ -544,13 +544,9 @@ scn_status launch_gather(GatherArgs a, hipStream_t st) {
       ((size_t)(TM * TILE + 1) * ACC_LD + 2 * (size_t)SROWS * (16 * nkt + 4)) * sizeof(float);
   const bool vec = a.vec_ok;
   GatherFn fn = gather_fn(nkt, vec);
-  static bool attr_done[2][17] = {};
-  bool& done = attr_done[vec][nkt];
-  if (!done) {
-    SCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    done = true;
-  }
+  static LdsLimit limits[2][17];
+  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn), limits[vec][nkt], smem))
+    return rc;
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg, ncb), dim3(NT), smem, st, a);
   SCN_LAUNCH_CHECK();
   return SCN_OK;

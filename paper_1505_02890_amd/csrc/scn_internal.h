@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <string>
@@ -67,6 +68,22 @@ void dfree(void* p, hipStream_t s, const Allocator& a);
       return SCN_ERR_HIP;                                                              \
     }                                                                                  \
   } while (0)
+
+// Raises a kernel's dynamic LDS limit to `want` bytes on the current device (the
+// limit belongs to a device's copy of the kernel), once per device and size.
+struct LdsLimit {
+  std::atomic<size_t> had[64];  // zero if static
+};
+inline scn_status allow_lds(const void* fn, LdsLimit& limit, size_t want) {
+  if (want <= 65536) return SCN_OK;
+  int dev = 0;
+  SCN_HIP(hipGetDevice(&dev));
+  std::atomic<size_t>* const had = dev >= 0 && dev < 64 ? &limit.had[dev] : nullptr;
+  if (had && had->load(std::memory_order_acquire) >= want) return SCN_OK;
+  SCN_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want));
+  if (had) had->store(want, std::memory_order_release);
+  return SCN_OK;
+}
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

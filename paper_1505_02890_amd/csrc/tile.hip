@@ -25,8 +25,6 @@
 // the MFMAs (1.37).
 #include <hip/hip_runtime.h>
 
-#include <atomic>
-
 #include "split.h"
 #include "tile.h"
 
@@ -1297,14 +1295,11 @@ scn_status launch_tile(const TileArgs& a, hipStream_t st) {
   const int tc = chunk_steps(a.Rk);
   const size_t base = split ? 65536 : wg_lds(tc) + 64, smem = base + (size_t)nst * 64;
   TileFn fn = tile_fn(tc, vec, a.subtract, a.nb != nullptr, split);
-  // once per process and kernel: its largest size
-  static std::atomic<bool> sized[2][2][3][2];
-  std::atomic<bool>& done = sized[tc - 1][vec][a.nb ? 2 : a.subtract ? 1 : 0][split];
-  if (base + 1024 > 65536 && !done.load(std::memory_order_acquire)) {
-    SCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)(base + 1024)));
-    done.store(true, std::memory_order_release);
-  }
+  static LdsLimit limits[2][2][3][2];
+  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn),
+                                limits[tc - 1][vec][a.nb ? 2 : a.subtract ? 1 : 0][split],
+                                base + 1024))  // its largest size
+    return rc;
   const int64_t nwg = split ? items : ceil_div(a.ntile, WGW) * ncb;
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(split ? NT : 64 * WGW), smem, st, a, nst / tc,
                      ncb);
@@ -1314,21 +1309,13 @@ scn_status launch_tile(const TileArgs& a, hipStream_t st) {
 
 bool few_channels(int K, int Cin) { return Cin <= FEW_C && K * Cin <= FEW_J; }
 
-// raises a kernel's dynamic LDS limit, once per process and kernel
-static scn_status allow_lds(const void* fn, std::atomic<size_t>& had, size_t want) {
-  if (want <= 65536 || had.load(std::memory_order_acquire) >= want) return SCN_OK;
-  SCN_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want));
-  had.store(want, std::memory_order_release);
-  return SCN_OK;
-}
-
 scn_status few_forward(const TileArgs& a, hipStream_t st) {
   if (a.nrows <= 0 || a.ntile <= 0) return SCN_OK;
   const int nst = tile_steps(a.K * a.Rk), ncb = (int)ceil_div(a.Nc, 64);
   const size_t smem = (size_t)WGW * few_lds(nst, ncb);  // at most 137 KB (6 steps)
   auto fn = a.nb ? few_fwd_kernel<true> : few_fwd_kernel<false>;
-  static std::atomic<size_t> had[2];
-  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn), had[a.nb != nullptr], smem))
+  static LdsLimit limits[2];
+  if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn), limits[a.nb != nullptr], smem))
     return rc;
   hipLaunchKernelGGL(fn, dim3((unsigned)ceil_div(a.ntile, WGW)), dim3(64 * WGW), smem, st, a,
                      nst, ncb);
@@ -1347,9 +1334,9 @@ static scn_status few_dw_launch(const FewArgs& f, bool v4, int nwg, hipStream_t 
                                        (4 * 2048 + 256 + 8 * (2 + JT)) * 4);
   auto fn = f.t.nb ? (v4 ? few_dw_kernel<JT, true, true> : few_dw_kernel<JT, true, false>)
                    : (v4 ? few_dw_kernel<JT, false, true> : few_dw_kernel<JT, false, false>);
-  static std::atomic<size_t> had[4];
+  static LdsLimit limits[4];
   if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn),
-                                had[(f.t.nb ? 2 : 0) + (v4 ? 1 : 0)], smem))
+                                limits[(f.t.nb ? 2 : 0) + (v4 ? 1 : 0)], smem))
     return rc;
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg, (unsigned)ceil_div(f.Cout, 64)), dim3(64 * WGW), smem,
                      st, f);
