@@ -437,11 +437,15 @@ scn_status scn_set_kernel_timer(const hipEvent_t* events);
  * independent v_mfma_f32_16x16x4f32 products on registers only (the fp32
  * matrix-core ceiling), writes one value per wave to out (device float
  * [4 * workgroups]) and stores its flop count in *flops (host).
+ * scn_ceiling_mfma_bf16 does the same with `iters` x 4 products of
+ * v_mfma_f32_32x32x16_bf16 (of the split products, six make one).
  * Errors: SCN_ERR_INVALID, SCN_ERR_HIP.
  */
 scn_status scn_ceiling_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
 scn_status scn_ceiling_mfma_f32(float* out, int64_t workgroups, int32_t iters, double* flops,
                                 hipStream_t stream);
+scn_status scn_ceiling_mfma_bf16(float* out, int64_t workgroups, int32_t iters, double* flops,
+                                 hipStream_t stream);
 
 /* Message describing the last failing call on this thread ("" if none). */
 const char* scn_last_error(void);

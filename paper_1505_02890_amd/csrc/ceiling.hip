@@ -1,18 +1,17 @@
 // Measured ceilings for the roofline fractions the benchmark reports beside
 // the published peaks: a plain streaming copy (what HBM delivers to a simple
 // kernel, and the reference reading of the memory-traffic counters) and a
-// register-only loop of fp32 matrix-core products (what the matrix cores
-// deliver at the clock they hold under sustained load).
+// register-only loop of fp32 or of bf16 matrix-core products (what the matrix
+// cores deliver at the clock they hold under sustained load).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
 #include "scn_internal.h"
+#include "split.h"
 
 namespace scn {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int COPY_THREADS = 256;
 
@@ -50,6 +49,30 @@ __global__ void __launch_bounds__(256) mfma_loop_kernel(float* __restrict__ out,
   if (lane == 0) out[(int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)] = s;
 }
 
+// The same of v_mfma_f32_32x32x16_bf16 (32768 flops each), which the split
+// products run on.
+constexpr int BF16_CHAINS = 4;
+__global__ void __launch_bounds__(256) mfma_bf16_loop_kernel(float* __restrict__ out, int iters) {
+  const uint32_t lane = threadIdx.x & 63;
+  const v4u a = {0x3f803f80u + lane, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  const v4u b = {0x3f803f80u, 0x3f803f80u + lane, 0x3f803f80u, 0x3f803f80u};
+  v16f acc[BF16_CHAINS];
+#pragma unroll
+  for (int c = 0; c < BF16_CHAINS; ++c)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+  for (int i = 0; i < iters; ++i) {
+#pragma unroll
+    for (int c = 0; c < BF16_CHAINS; ++c) acc[c] = mfma_bf16(a, b, acc[c]);
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < BF16_CHAINS; ++c)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += acc[c][r];
+  if (lane == 0) out[(int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)] = s;
+}
+
 }  // namespace
 }  // namespace scn
 
@@ -83,6 +106,20 @@ scn_status scn_ceiling_mfma_f32(float* out, int64_t workgroups, int32_t iters, d
   hipLaunchKernelGGL(mfma_loop_kernel, dim3((unsigned)workgroups), dim3(256), 0, st, out, iters);
   SCN_LAUNCH_CHECK();
   *flops = (double)workgroups * 4 * iters * MFMA_CHAINS * 2048.0;
+  return SCN_OK;
+}
+
+scn_status scn_ceiling_mfma_bf16(float* out, int64_t workgroups, int32_t iters, double* flops,
+                                 hipStream_t st) {
+  clear_error();
+  if (!out || !flops || workgroups < 1 || workgroups > INT32_MAX || iters < 1) {
+    set_error("scn_ceiling_mfma_bf16: invalid argument");
+    return SCN_ERR_INVALID;
+  }
+  hipLaunchKernelGGL(mfma_bf16_loop_kernel, dim3((unsigned)workgroups), dim3(256), 0, st, out,
+                     iters);
+  SCN_LAUNCH_CHECK();
+  *flops = (double)workgroups * 4 * iters * BF16_CHAINS * 32768.0;
   return SCN_OK;
 }
 

@@ -22,8 +22,11 @@ constexpr int KD_MAX = 4;  // coordinates per site of the keyed builder (keyed.h
 constexpr int DENSE_ROWS = 32;  // output rows per block of the dense forward view
 // Default policy for the dense forward view (scn_set_dense_forward): stride-1
 // rulebooks with at least this many output rows and offsets.  Below them the
-// view's sort and extra launches cost more than the forward saves (measured
-// on the paper's networks, whose 2x2x2 layers never gain).
+// view's sort and extra launches cost more than one forward saves: 3x3x3, 64 ->
+// 64 channels, 276k outputs: +64 us of build, -23 us of forward; 555k: +62, -97;
+// 1.1M: +80, -222.  2x2x2 layers gain at 445k outputs with 96 -> 128 channels
+// (+41, -96), lose there with 32 -> 64 (+48, -13); the channels are not known
+// when a rulebook is built.
 constexpr int64_t DENSE_MIN_ROWS = int64_t(1) << 19;
 constexpr int DENSE_MIN_K = 8;
 

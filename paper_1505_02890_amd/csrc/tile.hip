@@ -11,11 +11,12 @@
 // `sub` itself, so its difference is exactly zero.
 //
 // What bounds it: per 16 channels a wave issues 24 MFMAs of 32 clocks (768)
-// against about 110 vector instructions (440) and, per CU, 10 KB of LDS reads
+// against about 115 vector instructions (460) and, per CU, 10 KB of LDS reads
 // and 6 KB of L1 traffic per wave.  With everything in LDS the loop runs at
 // 1570 TFLOP/s of bf16 (the MFMAs alone at 2190); on the 1M-site 64 -> 64
-// layer the input gradient, whose tiles are full, runs at 985 (1.36 ms; 2.11
-// on the fp32 instruction with LDS accumulators), the clock at 1.95 GHz.
+// layer the input gradient, whose tiles are full, runs at 885 (1.50 ms, of
+// which 0.04 watch for tiny rows; 2.11 on the fp32 instruction with LDS
+// accumulators), the clock at 1.95 GHz.
 // Gathering 1024 fixed rows takes 0.09 ms off it, no gather at all 0.2.
 // Measured and not kept there: LDS reads and splits of the next step
 // interleaved with a step's MFMAs (1.33 ms against 1.23 left in blocks, before
@@ -1323,7 +1324,8 @@ scn_status few_forward(const TileArgs& a, hipStream_t st) {
   return SCN_OK;
 }
 
-// Work-groups of the weight gradient: three per CU, a tile per wave at least
+// Work-groups of the weight gradient, a tile per wave at least: three per CU for
+// up to 32 entries (JT = 1); of the longer ones two run at once
 int few_groups(int64_t nrows) {
   return (int)std::min<int64_t>(768, std::max<int64_t>(1, ceil_div(nrows, TILE * WGW)));
 }
