@@ -1039,6 +1039,7 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   __shared__ __align__(16) float red[4 * 32 * 64];
   __shared__ float redT[4 * 64];
   __shared__ uint32_t seen[4][2][4];  // [x 0, x 1, dy 0, dy 1][any, big][wave]
+  __shared__ uint32_t some[4];        // whether a wave saw a row without a large value
   // flattened (chunk, offset, block) work item, blocks then offsets fastest,
   // contiguous per XCD
   const int64_t item = xcd_remap(blockIdx.x, gridDim.x);
@@ -1116,7 +1117,7 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
   };
   // the MFMA operands of the two tiles
   Seen tiles[4];  // x's and dy's operand tiles (split.h)
-  auto operands = [&](const v4f (&v)[4], v4u (&f)[2][3], int o) {
+  auto operands = [&](const v4f (&v)[4], v4u (&f)[2][3]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -1131,8 +1132,6 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
           f[t][s][2 + j] = r[1];
         }
       }
-#pragma unroll
-    for (int t = 0; t < 2; ++t) tiles[o + t].add(f[t][0]);
   };
   v16f acc[2][2];
 #pragma unroll
@@ -1166,8 +1165,8 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
           S.x[i][e] = fmaf(S.x[i][e], sgn, gs[e]);  // +-(x - g_in), rounded once
           tsum[e] += S.d[i][e];
         }
-      operands(S.x, X, 0);
-      operands(S.d, D, 2);
+      operands(S.x, X);
+      operands(S.d, D);
       // the next stage's rows, and the indices after them, are on their way
       // during this one's products (past the chunk: its last pairs, unused)
       load(S, I);
@@ -1181,6 +1180,13 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             acc[i][j] = mfma_bf16(X[i][split_a(q)], D[j][split_b(q)], acc[i][j]);
+      // under the products (a branch before them would part the loads from the
+      // splits)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        tiles[t].add(X[t][0]);
+        tiles[2 + t].add(D[t][0]);
+      }
       if (p0 >= p_end) break;
     }
   }
@@ -1202,12 +1208,16 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
       seen[t][0][w] = tiles[t].any32();
       seen[t][1][w] = tiles[t].big32();
     }
+    some[w] = (tiles[0].any32() & ~tiles[0].big32()) | (tiles[1].any32() & ~tiles[1].big32()) |
+              (tiles[2].any32() & ~tiles[2].big32()) | (tiles[3].any32() & ~tiles[3].big32());
   }
-  auto tiny = [&](int t, int row) {  // row of operand tile t
-    const uint32_t(&s)[2][4] = seen[t];
-    return ((s[0][0] | s[0][1] | s[0][2] | s[0][3]) & ~(s[1][0] | s[1][1] | s[1][2] | s[1][3])) >>
-               row & 1;
+  auto put = [&](int i, int e, float v) {  // operand row e / 64 of tile i, column e % 64
+    const int m = e / 64, sx = 4 * (m & 15) + 2 * i + (m >> 4);
+    if (slot_live<QUAD>(sx, ci0, a.Cin) && slot_live<QUAD>(tid & 63, co0, a.Cout))
+      out[(int64_t)slot_channel<QUAD>(sx, ci0, a.Cin) * a.Cout +
+          slot_channel<QUAD>(tid & 63, co0, a.Cout)] = v;
   };
+  uint32_t odd = 0;  // which of the thread's sums are not finite
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (i) __syncthreads();
@@ -1218,62 +1228,64 @@ __global__ void __launch_bounds__(NT, DW_OCC) dw_partial_kernel(DwArgs a) {
         red[w * 2048 + (8 * (r >> 2) + 4 * h + (r & 3)) * 64 + 4 * (n32 & 15) + 2 * j +
             (n32 >> 4)] = acc[i][j][r];
     __syncthreads();
-    float v[8];
-    uint32_t bad = 0;
-    const bool td = tiny(2 + (tid >> 1 & 1), ((tid & 63) >> 2) + 16 * (tid & 1));
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = u * NT + tid;  // operand row e / 64, column e % 64
-      v[u] = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
-      if (td || !(v[u] * 0.f == 0.f) || tiny(i, e / 64)) bad |= 1u << u;
-    }
-    // Sums of operands that the split cannot hold again, on the fp32 matrix
-    // instruction: waves 0 and 1 take the columns' halves of the first half of the
-    // pairs, 2 and 3 of the second.  (All of them NaN, 64 -> 64 on 90k sites: 395
-    // us, 112 finite.)
-    if (__syncthreads_or(bad != 0)) {
-      const int64_t half = (p_end - p_begin + 1) / 2;
-      const int64_t p1 = w >> 1 ? p_end : p_begin + half;
-      const int ci = slot_channel<QUAD>(4 * (n32 & 15) + 2 * i + (n32 >> 4), ci0, a.Cin);
-      const int co = slot_channel<QUAD>(32 * (w & 1) + n32, co0, a.Cout);
-      const float g = a.g_in[ci];
-      v16f s;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll 1
-      for (int64_t p = w >> 1 ? p_begin + half : p_begin; p < p1; p += 8) {
-        float xv[4], dv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t q = p + 2 * u + h, qq = min(q, p1 - 1);
-          xv[u] = a.x[a.in_rows[qq] * ldx + ci] - g;
-          dv[u] = a.dyb[a.out_rows[qq] * ldd + co];
-          xv[u] = q < p1 ? xv[u] : 0.f;
-          dv[u] = q < p1 ? dv[u] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          s = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[u], dv[u], s, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        red[(w >> 1) * 2048 + (8 * (r >> 2) + 4 * h + (r & 3)) * 64 + 32 * (w & 1) + n32] = s[r];
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (bad >> u & 1) v[u] = red[u * NT + tid] + red[2048 + u * NT + tid];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int m = (u * NT + tid) / 64, sx = 4 * (m & 15) + 2 * i + (m >> 4);
-      if (slot_live<QUAD>(sx, ci0, a.Cin) && slot_live<QUAD>(tid & 63, co0, a.Cout))
-        out[(int64_t)slot_channel<QUAD>(sx, ci0, a.Cin) * a.Cout +
-            slot_channel<QUAD>(tid & 63, co0, a.Cout)] = v[u];
+      const int e = u * NT + tid;
+      const float v = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
+      odd |= v * 0.f == 0.f ? 0u : 1u << (8 * i + u);
+      put(i, e, v);
     }
   }
   if (ci0 == 0 && tid < 64 && slot_live<QUAD>(tid, co0, a.Cout))
     a.partT[((int64_t)k * a.maxc + c) * a.Cout + slot_channel<QUAD>(tid, co0, a.Cout)] =
         ((redT[tid] + redT[64 + tid]) + redT[128 + tid]) + redT[192 + tid];
+  // Sums of operands that the split cannot hold again, on the fp32 matrix
+  // instruction: waves 0 and 1 take the columns' halves of the first half of the
+  // pairs, 2 and 3 of the second.  (All of them NaN, 64 -> 64 on 90k sites: 395
+  // us, 112 finite.)
+  if (!__syncthreads_or(odd != 0 || (some[0] | some[1] | some[2] | some[3]) != 0)) return;
+  auto tiny = [&](int t, int row) {  // row of operand tile t
+    const uint32_t(&q)[2][4] = seen[t];
+    return ((q[0][0] | q[0][1] | q[0][2] | q[0][3]) & ~(q[1][0] | q[1][1] | q[1][2] | q[1][3])) >>
+               row & 1;
+  };
+  const bool td = tiny(2 + (tid >> 1 & 1), ((tid & 63) >> 2) + 16 * (tid & 1));
+#pragma unroll 1
+  for (int i = 0; i < 2; ++i) {
+    const int64_t half = (p_end - p_begin + 1) / 2;
+    const int64_t p1 = w >> 1 ? p_end : p_begin + half;
+    const int ci = slot_channel<QUAD>(4 * (n32 & 15) + 2 * i + (n32 >> 4), ci0, a.Cin);
+    const int co = slot_channel<QUAD>(32 * (w & 1) + n32, co0, a.Cout);
+    const float g = a.g_in[ci];
+    v16f s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll 1
+    for (int64_t p = w >> 1 ? p_begin + half : p_begin; p < p1; p += 8) {
+      float xv[4], dv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t q = p + 2 * u + h, qq = min(q, p1 - 1);
+        xv[u] = a.x[a.in_rows[qq] * ldx + ci] - g;
+        dv[u] = a.dyb[a.out_rows[qq] * ldd + co];
+        xv[u] = q < p1 ? xv[u] : 0.f;
+        dv[u] = q < p1 ? dv[u] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[u], dv[u], s, 0, 0, 0);
+    }
+    __syncthreads();  // the sums before have been read
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      red[(w >> 1) * 2048 + (8 * (r >> 2) + 4 * h + (r & 3)) * 64 + 32 * (w & 1) + n32] = s[r];
+    __syncthreads();
+#pragma unroll 1
+    for (int u = 0; u < 8; ++u) {
+      const int e = u * NT + tid;
+      if ((odd >> (8 * i + u) & 1) || td || tiny(i, e / 64)) put(i, e, red[e] + red[2048 + e]);
+    }
+  }
 }
 
 // dW[k][ci][co] = sum_c part + g_in[ci] * u0[co];  T[k][co] = sum_c partT.

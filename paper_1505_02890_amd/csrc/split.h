@@ -20,8 +20,12 @@
 //  - An infinity, a NaN or a value that rounds past bf16's largest turns the
 //    rests into NaN, so every sum it enters is NaN or infinite.
 //  - Values below 2^-109 lose what lies below 2^-133.  That counts where
-//    nothing larger stands beside them: kernels watch each operand row (Seen),
-//    and one whose largest value is below 2^-95 (tiny) is redone.  Beside a
+//    nothing larger stands beside them: an operand row whose largest value is
+//    below 2^-95 (tiny) is redone.  The tile kernels see it by a row's sums, none
+//    of which can then exceed its column's sum |W| 2^-95, and columns of tiny
+//    weights when they are packed; the weight gradient watches its operands
+//    (Seen).  (Watching them in the tile kernels' loops too cost 1 to 3%, or with
+//    Seen's branch, which spills there, all of the time again.)  Beside a
 //    value of 2^-95 or more the loss is below 2^-38 of it.  (Rows with nothing
 //    above 2^-134 have no high parts and are taken as zero.)
 #pragma once

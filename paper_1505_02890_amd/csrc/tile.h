@@ -11,7 +11,7 @@ struct TileArgs {
   const float* src;      // gathered rows [nsrc][Rk], Rk >= 4 (launch_tile)
   const float* sub;      // [TILE_PAD] subtracted from every row (zero past Rk); 16-byte aligned
   const uint32_t* Wp;    // split weights (tile_pack)
-  const uint32_t* wtiny; // ... and whether a column of them is tiny (tile_wtiny)
+  const uint32_t* wtiny; // ... per column whether it is tiny, then row_limit (tile_wtiny)
   const float* W;        // the weights themselves: W_k(j, n) = W[k*wk + j*wj + n*wn]
   int64_t wk, wj, wn;
   // Rows from pair lists (nb == null): list k of the rulebook ascends by

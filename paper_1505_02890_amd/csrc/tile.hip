@@ -11,12 +11,11 @@
 // `sub` itself, so its difference is exactly zero.
 //
 // What bounds it: per 16 channels a wave issues 24 MFMAs of 32 clocks (768)
-// against about 115 vector instructions (460) and, per CU, 10 KB of LDS reads
+// against about 110 vector instructions (440) and, per CU, 10 KB of LDS reads
 // and 6 KB of L1 traffic per wave.  With everything in LDS the loop runs at
 // 1570 TFLOP/s of bf16 (the MFMAs alone at 2190); on the 1M-site 64 -> 64
-// layer the input gradient, whose tiles are full, runs at 885 (1.50 ms, of
-// which 0.04 watch for tiny rows; 2.11 on the fp32 instruction with LDS
-// accumulators), the clock at 1.95 GHz.
+// layer the input gradient, whose tiles are full, runs at 905 (1.46 ms; 2.11
+// on the fp32 instruction with LDS accumulators), the clock at 1.95 GHz.
 // Gathering 1024 fixed rows takes 0.09 ms off it, no gather at all 0.2.
 // Measured and not kept there: LDS reads and splits of the next step
 // interleaved with a step's MFMAs (1.33 ms against 1.23 left in blocks, before
@@ -81,16 +80,17 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
                                                        float* __restrict__ g_pre,
                                                        float* __restrict__ g_out) {
   if ((int)blockIdx.x >= np) {
-    // Per column n whether it is tiny (split.h), and, if asked for, g_pre[n] = B[n] +
+    // Per column n whether it is tiny (split.h), the largest sum that a tiny row
+    // can have there (sum |W| 2^-95, rounded up), and, if asked for, g_pre[n] = B[n] +
     // sum_k g W_k(., n) and g_out = act(g_pre): PRE_COLS columns per block, NT /
     // PRE_COLS threads each, in 64 bits (few products, and every output starts
     // from them)
-    __shared__ double part[NT];
+    __shared__ double part[2][NT / 64][PRE_COLS];
     __shared__ uint32_t obits[NT / 64][PRE_COLS];
     const int c = threadIdx.x % PRE_COLS, t = threadIdx.x / PRE_COLS;
     const int n = ((int)blockIdx.x - np) * PRE_COLS + c;
     const float* const gs = g ? g : W;  // without g (gm = 1) some sum, not used
-    double s = 0.;
+    double s = 0., l = 0.;
     uint32_t o = 0;
     if (n < Nc) {
       const int tot = K * Rk;
@@ -99,23 +99,36 @@ __global__ void __launch_bounds__(NT) tile_pack_kernel(const float* __restrict__
         const int k = q / Rk, j = q - k * Rk;
         const float v = W[k * wk + j * wj + n * wn];
         o |= __float_as_uint(v);
+        l += (double)fabsf(v);
         s = fma((double)gs[j % gm], (double)v, s);
       }
     }
-    part[threadIdx.x] = s;
+    // over a wave's threads of a column, then the waves in order
 #pragma unroll
-    for (int d = PRE_COLS; d < 64; d <<= 1) o |= (uint32_t)__shfl_xor((int)o, d, 64);
-    if ((threadIdx.x & 63) < PRE_COLS) obits[threadIdx.x >> 6][c] = o;
-    __syncthreads();
-    if (t == 0 && n < Nc)
-      wtiny[n] = tiny_floats(obits[0][c] | obits[1][c] | obits[2][c] | obits[3][c]);
-    if (!g_pre) return;
-    for (int q = NT / 2; q >= PRE_COLS; q >>= 1) {
-      if ((int)threadIdx.x < q) part[threadIdx.x] += part[threadIdx.x + q];
-      __syncthreads();
+    for (int d = PRE_COLS; d < 64; d <<= 1) {
+      o |= (uint32_t)__shfl_xor((int)o, d, 64);
+      l += __shfl_xor(l, d, 64);
+      s += __shfl_xor(s, d, 64);
     }
+    if ((threadIdx.x & 63) < PRE_COLS) {
+      const int w = threadIdx.x >> 6;
+      obits[w][c] = o;
+      part[0][w][c] = s;
+      part[1][w][c] = l;
+    }
+    __syncthreads();
     if (t == 0 && n < Nc) {
-      const float v = (float)(part[c] + (bias ? (double)bias[n] : 0.));
+#pragma unroll
+      for (int w = 1; w < NT / 64; ++w) {
+        o |= obits[w][c];
+        s += part[0][w][c];
+        l += part[1][w][c];
+      }
+      wtiny[n] = tiny_floats(o);
+      wtiny[Nc + n] = __float_as_uint((float)(l * 0x1.01p-95));
+    }
+    if (g_pre && t == 0 && n < Nc) {
+      const float v = (float)(s + (bias ? (double)bias[n] : 0.));
       g_pre[n] = v;
       g_out[n] = relu && !(v > 0.f) ? 0.f : v;
     }
@@ -367,6 +380,29 @@ __device__ inline uint32_t tiny_sums(bool row, uint32_t cols, int lane) {
   m = (m | m >> 4) & 0x00ff00ffu;
   return row ? 0xffffu : (m | m >> 8) & 0xffffu;
 }
+// The largest sum that a tiny row can have at a column.
+__device__ inline float row_limit(const TileArgs& a, int col) {
+  return __uint_as_float(a.wtiny[a.Nc + min(col, a.Nc - 1)]);
+}
+// The rows of a quarter (bit n32) that have a sum but zero, and one too large for
+// a tiny row; limit(c): of the quarter's column c.
+struct RowSums {
+  uint32_t any, big;
+};
+template <class Limit>
+__device__ inline RowSums row_sums(const v16f& e, int lane, Limit limit) {
+  bool any = false, big = false;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    any |= e[r] != 0.f;
+    const float l = limit(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));  // all lanes take part
+    big |= fabsf(e[r]) > l;
+    __builtin_amdgcn_sched_barrier(0);  // seldom run: one limit in registers at a time
+  }
+  const uint64_t m = __ballot(any), b = __ballot(big);
+  return {(uint32_t)(m | m >> 32), (uint32_t)(b | b >> 32)};
+}
+
 // the registers of a quarter that are not finite
 __device__ inline uint32_t bad_sums(const v16f& e) {
   uint32_t m = 0;
@@ -452,13 +488,29 @@ constexpr int OUT_LD = 68;                 // floats per row
 constexpr int OUT_B = 32 * OUT_LD * 4;     // bytes of ob
 template <bool SUB, bool SORTED>
 __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
-                                  const v16f (&acc)[2][2], uint64_t tiny_rows, uint64_t tiny_cols,
-                                  float* ob, int cb, int lane) {
+                                  const v16f (&acc)[2][2], uint64_t tiny_cols, float* ob,
+                                  int cb, int lane) {
+  // A row is not tiny if one of its sums is too large for that; the first column's
+  // mostly are.
+  const float limit = row_limit(a, 64 * cb + lane);
+  const float first = __shfl(limit, 4 * (lane >> 5), 64);
+  const uint64_t big0 = __ballot(fabsf(acc[0][0][0]) > first);
+  const uint64_t big1 = __ballot(fabsf(acc[1][0][0]) > first);
+  uint64_t tiny_rows = 0;
+  if (__builtin_expect(~((uint32_t)(big0 | big0 >> 32) & (uint32_t)(big1 | big1 >> 32)), 0)) {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const RowSums l = row_sums(acc[rt][0], lane, [&](int c) { return __shfl(limit, c, 64); });
+      const RowSums r =
+          row_sums(acc[rt][1], lane, [&](int c) { return __shfl(limit, 32 + c, 64); });
+      tiny_rows |= (uint64_t)((l.any | r.any) & ~(l.big | r.big)) << 32 * rt;
+    }
+  }
   const bool redo = tiny_rows || tiny_cols ||
                     __ballot(!(not_finite(acc[0][0]) + not_finite(acc[0][1]) +
                                    not_finite(acc[1][0]) + not_finite(acc[1][1]) == 0.f)) != 0;
   uint32_t bad0 = 0, bad1 = 0;  // 16 bits per quarter
-  if (redo) {
+  if (__builtin_expect(redo, 0)) {
     const bool row0 = tiny_rows >> (lane & 31) & 1, row1 = tiny_rows >> (32 + (lane & 31)) & 1;
     const uint32_t col0 = (uint32_t)tiny_cols, col1 = (uint32_t)(tiny_cols >> 32);
     bad0 = bad_sums(acc[0][0]) | tiny_sums(row0, col0, lane) |
@@ -485,7 +537,7 @@ __device__ inline void store_tile(const TileArgs& a, const Rows<SORTED>& R,
                            *reinterpret_cast<const v4f*>(ob + r * OUT_LD + 4 * (lane & 15)));
     }
   }
-  if (redo) {
+  if (__builtin_expect(redo, 0)) {
     __threadfence();  // the stores that are replaced come from other lanes
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
@@ -599,9 +651,6 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // Bits of the rows' high parts, or'ed (split.h; Seen's branch spills here and
-  // doubles the kernel's time).
-  uint32_t ro[2] = {0, 0};
   const int nit = __builtin_popcount(U) * nchunk;
   if (nit > 0) {
     Item c{__builtin_ctz(U), 0, U & (U - 1)};
@@ -657,8 +706,6 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
 #pragma unroll
           for (int q = 0; q < 3; ++q)
             Wf[s][ct][q] = *reinterpret_cast<const v4u*>(wl + ((s * 2 + ct) * 3 + q) * 1024);
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) ro[rt] = or_bits(ro[rt], X[s][rt].s[0]);
         if (SORTED)
           step_products<false>(acc, Wf[s], X[s]);
         else if (s == 0 && first)
@@ -679,14 +726,7 @@ __global__ void __launch_bounds__(64 * WGW, SORTED ? 3 : 2) tile_wg_kernel(TileA
     }
   }
   if (!live) return;
-  uint64_t tiny_rows = 0;
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const uint64_t any = __ballot((ro[rt] & 0x7fff7fffu) != 0);
-    const uint64_t big = __ballot((ro[rt] & 0x70007000u) != 0);
-    tiny_rows |= (uint64_t)((uint32_t)(any | any >> 32) & ~(uint32_t)(big | big >> 32)) << 32 * rt;
-  }
-  store_tile<SUB, SORTED>(a, R, acc, tiny_rows, tiny_cols, reinterpret_cast<float*>(smem + w * OUT_B), cb,
+  store_tile<SUB, SORTED>(a, R, acc, tiny_cols, reinterpret_cast<float*>(smem + w * OUT_B), cb,
                           lane);
 }
 
@@ -711,10 +751,14 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
   const int64_t u = xcd_item(blockIdx.x, gridDim.x);
   const int64_t tile = u / ncb;
   const int cb = (int)(u - tile * ncb);
-  const bool wtiny = column_tiny(a, cb, lane);
   Rows<SORTED> R;
   R.init(a, tile, lane);
-  const uint64_t tiny_cols = __ballot(wtiny);
+  // the columns' limits and whether they are tiny, for the end
+  uint32_t* const limits = reinterpret_cast<uint32_t*>(smem + GOFF + 1024);
+  if (tid < 128) {
+    const int n = min(64 * cb + (tid & 63), a.Nc - 1);
+    limits[tid] = a.wtiny[tid < 64 ? a.Nc + n : n];
+  }
   const uint32_t U = R.U;
   const float* const src = a.src;
   const int Rk = a.Rk;
@@ -739,7 +783,6 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  Seen rows[2];  // (split.h)
   auto mult = [&](int s, int ch, const WSet& A) {
     Frag3 X[2];
     v4f g0 = {0.f, 0.f, 0.f, 0.f}, g1 = g0;
@@ -749,10 +792,7 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
       g1 = *reinterpret_cast<const v4f*>(gp + 4);
     }
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      X[rt] = turn_read<SUB, false>(buf + s * 4096, turn, rt, g0, g1, 1.f);
-      rows[rt].add(X[rt].s[0]);
-    }
+    for (int rt = 0; rt < 2; ++rt) X[rt] = turn_read<SUB, false>(buf + s * 4096, turn, rt, g0, g1, 1.f);
     if (s == 0)
       step_products<true>(part, A.f, X);
     else
@@ -809,14 +849,6 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
   // quarter j = 2 rt + ct of the tile goes to wave j, which adds the four
   // waves' sums in wave order
   __syncthreads();
-  uint32_t* const seen = reinterpret_cast<uint32_t*>(smem + GOFF);  // [row tile][any, big][wave]
-  if (lane == 0) {
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      seen[8 * rt + w] = rows[rt].any32();
-      seen[8 * rt + 4 + w] = rows[rt].big32();
-    }
-  }
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -836,9 +868,15 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
 #pragma unroll
     for (int z = 0; z < 4; ++z) e[4 * r + z] = s[z];
   }
-  const uint32_t* const sn = seen + 8 * (w >> 1);
-  const uint32_t tiny_rows =
-      (sn[0] | sn[1] | sn[2] | sn[3]) & ~(sn[4] | sn[5] | sn[6] | sn[7]);
+  // as in store_tile
+  const float* const lim = reinterpret_cast<const float*>(limits) + 32 * (w & 1);
+  const uint64_t tiny_cols = __ballot(limits[64 + lane] != 0);
+  const uint64_t big = __ballot(fabsf(e[0]) > lim[4 * (lane >> 5)]);
+  uint32_t tiny_rows = 0;
+  if (__builtin_expect(~(uint32_t)(big | big >> 32), 0)) {
+    const RowSums sums = row_sums(e, lane, [&](int c) { return lim[c]; });
+    tiny_rows = sums.any & ~sums.big;
+  }
   const uint32_t bad = bad_sums(e) | tiny_sums(tiny_rows >> (lane & 31) & 1,
                                                (uint32_t)(tiny_cols >> 32 * (w & 1)), lane);
 #pragma unroll
@@ -846,7 +884,7 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
     put4<SORTED, false>(a, R.row0 + 32 * (w >> 1) + (lane & 31),
                  64 * cb + 32 * (w & 1) + 8 * j + 4 * (lane >> 5),
                  v4f{e[4 * j], e[4 * j + 1], e[4 * j + 2], e[4 * j + 3]});
-  if (__ballot(bad != 0)) {
+  if (__builtin_expect(__ballot(bad != 0) != 0, 0)) {
     __threadfence();  // as in store_tile
     redo_quarter<SUB, SORTED>(a, R, w >> 1, w & 1, cb, lane, bad);
   }
@@ -864,19 +902,18 @@ __global__ void __launch_bounds__(NT, 2) tile_split_kernel(TileArgs a, int nchun
 constexpr int FEW_C = 4, FEW_J = 96;
 
 // V(row, j) of the wave's tile: v[row * ldr + j * ldj], times sgn; zeroed first.
-// Returns the bits of the lane's row's values.
 // All channels of eight offsets' rows are on their way together: with a round
 // of loads for each channel, a layer of three channels waited three times
 // (3 -> 32 channels on 1.4M tetrahedral outputs, ten offsets: 350 -> 247 us).
 // REDO: a NaN is stored as any but ABSENT, which few_values fills in first.
 constexpr uint32_t ABSENT = 0xffffffffu;
 template <bool SORTED, int C, bool REDO>
-__device__ inline uint32_t few_rows(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
-                                    int ldj, float sgn, int lane) {
+__device__ inline void few_rows(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
+                                int ldj, float sgn, int lane) {
   float g[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) g[c] = a.sub[c];
-  uint32_t rest = R.U, bits = 0;
+  uint32_t rest = R.U;
   while (rest) {
     // eight offsets at a time, so that their loads overlap (past the last one
     // it is repeated: the same value again)
@@ -903,28 +940,24 @@ __device__ inline uint32_t few_rows(const TileArgs& a, const Rows<SORTED>& R, fl
         for (int c = 0; c < C; ++c) {
           const float d = sgn * (t[i][c] - g[c]);
           v[lane * ldr + (k[i] * C + c) * ldj] = REDO && d != d ? __uint_as_float(0x7fc00000u) : d;
-          bits |= __float_as_uint(d);
         }
       }
   }
-  return bits;
 }
 
 template <bool SORTED, bool REDO = false>
-__device__ inline uint32_t few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
+__device__ inline void few_values(const TileArgs& a, const Rows<SORTED>& R, float* v, int ldr,
                                   int ldj, int words, float sgn, int lane) {
   for (int i = lane; i < words / 4; i += 64)
     reinterpret_cast<v4u*>(v)[i] = REDO ? v4u{ABSENT, ABSENT, ABSENT, ABSENT} : v4u{0, 0, 0, 0};
   wave_sync();
-  uint32_t bits;
   switch (a.Rk) {
-    case 1: bits = few_rows<SORTED, 1, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 2: bits = few_rows<SORTED, 2, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    case 3: bits = few_rows<SORTED, 3, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
-    default: bits = few_rows<SORTED, 4, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 1: few_rows<SORTED, 1, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 2: few_rows<SORTED, 2, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    case 3: few_rows<SORTED, 3, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
+    default: few_rows<SORTED, 4, REDO>(a, R, v, ldr, ldj, sgn, lane); break;
   }
   wave_sync();
-  return bits;
 }
 
 __host__ __device__ constexpr int few_lds(int nst, int ncb) {
@@ -945,8 +978,7 @@ __global__ void __launch_bounds__(64 * WGW, 3) few_fwd_kernel(TileArgs a, int ns
   float* const ob = ncb == 1 ? v : v + 64 * ldr;
   Rows<SORTED> R;
   R.init(a, tile, lane);
-  const uint64_t tiny_rows =
-      __ballot(tiny_floats(few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane)));
+  few_values<SORTED>(a, R, v, ldr, 1, 64 * ldr, 1.f, lane);
   const int n32 = lane & 31, h = lane >> 5;
   for (int cb = 0; cb < ncb; ++cb) {
     const v4u* wp = reinterpret_cast<const v4u*>(a.Wp) + (int64_t)cb * nst * 384 + lane;
@@ -1010,8 +1042,7 @@ __global__ void __launch_bounds__(64 * WGW, 3) few_fwd_kernel(TileArgs a, int ns
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    store_tile<true, SORTED>(a, R, acc, tiny_rows, __ballot(column_tiny(a, cb, lane)), ob, cb,
-                             lane);
+    store_tile<true, SORTED>(a, R, acc, __ballot(column_tiny(a, cb, lane)), ob, cb, lane);
   }
 }
 
@@ -1157,18 +1188,19 @@ __global__ void __launch_bounds__(64 * WGW, JT == 1 ? 3 : 2) few_dw_kernel(FewAr
       }
     }
     __syncthreads();
-    auto tiny = [&](int t, int row) {
+    auto tiny = [&](int t) {
       const uint32_t* const sn = seen + 8 * t;
-      return ((sn[0] | sn[1] | sn[2] | sn[3]) & ~(sn[4] | sn[5] | sn[6] | sn[7])) >> row & 1;
+      return (sn[0] | sn[1] | sn[2] | sn[3]) & ~(sn[4] | sn[5] | sn[6] | sn[7]);
     };
-    const bool tc = tiny(tid >> 1 & 1, ((tid & 63) >> 2) + 16 * (tid & 1));
+    const bool tc = tiny(tid >> 1 & 1) >> (((tid & 63) >> 2) + 16 * (tid & 1)) & 1;
+    const uint32_t te = tiny(2 + jt);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = u * 256 + tid, j = 32 * jt + e / 64, co = co0 + (tid & 63);
       const float t = (red[e] - red[2048 + e]) + (red[4096 + e] - red[6144 + e]);
       if (j < f.J && co < f.Cout) {
         // a sum to be redone is marked by a NaN
-        const bool bad = !(t * 0.f == 0.f) || tc || tiny(2 + jt, e / 64);
+        const bool bad = !(t * 0.f == 0.f) || tc || (te >> e / 64 & 1);
         out[(int64_t)j * f.Cout + co] = bad ? __uint_as_float(0x7fc00000u) : t;
         odd = odd || bad;
       }
@@ -1263,11 +1295,11 @@ TileFn tile_fn(int tc, bool vec, bool sub, bool sorted, bool split) {
 
 int tile_steps(int Rk) { return (int)ceil_div(Rk, 16); }
 
-// Split weights, then a word per column (wtiny).
+// Split weights, then two words per column (wtiny).
 static size_t pack_words(int K, int Rk, int Nc) {
   return (size_t)K * ceil_div(Nc, 64) * tile_steps(Rk) * 1536;
 }
-size_t tile_pack_bytes(int K, int Rk, int Nc) { return (pack_words(K, Rk, Nc) + Nc) * 4; }
+size_t tile_pack_bytes(int K, int Rk, int Nc) { return (pack_words(K, Rk, Nc) + 2 * Nc) * 4; }
 const uint32_t* tile_wtiny(const uint32_t* Wp, int K, int Rk, int Nc) {
   return Wp + pack_words(K, Rk, Nc);
 }
@@ -1294,12 +1326,14 @@ scn_status launch_tile(const TileArgs& a, hipStream_t st) {
   const int64_t items = a.ntile * ncb;
   const bool split = items < TILE_SPLIT;
   const int tc = chunk_steps(a.Rk);
-  const size_t base = split ? 65536 : wg_lds(tc) + 64, smem = base + (size_t)nst * 64;
+  // (split: g_in from 65536, the columns' limits from 66560)
+  const size_t base = split ? 65536 : wg_lds(tc) + 64;
+  const size_t smem = split ? base + 1024 + 512 : base + (size_t)nst * 64;
   TileFn fn = tile_fn(tc, vec, a.subtract, a.nb != nullptr, split);
   static LdsLimit limits[2][2][3][2];
   if (scn_status rc = allow_lds(reinterpret_cast<const void*>(fn),
                                 limits[tc - 1][vec][a.nb ? 2 : a.subtract ? 1 : 0][split],
-                                base + 1024))  // its largest size
+                                base + 1024 + 512))  // its largest size
     return rc;
   const int64_t nwg = split ? items : ceil_div(a.ntile, WGW) * ncb;
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(split ? NT : 64 * WGW), smem, st, a, nst / tc,
